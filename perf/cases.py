@@ -1,0 +1,272 @@
+"""Workloads of the gist-attention library as its users run it, for timing.
+
+A case is a dict of plain values; its "kind" says which public entry points it goes through:
+
+  train     gist_attention (autograd): forward, then the backward of a given output gradient
+  pack      the same for documents packed along the token axis (gist_attention_varlen)
+  score     attn_fwd alone: a forward pass without gradients (evaluation, reward or log-likelihood scoring)
+  prefill   a prompt pushed through the compressed cache (KVCache.update + prefill_chunk), chunk by chunk
+  decode    one decoding step of a batch over the compressed cache in bf16
+  decode8   the same over a cache stored as E4M3 codes
+  generate  a batch with its prompts in the cache switches to the ring layout and decodes a few tokens
+
+q, k, v and dout are i.i.d. N(0, 1) rounded to bf16, like every workload of the package (attention cost does not depend
+on the data).
+"""
+import math
+
+import torch
+
+import paper_2509_15763_amd as u
+from paper_2509_15763_amd import synth
+
+DEV = "cuda"
+
+
+def listed():
+    return [
+        # the smallest layer in the package's tables: one head, 1K tokens; launches and host work are all there is
+        dict(name="train_1k_one_head", kind="train", B=1, Hq=1, Hkv=1, L=1024, D=64, r=4, W=128, sinks=0, units=False,
+             projected=False),
+        # fine-tuning on short samples: a small batch of sequences just under 2K tokens, a window of 128 raw tokens
+        dict(name="train_2k_batch", kind="train", B=2, Hq=32, Hkv=8, L=2047, D=128, r=4, W=128, sinks=0, units=False,
+             projected=False),
+        # the headline layer: one 32K-token sequence, grouped heads
+        dict(name="train_32k", kind="train", B=1, Hq=32, Hkv=8, L=32768, D=128, r=4, W=1024, sinks=0, units=False,
+             projected=False),
+        # a batch of 16K sequences at a high compression ratio, tensors as the projection layers leave them
+        # ([B, L, H, D] in memory, passed as [B, H, L, D] views)
+        dict(name="train_16k_batch_r16", kind="train", B=4, Hq=32, Hkv=8, L=16384, D=128, r=16, W=1024, sinks=0,
+             units=False, projected=True),
+        # 32K tokens packed from five documents in the paper's training layout: sinks in front of every document, a
+        # window counted in gist units
+        dict(name="train_pack_32k", kind="pack", Hq=32, Hkv=8, docs="8192,4100,12288,1020,7168", D=128, r=4, W=25,
+             sinks=128, units=True),
+        # long-context training: one 128K-token sequence
+        dict(name="train_128k", kind="train", B=1, Hq=32, Hkv=8, L=131072, D=128, r=8, W=2048, sinks=0, units=False,
+             projected=False),
+        # scoring a couple of 8K documents with a model of head dimension 64 (odd length: no padding in front of it)
+        dict(name="score_8k_d64", kind="score", B=2, Hq=16, Hkv=8, L=8001, D=64, r=8, W=512, sinks=0, units=False),
+        # prefill of a 32K prompt in 4096-token chunks
+        dict(name="prefill_32k_chunks", kind="prefill", B=1, Hq=32, Hkv=8, L=32768, chunk=4096, D=128, r=4, W=1024, sinks=0),
+        # interactive decoding: one sequence with a short history
+        dict(name="decode_1_short", kind="decode", B=1, Hq=32, Hkv=8, Lk=1500, D=128, ragged=False),
+        # serving: 64 sequences over 147K-token contexts (16384 gists + a window of 1024)
+        dict(name="decode_64_long", kind="decode", B=64, Hq=32, Hkv=8, Lk=17408, D=128, ragged=False),
+        # serving a mid-sized batch of sequences of different lengths from the 8-bit cache
+        dict(name="decode8_16_ragged", kind="decode8", B=16, Hq=32, Hkv=8, Lk=9001, D=128, ragged=True),
+        # the first tokens of a batch of eight after its prompts: ring layout, appends, decoding
+        dict(name="generate_8", kind="generate", B=8, Hq=32, Hkv=8, prompt=12000, D=128, r=4, W=1024, tokens=4),
+    ]
+
+
+# ---------------------------------------------------------------- drawn cases
+def _log(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+_HEADS = ((32, 8), (32, 8), (16, 4), (16, 16), (8, 1), (28, 4))
+
+
+def draw(rng):
+    """One more case of the ranges above; the sizes are redrawn until the pass costs no more than the largest listed."""
+    while True:
+        c = _draw(rng)
+        w = work(c)
+        if w["flops"] <= 60e12 and w["bytes"] <= 6e9 and _state_bytes(c) <= 20e9:
+            return c
+
+
+def _draw(rng):
+    kind = rng.choice(("train", "train", "train", "pack", "score", "prefill", "decode", "decode8", "generate"))
+    Hq, Hkv = rng.choice(_HEADS)
+    D = rng.choice((128, 128, 128, 64, 64, 96))
+    r = rng.choice((2, 4, 4, 8, 8, 16, 32))
+    if kind in ("train", "score", "pack"):
+        units = rng.random() < 0.35
+        W = _log(rng, 8, 200) if units else _log(rng, 64, 2048)
+        sinks = rng.choice((0, 4, 128)) if units else rng.choice((0, 0, 0, 64))
+        c = dict(kind=kind, Hq=Hq, Hkv=Hkv, D=D, r=r, W=W, sinks=sinks, units=units)
+        if kind == "pack":
+            docs = [_log(rng, 100, 12000) for _ in range(rng.randint(2, 40))]
+            c["docs"] = ",".join(map(str, docs))
+        else:
+            c["B"] = rng.choice((1, 1, 2, 3, 4, 8))
+            c["L"] = _log(rng, 300, 100000)
+            if kind == "train":
+                c["projected"] = rng.random() < 0.3
+        return c
+    if kind == "prefill":
+        return dict(kind=kind, B=rng.choice((1, 1, 2, 4)), Hq=Hq, Hkv=Hkv, L=_log(rng, 1000, 60000),
+                    chunk=_log(rng, 512, 8192), D=D, r=r, W=_log(rng, 128, 2048), sinks=rng.choice((0, 0, 128)))
+    if kind == "generate":
+        return dict(kind=kind, B=_log(rng, 1, 32), Hq=Hq, Hkv=Hkv, prompt=_log(rng, 300, 30000), D=D, r=r,
+                    W=_log(rng, 128, 2048), tokens=rng.randint(1, 8))
+    return dict(kind=kind, B=_log(rng, 1, 128), Hq=Hq, Hkv=Hkv, Lk=_log(rng, 200, 40000), D=D, ragged=rng.random() < 0.6)
+
+
+# ---------------------------------------------------------------- sizes
+def _mode(case):
+    return u.UNIGIST_WINDOW_UNITS if case["units"] else u.UNIGIST_WINDOW_SLIDING
+
+
+def _docs(case):
+    return [int(x) for x in case["docs"].split(",")]
+
+
+def _lens(case):
+    """Cache rows in use per sequence of a decode case: the whole slab, or spread from a sixteenth of it upwards."""
+    B, Lk = case["B"], case["Lk"]
+    if not case["ragged"]:
+        return [Lk] * B
+    return [max(1, round(Lk * (1.0 - (15.0 / 16.0) * ((7 * b + 3) % B) / B))) for b in range(B)]
+
+
+def _prompts(case):
+    """Prompt lengths of a generate case: the longest first, down to about half of it."""
+    return [max(1, case["prompt"] - b * (case["prompt"] // (2 * case["B"]))) for b in range(case["B"])]
+
+
+def _state_bytes(case):
+    k = case["kind"]
+    if k in ("decode", "decode8"):
+        return 2 * case["B"] * case["Hkv"] * case["Lk"] * case["D"] * 2
+    if k == "generate":
+        return 6 * case["B"] * case["Hkv"] * case["prompt"] * case["D"] * 2
+    n = sum(_docs(case)) if k == "pack" else case["B"] * case["L"]
+    return (3 * case["Hq"] + 4 * case["Hkv"]) * n * case["D"] * 2
+
+
+def work(case):
+    """What one pass cannot do without: every input read once, every output written once; 4 D flops per visible (query,
+    key) pair forward, 10 D backward."""
+    k = case["kind"]
+    Hq, Hkv, D = case["Hq"], case["Hkv"], case["D"]
+    if k in ("train", "pack", "score"):
+        mask = (case["r"], case["W"], case["sinks"], _mode(case))
+        if k == "pack":
+            tokens = sum(_docs(case))
+            pairs = sum(u.n_vis(n, *mask) for n in _docs(case)) * Hq
+        else:
+            tokens = case["B"] * case["L"]
+            pairs = u.n_vis(case["L"], *mask) * Hq * case["B"]
+        if k == "score":
+            return {"bytes": (2 * Hq + 2 * Hkv) * tokens * D * 2 + 4 * Hq * tokens, "flops": 4 * D * pairs}
+        return {"bytes": (4 * Hq + 4 * Hkv) * tokens * D * 2, "flops": 14 * D * pairs}
+    if k == "prefill":
+        pairs = u.n_vis(case["L"], case["r"], case["W"], case["sinks"]) * Hq * case["B"]
+        tokens = case["B"] * case["L"]
+        return {"bytes": (2 * Hq + 2 * Hkv) * tokens * D * 2 + 4 * Hq * tokens, "flops": 4 * D * pairs}
+    if k == "generate":
+        byts = flops = 0
+        for n in _prompts(case):
+            for t in range(case["tokens"]):
+                rows = u.unigist_cache_ring_rows(n + t, case["r"], case["W"])
+                byts += 2 * Hkv * rows * D * 2 + 2 * Hq * D * 2 + 4 * Hkv * D * 2
+                flops += 4 * Hq * rows * D
+        return {"bytes": byts, "flops": flops}
+    keys = sum(_lens(case))
+    eb = 1 if k == "decode8" else 2
+    return {"bytes": 2 * Hkv * keys * D * eb + case["B"] * Hq * (4 * D + 4), "flops": 4 * Hq * keys * D}
+
+
+def tolerance(case):
+    """Measured against a float64 reference (sequences of 333 to 5001 tokens, head dimensions 64, 96 and 128), results
+    differ in the 2-norm by 2.0e-3 to 2.2e-3 (out) and 2.3e-3 to 2.5e-3 (gradients): operands, P and dS rounded to bf16
+    before a contraction, and the stored bf16 result.  Implementations that round alike at other places stay within
+    four times that."""
+    return {"rel": 1e-2}
+
+
+# ---------------------------------------------------------------- inputs and passes
+def _randn(gen, *shape):
+    return torch.randn(*shape, generator=gen, device=DEV, dtype=torch.float32).to(torch.bfloat16)
+
+
+def prepare(case, seed):
+    k = case["kind"]
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    Hq, Hkv, D = case["Hq"], case["Hkv"], case["D"]
+    st = {"case": case}
+    if k in ("train", "score"):
+        B, L = case["B"], case["L"]
+        shape = (lambda H: (B, L, H, D)) if case.get("projected") else (lambda H: (B, H, L, D))
+        view = (lambda t: t.transpose(1, 2)) if case.get("projected") else (lambda t: t)
+        q, kk, v = (_randn(gen, *shape(H)) for H in (Hq, Hkv, Hkv))
+        if k == "train":
+            st["dout"] = view(_randn(gen, *shape(Hq)))
+            st["q"], st["k"], st["v"] = (view(t).detach().requires_grad_() for t in (q, kk, v))
+        else:
+            st["q"], st["k"], st["v"] = q, kk, v
+    elif k == "pack":
+        docs = _docs(case)
+        T = sum(docs)
+        st["cu"] = [sum(docs[:i]) for i in range(len(docs) + 1)]
+        st["q"], st["k"], st["v"] = (_randn(gen, H, T, D).requires_grad_() for H in (Hq, Hkv, Hkv))
+        st["dout"] = _randn(gen, Hq, T, D)
+    elif k == "prefill":
+        B, L, W, r = case["B"], case["L"], case["W"], case["r"]
+        st["q"], st["k"], st["v"] = (_randn(gen, B, H, L, D) for H in (Hq, Hkv, Hkv))
+        cap = min(L, W + case["chunk"]) + L // (r + 1) + case["sinks"] + 8
+        st["cache"] = u.KVCache(B, Hkv, cap, D, r, sinks=case["sinks"])
+        st["out"] = torch.empty_like(st["q"])
+        st["lse"] = torch.empty(B, Hq, L, device=DEV, dtype=torch.float32)
+    elif k in ("decode", "decode8"):
+        B, Lk = case["B"], case["Lk"]
+        st["q"] = _randn(gen, B, Hq, D)
+        kv = [torch.empty(B, Hkv, Lk, D, device=DEV, dtype=torch.bfloat16) for _ in range(2)]
+        for t in kv:
+            for b in range(B):
+                t[b] = _randn(gen, Hkv, Lk, D)
+        st["lens"] = torch.tensor(_lens(case), dtype=torch.int32, device=DEV) if case["ragged"] else None
+        if k == "decode8":
+            st["ks"], st["vs"] = synth.e4m3_scales(Hkv, seed=seed, device=DEV)
+            kv = [u.quantize_e4m3(t, s) for t, s in zip(kv, (st["ks"], st["vs"]))]
+        st["kc"], st["vc"] = kv
+        # a serving loop keeps the split-K workspace of its batch
+        st["ws"] = torch.empty(u.unigist_decode_workspace(B, Hq, Hkv, Lk, D, u.UNIGIST_BF16), device=DEV, dtype=torch.uint8)
+    else:
+        B, T, W, r = case["B"], case["tokens"], case["W"], case["r"]
+        n = _prompts(case)
+        cap = u.unigist_cache_ring_rows(max(n) + T, r, W) + 8
+        cap = max(cap, max(u.unigist_cache_rows(u.unigist_window_start(x - 1, r, W), x - 1, r) for x in n))
+        st["ragged"] = u.RaggedKVCache(B, Hkv, cap, D, r)
+        kp, vp = _randn(gen, B, Hkv, max(n), D), _randn(gen, B, Hkv, max(n), D)
+        st["ragged"].update_batch(kp, vp, n, [u.unigist_window_start(x - 1, r, W) for x in n])
+        st["q"] = [_randn(gen, B, Hq, D) for _ in range(T)]
+        st["k"] = [_randn(gen, B, Hkv, 1, D) for _ in range(T)]
+        st["v"] = [_randn(gen, B, Hkv, 1, D) for _ in range(T)]
+    return st
+
+
+def run(st):
+    case = st["case"]
+    k = case["kind"]
+    if k == "train":
+        out = u.gist_attention(st["q"], st["k"], st["v"], case["r"], case["W"], sinks=case["sinks"], window_mode=_mode(case))
+        return (out.detach(),) + torch.autograd.grad(out, (st["q"], st["k"], st["v"]), st["dout"])
+    if k == "pack":
+        out = u.gist_attention_varlen(st["q"], st["k"], st["v"], case["r"], case["W"], st["cu"], sinks=case["sinks"],
+                                      window_mode=_mode(case))
+        return (out.detach(),) + torch.autograd.grad(out, (st["q"], st["k"], st["v"]), st["dout"])
+    if k == "score":
+        return u.attn_fwd(st["q"], st["k"], st["v"], case["r"], case["W"], sinks=case["sinks"], window_mode=_mode(case))
+    if k == "prefill":
+        cache, q, out, lse = st["cache"], st["q"], st["out"], st["lse"]
+        L, C, W, r = case["L"], case["chunk"], case["W"], case["r"]
+        cache.cur, cache.s, cache.t = 0, 0, -1  # a new prompt in the same buffers
+        for p0 in range(0, L, C):
+            p1 = min(L, p0 + C)
+            cache.update(st["k"][:, :, p0:p1], st["v"][:, :, p0:p1], u.unigist_window_start(p0, r, W, case["sinks"]))
+            u.prefill_chunk(q[:, :, p0:p1], cache, r, W, p0, out=out[:, :, p0:p1], lse=lse[:, :, p0:p1])
+        return out, lse
+    if k == "decode":
+        return u.decode(st["q"], st["kc"], st["vc"], st["lens"], workspace=st["ws"])
+    if k == "decode8":
+        return u.decode_e4m3(st["q"], st["kc"], st["vc"], st["ks"], st["vs"], st["lens"], workspace=st["ws"])
+    ring = u.RingKVCache(st["ragged"], case["W"])
+    outs = []
+    for q, kn, vn in zip(st["q"], st["k"], st["v"]):
+        rows = ring.append(kn, vn)
+        outs.append(u.decode(q, ring.kc, ring.vc, rows))
+    return outs
