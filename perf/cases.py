@@ -270,3 +270,99 @@ def run(st):
         rows = ring.append(kn, vn)
         outs.append(u.decode(q, ring.kc, ring.vc, rows))
     return outs
+
+
+# ---------------------------------------------------------------- the same results in 64 bits
+def _visible(i, j, r, W, sinks, units):
+    """Mask [len(i), len(j)] of the visible pairs: causal, and the key is a sink, a gist or inside the query's window."""
+    d = i[:, None] - j[None, :]
+    always = (j < sinks) | ((j >= sinks) & ((j - sinks + 1) % (r + 1) == 0))
+    if units:
+        unit = lambda p: torch.div(p - sinks, r + 1, rounding_mode="floor")
+        near = (unit(j)[None, :] >= unit(i)[:, None] - W) & (j >= sinks)[None, :]
+    else:
+        near = d < W
+    return (d >= 0) & (always[None, :] | near)
+
+
+def _exact_attention(q, k, v, dout, r, W, sinks, units):
+    """Masked softmax attention and its gradients in float64, over blocks of query rows and the keys a block can see."""
+    B, Hq, L, D = q.shape
+    Hkv, G = k.shape[1], Hq // k.shape[1]
+    scale = 1.0 / math.sqrt(D)
+    k, v = k.detach().double(), v.detach().double()
+    q = q.detach().reshape(B, Hkv, G, L, D)
+    pos = torch.arange(L, device=q.device)
+    out = torch.empty(B, Hkv, G, L, D, device=q.device, dtype=torch.float64)
+    lse = torch.empty(B, Hkv, G, L, device=q.device, dtype=torch.float64)
+    if dout is not None:
+        dout = dout.reshape(B, Hkv, G, L, D)
+        dq, dk, dv = torch.empty_like(out), torch.zeros_like(k), torch.zeros_like(v)
+    reach = min(L, sinks + L // (r + 1) + (W + 1) * (r + 1 if units else 1))
+    rows = max(16, min(1024, int(2e8 / (B * Hq * reach))))
+    for i0 in range(0, L, rows):
+        i = pos[i0:i0 + rows]
+        n = i.numel()
+        seen = _visible(i, pos[:i0 + n], r, W, sinks, units)
+        j = seen.any(0).nonzero()[:, 0]
+        seen = seen[:, j].repeat(G, 1)
+        kj, vj = k[:, :, j], v[:, :, j]
+        qi = q[..., i0:i0 + n, :].double().reshape(B, Hkv, G * n, D)
+        s = (qi @ kj.transpose(2, 3)).mul_(scale).masked_fill_(~seen, -math.inf)
+        l = torch.logsumexp(s, 3, keepdim=True)
+        p = s.sub_(l).exp_()
+        o = p @ vj
+        out[..., i0:i0 + n, :] = o.view(B, Hkv, G, n, D)
+        lse[..., i0:i0 + n] = l.view(B, Hkv, G, n)
+        if dout is None:
+            continue
+        do = dout[..., i0:i0 + n, :].double().reshape(B, Hkv, G * n, D)
+        dv.index_add_(2, j, p.transpose(2, 3) @ do)
+        ds = (do @ vj.transpose(2, 3)).sub_((do * o).sum(3, keepdim=True)).mul_(p).mul_(scale)
+        dq[..., i0:i0 + n, :] = (ds @ kj).view(B, Hkv, G, n, D)
+        dk.index_add_(2, j, ds.transpose(2, 3) @ qi)
+    out, lse = out.view(B, Hq, L, D), lse.view(B, Hq, L)
+    return (out, lse) if dout is None else (out, dq.view(B, Hq, L, D), dk, dv)
+
+
+def _exact_decode(q, k, v):
+    """One query per head over all of [Hkv, n, D]: out [Hq, D], lse [Hq] in float64."""
+    Hkv, D = k.shape[0], k.shape[2]
+    s = q.double().view(Hkv, -1, D) @ k.double().transpose(1, 2) / math.sqrt(D)
+    l = torch.logsumexp(s, 2, keepdim=True)
+    return ((s - l).exp() @ v.double()).view(-1, D), l.view(-1)
+
+
+def exact(case, seed):
+    st = prepare(case, seed)
+    k = case["kind"]
+    if k in ("train", "score", "prefill"):
+        return _exact_attention(st["q"], st["k"], st["v"], st.get("dout"), case["r"], case["W"], case["sinks"],
+                                case.get("units", False))
+    if k == "pack":
+        parts = []
+        for a, b in zip(st["cu"][:-1], st["cu"][1:]):
+            q, kk, v, do = (st[n][None, :, a:b] for n in ("q", "k", "v", "dout"))
+            parts.append(_exact_attention(q, kk, v, do, case["r"], case["W"], case["sinks"], case["units"]))
+        return tuple(torch.cat(t, 2)[0] for t in zip(*parts))
+    pairs = lambda res: tuple(torch.stack(t) for t in zip(*res))
+    if k in ("decode", "decode8"):
+        kc, vc = st["kc"], st["vc"]
+        if k == "decode8":
+            wide = lambda c, s: c.view(torch.float8_e4m3fn).float() * s.view(-1, 1, 1)
+            kc, vc = ([wide(t[b], s) for b in range(case["B"])] for t, s in ((kc, st["ks"]), (vc, st["vs"])))
+        return pairs(_exact_decode(st["q"][b], kc[b][:, :n], vc[b][:, :n]) for b, n in enumerate(_lens(case)))
+    # generate: the prompts' own keys are the first draws of the seed, after them come the tokens'
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    n = _prompts(case)
+    kp, vp = (_randn(gen, case["B"], case["Hkv"], max(n), case["D"]) for _ in range(2))
+    outs = []
+    for t in range(case["tokens"]):
+        res = []
+        for b, nb in enumerate(n):
+            pos = torch.arange(nb + t + 1, device=DEV)
+            j = _visible(pos[-1:], pos, case["r"], case["W"], 0, False)[0]
+            rows = lambda p, new: torch.cat([p[b, :, :nb]] + [x[b] for x in new[:t + 1]], 1)[:, j]
+            res.append(_exact_decode(st["q"][t][b], rows(kp, st["k"]), rows(vp, st["v"])))
+        outs.append(pairs(res))
+    return outs
