@@ -56,11 +56,25 @@ long gist_chunk_steps(const AttnShape& s) {
 }
 
 // Segment length (query chunks per gist-phase workgroup) for a launch with `steps` chunk steps in total over all
-// (batch, kv head) pairs: 32 chunks (x Hq/Hkv heads = 128 steps per workgroup) balance the last round of a 32K
-// sequence; a launch that could not give the 512 workgroup slots of the chip (2 per CU) about five such rounds
-// gets segments of 16 (one 8K sequence: 10 % faster, a 32K pack of five documents: 2 %; 8 and 4 were no better,
-// their partial sums cost what the balance gains).
-int pick_segc(long steps) { return steps / (512 * 5) >= 32 ? 32 : 16; }
+// (batch, kv head) pairs.  A workgroup of segc chunks walks segc * Hq/Hkv steps one after the other, so a launch that
+// does not fill the chip's 512 workgroup slots (2 per CU) takes as long as its longest workgroup and wants short
+// segments; a launch of many rounds wants long ones, whose fp32 partial sums (128 KB per workgroup at D = 128, written
+// and read back once) are fewer.  Measured, gist phase + reduction in us, segments of 2 / 4 / 8 / 16 / 32 chunks:
+//   816 steps (2 x 2047 tokens, r 4, W 128)   58 /   62 /   92 /  152 /  248     (16 was the shortest before)
+//   1300      (4096, W 512)                   83 /   76 /   95 /  152 /  278
+//   5400      (8192, W 1024)                 220 /  219 /  198 /  207 /  279
+//   10900     (8192, r 2, W 128)             441 /  433 /  361 /  356 /  375
+//   23000     (16384, W 1024)                785 /  787 /  791 /  729 /  745
+//   104000    (32768, W 1024)               2806 / 2816 / 2842 / 2833 / 2690
+// The lines lie where neighbours cross: half a round of 512 such workgroups for the short ones, three quarters for
+// 16, five rounds for 32.
+int pick_segc(long steps) {
+    const long slots = 512;
+    if (steps >= slots * 32 * 5) return 32;
+    if (steps >= slots * 16 * 3 / 4) return 16;
+    if (steps >= slots * 8 / 2) return 8;
+    return steps >= slots * 4 / 2 ? 4 : 2;
+}
 
 BwdPlan make_plan(const AttnShape& s) {
     BwdPlan p;
