@@ -12,7 +12,7 @@
 //   3. gist_reduce_kernel   sums the segments of a gist tile in a fixed order
 //   4. dkdv_kernel<WINDOW>  one workgroup per contiguous 128-key tile: the pairs of the window phase; its
 //                           epilogue adds the reduced gist-phase sums to the gist rows and writes dK, dV
-//   5. dq_kernel            one workgroup per 128-query tile, same tile walk as the forward
+//   5. dq_kernel            one workgroup per four units of 32 query rows of a head, same tile walk as the forward
 // Every (query, key) pair is handled by exactly one of the two dkdv phases: a query chunk c (64 rows) sees
 // the sinks and gists at positions < far(c) = floor(win_lo(64c) / 128) * 128 in the gist phase (win_lo = first
 // position of a row's local window) and every key >= far(c) in the window phase.
@@ -37,7 +37,6 @@ namespace unigist {
 namespace {
 
 constexpr int NT = 256;
-constexpr int BMQ = kDqBm;  // query rows per dq workgroup
 constexpr int BNQ = kDqBn;  // keys per dq step
 constexpr int PFS = 2, PFT = 2;  // dq: LDS fragment reads issued this many MFMA groups ahead (S/dP phase, dQ phase)
 constexpr float kLog2e = 1.4426950408889634f;
@@ -642,7 +641,7 @@ __global__ __launch_bounds__(NT, 2) void dq_kernel(const bf16_t* __restrict__ q,
         const int d = doc_of_block(docs, n);
         n -= docs.blk0[d];
         s = doc_view(s, docs.len[d]);
-        nq = (s.L + BMQ - 1) / BMQ;
+        nq = row_units(s.L, s.Hq / s.Hkv).per;
         const size_t ro = (size_t)docs.c0[d] * (QSTR ? s.D : D);
         const size_t qro = QSTR ? (size_t)docs.c0[d] * s.q_rs : ro;
         q += qro;
@@ -660,25 +659,27 @@ __global__ __launch_bounds__(NT, 2) void dq_kernel(const bf16_t* __restrict__ q,
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int g4 = lane >> 4;  // with r16 = lane % 16: the lane's place in a 16x16x32 operand
+    // four units of 32 rows of one query head each, one per wave (plan.h), as in the forward
     const int G = s.Hq / s.Hkv, NP = s.B * s.Hkv;
-    int g, pr, qt;
+    int pr, wt;
     if ((NP & 7) == 0) {
-        const int xcd = n & 7, mm = n >> 3;
-        g = mm % G;
-        const int rest = mm / G;
-        const int pb = rest % (NP >> 3);
-        qt = nq - 1 - rest / (NP >> 3);
-        pr = xcd + 8 * pb;
+        const int mm = n >> 3;
+        pr = (n & 7) + 8 * (mm % (NP >> 3));
+        wt = nq - 1 - mm / (NP >> 3);
     } else {
-        g = n % G;
-        const int rest = n / G;
-        pr = rest % NP;
-        qt = nq - 1 - rest / NP;
+        pr = n % NP;
+        wt = nq - 1 - n / NP;
     }
-    const int b = pr / s.Hkv, hk = pr % s.Hkv, hq = hk * G + g;
     const int L = s.L, rp1 = s.rp1;
-    const int i0 = qt * BMQ, i1 = min(L, i0 + BMQ) - 1;
-    const int wrow0 = i0 + 32 * w;  // first row of the wave; the lane's two rows are wrow0 + 16 qb + r16
+    const int nu = row_units(L, G).n;
+    const int u0 = wt * kUnitsPerWg;
+    const int wv = __builtin_amdgcn_readfirstlane(w);
+    const bool live = u0 + wv < nu;  // the last workgroup may have waves without a unit: they only stage
+    const int u = live ? u0 + wv : nu - 1;
+    const int b = pr / s.Hkv, hk = pr % s.Hkv, hq = hk * G + u % G;
+    const int i0 = u0 / G * kWaveRows;                                       // the workgroup's first and last row
+    const int i1 = min(L, (min(u0 + kUnitsPerWg, nu) - 1) / G * kWaveRows + kWaveRows) - 1;
+    const int wrow0 = u / G * kWaveRows;  // first row of the wave; the lane's two rows are wrow0 + 16 qb + r16
     const int Dt = QSTR ? s.D : D;  // elements per row in memory (see dkdv_kernel)
     const char* kbytes = (const char*)(k + ((size_t)b * s.Hkv + hk) * s.kvhs * Dt);
     const char* vbytes = (const char*)(v + ((size_t)b * s.Hkv + hk) * s.kvhs * Dt);
@@ -737,7 +738,6 @@ __global__ __launch_bounds__(NT, 2) void dq_kernel(const bf16_t* __restrict__ q,
 
     // ---- staging (same scheme as the forward kernel)
     const int lrow = lane / CH;
-    const int wv = __builtin_amdgcn_readfirstlane(w);
     int choff[IPW];
 #pragma unroll
     for (int i = 0; i < IPW; ++i) {
@@ -888,7 +888,7 @@ __global__ __launch_bounds__(NT, 2) void dq_kernel(const bf16_t* __restrict__ q,
 
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb)
-        if (qrow[qb] < L) {
+        if (live && qrow[qb] < L) {
             bf16_t* op = dq + rowoff[qb] + 4 * g4;
 #pragma unroll
             for (int db = 0; db < DB; ++db) {
@@ -944,8 +944,8 @@ hipError_t bwd_launch(const bf16_t* q, const bf16_t* k, const bf16_t* v, const b
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if (!(stages & UNIGIST_BWD_DQ)) return hipSuccess;
-    const int nq = (s.L + BMQ - 1) / BMQ;
-    const long nblk = (long)nq * s.Hq * s.B;
+    const int nq = row_units(s.L, s.Hq / s.Hkv).per;
+    const long nblk = (long)nq * s.Hkv * s.B;
     if (nblk > 0x7fffffffL) return hipErrorInvalidValue;
     if (qstr) {
         if (gen) dq_kernel<D, true, false, true><<<dim3((unsigned)nblk), NT, 0, st>>>(q, k, v, lse2, dout, delta, dq, s, nq, NoDocs{});
@@ -1070,7 +1070,7 @@ hipError_t bwd_launch_pack(const bf16_t* q, const bf16_t* k, const bf16_t* v, co
                        else gen ? go(dkdv_kernel<D, false, true, true>) : go(dkdv_kernel<D, false, false, true>);
                    });
     if (e != hipSuccess) return e;
-    return for_chunks([&](int len) { return (long)((len + BMQ - 1) / BMQ) * s.Hq; },
+    return for_chunks([&](int len) { return (long)row_units(len, s.Hq / s.Hkv).per * s.Hkv; },
                       [&](const DocTab& t, unsigned nblk) {
                           auto go = [&](auto kern) { kern<<<dim3(nblk), NT, 0, st>>>(q, k, v, lse2, dout, delta, dq, s, 0, t); };
                           if (qstr) gen ? go(dq_kernel<D, true, true, true>) : go(dq_kernel<D, false, true, true>);

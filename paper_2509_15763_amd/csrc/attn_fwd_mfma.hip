@@ -9,7 +9,8 @@
 //   2. the contiguous key tiles from the window's first tile to the diagonal, where the
 //      full predicate is applied only on tiles that can contain an invisible pair.
 //
-// Work split: one workgroup = 128 query rows of one head, 4 waves x 32 rows; 32 keys per step.
+// Work split: one workgroup = four units of 32 query rows of one head each (with groups of four heads: the same 32
+// rows of the four heads of a kv head), one per wave; 32 keys per step.
 // The matrix instruction is v_mfma_f32_16x16x32_bf16 (D = A * B + C, A 16 x 32, B 32 x 16).  With r16 = lane % 16
 // and g4 = lane / 16:
 //   A: lane holds A[r16][8 g4 .. 8 g4 + 7]      B: lane holds B[8 g4 .. 8 g4 + 7][r16]
@@ -37,7 +38,6 @@
 namespace unigist {
 namespace {
 
-constexpr int BM = kFwdBm;  // query rows per workgroup
 constexpr int BN = kFwdBn;  // keys per step
 constexpr int NT = 256;  // threads
 constexpr float kLazy = 8.f;  // slack of the softmax reference, in exp2 units
@@ -78,7 +78,7 @@ __global__ __launch_bounds__(NT, 3) void fwd_mfma_kernel(const bf16_t* __restric
         const int d = doc_of_block(ext, n);
         n -= ext.blk0[d];
         s = doc_view(s, ext.len[d]);
-        nq = (s.L + BM - 1) / BM;
+        nq = row_units(s.L, s.Hq / s.Hkv).per;
         const size_t ro = (size_t)ext.c0[d] * s.D;
         const size_t qro = s.q_rs ? (size_t)ext.c0[d] * s.q_rs : ro;  // q and out may have explicit strides
         q += qro;
@@ -98,28 +98,23 @@ __global__ __launch_bounds__(NT, 3) void fwd_mfma_kernel(const bf16_t* __restric
     const int lane = tid & 63, w = tid >> 6;
     const int r16 = lane & 15, g4 = lane >> 4;  // MFMA 16x16x32: lane = (row or column r16, k-group g4)
 
-    // ---- which (batch, head, query tile): heads of one kv group stay on one XCD, long tiles first
+    // ---- which (batch, kv head) and which four units of it (plan.h: a unit is 32 rows of one query head): a kv head
+    // stays on one XCD, long walks first
     const int G = s.Hq / s.Hkv;
     const int NP = s.B * s.Hkv;
-    int g, pr, qt;
+    int pr, wt;
     if ((NP & 7) == 0) {
-        const int xcd = n & 7, mm = n >> 3;
-        g = mm % G;
-        const int rest = mm / G;
-        const int pb = rest % (NP >> 3);
-        qt = nq - 1 - rest / (NP >> 3);
-        pr = xcd + 8 * pb;
+        const int mm = n >> 3;
+        pr = (n & 7) + 8 * (mm % (NP >> 3));
+        wt = nq - 1 - mm / (NP >> 3);
     } else {
-        g = n % G;
-        const int rest = n / G;
-        pr = rest % NP;
-        qt = nq - 1 - rest / NP;
+        pr = n % NP;
+        wt = nq - 1 - n / NP;
     }
     const int b = pr / s.Hkv, hk = pr % s.Hkv;
-    const int hq = hk * G + g;
     if constexpr (MODE == RAGGED) {
         // The sequence's state comes from device memory, so it is checked here: a workgroup of a sequence whose
-        // state is invalid, or whose tile lies past the sequence's rows, leaves (the whole workgroup, before any
+        // state is invalid, or whose units lie past the sequence's rows, leaves (the whole workgroup, before any
         // barrier); one workgroup per sequence reports the cache rows in use, or -1.
         const int p0 = ext.p0[b], nb = ext.n[b], s0b = ext.s0[b];
         int rows = -1;
@@ -135,17 +130,23 @@ __global__ __launch_bounds__(NT, 3) void fwd_mfma_kernel(const bf16_t* __restric
                 }
             }
         }
-        if (hq == 0 && qt == nq - 1 && threadIdx.x == 0) ext.rows[b] = rows;
-        if (rows < 0 || qt * BM >= nb) return;
+        if (hk == 0 && wt == nq - 1 && threadIdx.x == 0) ext.rows[b] = rows;
+        if (rows < 0 || wt >= row_units(nb, G).per) return;
     }
 
     // Positions are absolute; q/out/lse hold the rows qpos0 .. L-1, K/V hold ngb compact gist rows followed
     // by the positions s0 .. L-1 (training: everything from position 0, no compact rows).
     const int L = s.L, rp1 = s.rp1, Dt = s.D;
     const int qpos0 = s.qpos0, s0 = s.s0, ngb = s.ngb;
-    const int i0 = qpos0 + qt * BM;
-    const int i1 = min(L, i0 + BM) - 1;
-    const int wrow0 = i0 + 32 * w;           // first row of the wave
+    const int nu = row_units(s.Lq, G).n;
+    const int u0 = wt * kUnitsPerWg;
+    const int wv = __builtin_amdgcn_readfirstlane(w);
+    const bool live = u0 + wv < nu;          // the last workgroup may have waves without a unit: they only stage
+    const int u = live ? u0 + wv : nu - 1;
+    const int hq = hk * G + u % G;
+    const int i0 = qpos0 + u0 / G * kWaveRows;                                // the workgroup's first and last row
+    const int i1 = min(L, qpos0 + (min(u0 + kUnitsPerWg, nu) - 1) / G * kWaveRows + kWaveRows) - 1;
+    const int wrow0 = qpos0 + u / G * kWaveRows;  // first row of the wave
     int qrow[2], qrow_ld[2];                 // this lane's two query rows (16-row blocks qb = 0, 1)
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
@@ -193,7 +194,6 @@ __global__ __launch_bounds__(NT, 3) void fwd_mfma_kernel(const bf16_t* __restric
 
     // ---- staging: direct global->LDS loads; lane fetches chunk (lane % CH) ^ swz(row) of its row.
     const int lrow = lane / CH;
-    const int wv = __builtin_amdgcn_readfirstlane(w);
     int choff[IPW];  // byte offset of the lane's (swizzled) chunk inside its row, per load slot
 #pragma unroll
     for (int i = 0; i < IPW; ++i) {
@@ -401,7 +401,7 @@ __global__ __launch_bounds__(NT, 3) void fwd_mfma_kernel(const bf16_t* __restric
         lt += __shfl_xor(lt, 32, 64);
         float inv = 1.f / lt;
         if (s.vscale) inv *= s.vscale[hk];  // the stored values stand for V * vscale
-        if (qrow[qb] < L) {
+        if (live && qrow[qb] < L) {
             const size_t orow = ((size_t)b * s.Hq + hq) * s.qhs + (qrow[qb] - qpos0);
             const size_t ooff = s.q_rs ? (size_t)b * s.q_bs + (size_t)hq * s.q_hs + (size_t)(qrow[qb] - qpos0) * s.q_rs : orow * Dt;
             bf16_t* op = out + ooff + 4 * g4;
@@ -420,14 +420,33 @@ __global__ __launch_bounds__(NT, 3) void fwd_mfma_kernel(const bf16_t* __restric
 
 }  // namespace
 
+// Unused LDS to ask for so that two workgroups share a CU instead of three, where that ends a launch earlier.  At
+// D = 128 the time in which a CU finishes one, two or three workgroups that run together is about 0.52 : 0.66 : 1
+// (4096-row chunks of the 32/8-head layer over 24K tokens: 145, 184, 278 us): two at a time are as fast per workgroup
+// as three, and when all walks are about equally long a launch ends with its last, partly filled round.  So 1024
+// workgroups take 3 + 1 per CU (measured 408 us) or 2 + 2 (367 us).  Walks of different lengths (a whole sequence
+// from its first token) fill the last round by themselves and keep three.
+unsigned lds_for_two_per_cu(const AttnShape& s, int nq, long nblk) {
+    if (s.D <= 64) return 0;
+    const int first = row_walk(s, s.qpos0, s.qpos0 + std::min(kWaveRows, s.Lq) - 1, BN).steps();
+    const int last = row_walk(s, s.L - 1, s.L - 1, BN).steps();
+    if (nq > 1 && first < 0.75 * last) return 0;
+    auto cost = [nblk](int per_cu, double full_round) {
+        const long rem = nblk % (256 * per_cu);
+        return (double)(nblk / (256 * per_cu)) * full_round + (rem == 0 ? 0. : rem <= 256 ? 0.52 : rem <= 512 ? 0.66 : 1.);
+    };
+    return cost(2, 0.66) < 0.97 * cost(3, 1.) ? 24 * 1024 : 0;
+}
+
 hipError_t launch_fwd_mfma(const void* q, const void* k, const void* v, void* out, float* lse, const AttnShape& s,
                            hipStream_t st) {
-    const int nq = (s.Lq + BM - 1) / BM;
-    const long nblk = (long)nq * s.Hq * s.B;
+    const int nq = row_units(s.Lq, s.Hq / s.Hkv).per;
+    const long nblk = (long)nq * s.Hkv * s.B;
     if (nblk > 0x7fffffffL) return hipErrorInvalidValue;
     const bool gen = s.S != 0 || s.umode != 0;
+    const unsigned lds = lds_for_two_per_cu(s, nq, nblk);
     auto go = [&](auto kern) {
-        kern<<<dim3((unsigned)nblk), NT, 0, st>>>((const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)out, lse,
+        kern<<<dim3((unsigned)nblk), NT, lds, st>>>((const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)out, lse,
                                                   s, nq, NoDocs{});
     };
     if (s.D <= 64) gen ? go(fwd_mfma_kernel<64, true, PLAIN>) : go(fwd_mfma_kernel<64, false, PLAIN>);
@@ -437,8 +456,8 @@ hipError_t launch_fwd_mfma(const void* q, const void* k, const void* v, void* ou
 
 hipError_t launch_fwd_mfma_ragged(const void* q, const void* k, const void* v, void* out, float* lse, const AttnShape& s,
                                   const RaggedSeqs& seqs, hipStream_t st) {
-    const int nq = (s.Lq + BM - 1) / BM;  // tiles of the longest possible chunk; shorter sequences skip theirs
-    const long nblk = (long)nq * s.Hq * s.B;
+    const int nq = row_units(s.Lq, s.Hq / s.Hkv).per;  // of the longest possible chunk; shorter sequences skip theirs
+    const long nblk = (long)nq * s.Hkv * s.B;
     if (nblk > 0x7fffffffL) return hipErrorInvalidValue;
     const bool gen = s.S != 0 || s.umode != 0;
     auto go = [&](auto kern) {
@@ -468,7 +487,7 @@ hipError_t launch_fwd_mfma_pack(const void* q, const void* k, const void* v, voi
             t.c0[i] = cu[d];
             t.len[i] = cu[d + 1] - cu[d];
             t.blk0[i] = (int)nblk;
-            nblk += (long)((t.len[i] + BM - 1) / BM) * s.Hq;
+            nblk += (long)row_units(t.len[i], s.Hq / s.Hkv).per * s.Hkv;
         }
         if (nblk > 0x7fffffffL) return hipErrorInvalidValue;
         t.blk0[t.n] = (int)nblk;

@@ -25,11 +25,30 @@ constexpr int kFwdBm = 128, kFwdBn = 32;  // forward: query rows per workgroup, 
 constexpr int kDqBm = 128, kDqBn = 64;    // dQ
 constexpr int kWaveRows = 32;             // query rows per wave in both
 
+// A row-side workgroup is four waves, and a wave takes one unit: the kWaveRows rows of one row block of one query
+// head.  The units of a kv head are numbered heads first (unit = row block * G + head of the group), and a workgroup
+// takes four consecutive ones, so with G = Hq / Hkv = 4 its waves hold the same 32 rows of four heads: they share
+// every staged tile exactly, and the workgroup walks a window of W + 32 positions.  Four row blocks of one head,
+// which is what is left of it at G = 1, walk W + 128, in which every wave idles through the steps right of its
+// diagonal and computes the steps left of its window for the few gists in them.
+constexpr int kUnitsPerWg = 4;
+struct RowUnits {
+    int n;      // units of the kv head
+    int per;    // workgroups
+};
+__host__ __device__ inline RowUnits row_units(int rows, int G) {
+    RowUnits u;
+    u.n = (rows + kWaveRows - 1) / kWaveRows * G;
+    u.per = (u.n + kUnitsPerWg - 1) / kUnitsPerWg;
+    return u;
+}
+
 struct RowWalk {
     int wstart;  // first position of the window phase: a step boundary at or left of every window of the tile
     int nfar;    // compact entries (sinks, gists) strictly left of it -- the gist phase, visible to every row
     int ngt;     // steps of the gist phase
     int nwin;    // steps of the window phase (up to the step holding the tile's last row)
+    __host__ __device__ int steps() const { return ngt + nwin; }
 };
 
 // the walk of the query rows i0 .. i1 (positions) with steps of Bn keys; s.s0 > 0: K/V hold no position left of s0
