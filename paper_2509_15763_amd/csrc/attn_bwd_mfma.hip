@@ -13,6 +13,7 @@
 //   4. dkdv_kernel<WINDOW>  one workgroup per contiguous 128-key tile: the pairs of the window phase; its
 //                           epilogue adds the reduced gist-phase sums to the gist rows and writes dK, dV
 //   5. dq_kernel            one workgroup per four units of 32 query rows of a head, same tile walk as the forward
+// Short backwards run 2, 4 and 5 as one launch (bwd_joint_kernel) and 3 behind it, where it writes the gist rows.
 // Every (query, key) pair is handled by exactly one of the two dkdv phases: a query chunk c (64 rows) sees
 // the sinks and gists at positions < far(c) = floor(win_lo(64c) / 128) * 128 in the gist phase (win_lo = first
 // position of a row's local window) and every key >= far(c) in the window phase.
@@ -157,437 +158,59 @@ __global__ __launch_bounds__(NT, 2) void dkdv_kernel(const bf16_t* __restrict__ 
                                                     float* __restrict__ part, const float* __restrict__ comp,
                                                     AttnShape s_arg, BwdPlan pl,
                                                     std::conditional_t<PACK, DocTab, NoDocs> docs) {
-    AttnShape s = s_arg;
-    if constexpr (!GEN) {
-        s.S = 0;
-        s.umode = 0;
-    }
-    int n = blockIdx.x;
-    if constexpr (PACK) {  // the document becomes the whole problem
-        const int d = doc_of_block(docs, n);
-        n -= docs.blk0[d];
-        s = doc_view(s, docs.len[d]);
-        plan_counts(s, pl, pl.segc);  // pl arrives with the launch's segment length only
-        const size_t ro = (size_t)docs.c0[d] * (QSTR ? s.D : D);
-        const size_t qro = QSTR ? (size_t)docs.c0[d] * s.q_rs : ro;
-        q += qro;
-        k += ro;
-        v += ro;
-        dout += qro;
-        dk += ro;
-        dv += ro;
-        lse2 += docs.c0[d];
-        delta += docs.c0[d];
-        part += (size_t)docs.part0[d] * (2 * D * BNK);
-        comp += (size_t)docs.comp0[d] * (2 * D * BNK);
-    }
-    constexpr int KS = D / 32, DB = D / 16, CH = D / 8;  // 16x16x32 MFMA: k-steps of 32, 16-row blocks of dK^T / dV^T
-    constexpr int RPI = 64 / CH;        // chunk rows covered by one direct-load instruction
-    constexpr int IPW = MQ / RPI / 4;   // such instructions per wave, per matrix, per step
-    constexpr int ROWB = CH * 16;       // bytes per row
+    constexpr bool JOINT = false;
+    constexpr int BLOCK0 = 0;
+    constexpr float* keep = nullptr;
     __shared__ __attribute__((aligned(1024))) DkdvSmem<D> sm;
+#include "dkdv_body.inc"
+}
 
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int r16 = lane & 15, g4 = lane >> 4;  // the lane's place in a 16x16x32 operand
-    const int L = s.L;
-    const int G = s.Hq / s.Hkv;
-    const float c = s.scale * kLog2e;
-    const int Dt = QSTR ? s.D : D;  // elements per row in memory
-
-    // ---- which (batch, kv head) and which unit of work.  Workgroup ids go round-robin over the 8
-    // XCDs, so with id % 8 selecting the (batch, kv head) pair every XCD gets the same amount of work
-    // and one head's Q/dO stream stays in one XCD's L2.
-    const int NP = s.B * s.Hkv;
-    int pr, unit;
-    if ((NP & 7) == 0) {
-        const int mm = n >> 3;
-        pr = (n & 7) + 8 * (mm % (NP >> 3));
-        unit = mm / (NP >> 3);
-    } else {
-        pr = n % NP;
-        unit = n / NP;
-    }
-    const int b = pr / s.Hkv, hk = pr % s.Hkv;
-
-    // ---- which keys, which query chunks
-    int tile, c_lo, c_hi;  // chunks c_lo .. c_hi inclusive
-    int seg = 0;
-    int slot = 0, nslots = 0;  // gist phase: the workgroup's slot among the nslots partial sums of its (batch, kv head)
-    if (GIST) {
-        // One workgroup per (segment, compact tile the segment reaches), segment-major, late (fully populated)
-        // segments first: the workgroups running together on an XCD then stream the same Q/dO chunks of the same
-        // head through its L2.  A dense launch puts the shorter units -- tiles first reached inside their segment --
-        // at the end, longest first, where they even out the last round (gist_unit); a document of a pack counts
-        // the slots of its own plan from the last segment down.
-        seg = pl.nseg - 1;
-        if constexpr (PACK) {  // the document's plan has no table: sum the segments' tile counts
-            int rem = unit, nt;
-            while ((nt = seg_tiles(s, pl, seg)) <= rem && seg > 0) {
-                rem -= nt;
-                --seg;
-            }
-            tile = rem;
-            slot = tile;
-            for (int sg = 0; sg < seg; ++sg) slot += seg_tiles(s, pl, sg);
-            nslots = slot - tile + nt + (unit - rem);
-        } else {
-            nslots = pl.slot0[pl.nseg];
-            gist_unit(pl, unit, seg, tile);
-            slot = pl.slot0[seg] + tile;
-        }
-        const ChunkRange cr = gist_tile_chunks(s, pl, tile, seg);
-        c_lo = cr.c_lo;
-        c_hi = cr.c_hi;
-        if (c_lo > c_hi) return;  // cannot happen for a slot of the plan (uniform exit all the same)
-    } else {
-        tile = unit;
-        const ChunkRange cr = window_tile_chunks(s, pl, tile);
-        c_lo = cr.c_lo;
-        c_hi = cr.c_hi;
-    }
-    const int key0 = tile * BNK + 32 * w;      // first key (position, or compact gist index) of the wave
-    // The wave's 32 keys are two 16-key blocks kb = 0, 1; this lane's keys are key0 + 16 kb + r16.
-    // K, V fragments (B operands): lane holds K[key[kb]][32 ks + 8 g4 .. +7].
-    int key[2], span_j[2];
-    bool gist_lane[2];
-    bf16x8 kf[2][KS], vf[2][KS];
-    f32x4 akT[DB][2], avT[DB][2];  // dK^T, dV^T: register i of [db][kb] is d = 16 db + 4 g4 + i, column = key[kb]
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-        key[kb] = key0 + 16 * kb + r16;
-        int krow;                              // row of K/V holding it
-        if (GIST) {
-            const int atot = count_always(s, L);  // sinks + gists, >= 1 whenever a gist workgroup exists
-            krow = pos_of_always(s, min(key[kb], atot - 1));
-        } else {
-            krow = min(key[kb], L - 1);
-        }
-        gist_lane[kb] = GIST ? true : is_always(s, key[kb]);  // a sink or a gist: visible to every later row
-        // the key stays in the window for span_j more rows (W - 1 for every key in the sliding mode)
-        span_j[kb] = 0;
-        if constexpr (!GIST && GEN) span_j[kb] = key[kb] < L ? win_hi(s, key[kb]) - key[kb] : 0;
-        const size_t base = (((size_t)b * s.Hkv + hk) * s.kvhs + krow) * Dt + 8 * g4;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            u32x4 zk = {0u, 0u, 0u, 0u}, zv = {0u, 0u, 0u, 0u};  // columns past the tensors' head dimension are zero
-            if (!QSTR || 32 * ks + 8 * g4 < Dt) {
-                zk = *(const u32x4*)(k + base + 32 * ks);
-                zv = *(const u32x4*)(v + base + 32 * ks);
-            }
-            kf[kb][ks] = __builtin_bit_cast(bf16x8, zk);
-            vf[kb][ks] = __builtin_bit_cast(bf16x8, zv);
-        }
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {
-            akT[db][kb] = zero4();
-            avT[db][kb] = zero4();
-        }
-    }
-    // last row that has the wave's first key in its window
-    int hi_w0 = 0;
-    if constexpr (!GIST) hi_w0 = win_hi(s, min(key0, L - 1));
-
-    // ---- staging of the Q / dO chunk: direct global->LDS loads
-    const int nch = c_hi - c_lo + 1;
-    const int nsteps = nch * G;
-    // Load slot i of wave w covers the chunk rows (w * IPW + i) * RPI + lane / CH.  The swizzle repeats every 16 rows and
-    // w * IPW * RPI is a multiple of 16, so the lane's byte offset inside the slot's rows takes only NLP different
-    // values; everything else of the address is wave-uniform or an immediate.
-    // They are recomputed from the lane id at every use: kept in registers across the step they would be
-    // spilled, and a reload from scratch waits on the same counter as the direct loads still in flight.
-    constexpr int NLP = 16 / RPI;
-    static_assert(IPW * RPI == 16 && NLP == IPW, "a wave stages 16 rows per matrix and step");
-    auto issue = [&](int g, int cc, int buf) __attribute__((always_inline)) {
-        int ln = lane;
-        asm volatile("" : "+v"(ln));  // opaque: keeps the address arithmetic below inside this call
-        const int lrow_ = ln / CH;
-        int lanepart[NLP];
-        const unsigned rsb = QSTR ? (unsigned)s.q_rs * 2u : (unsigned)ROWB;  // bytes between consecutive rows in q / dout
-#pragma unroll
-        for (int i = 0; i < NLP; ++i) {
-            int sc = (ln % CH) ^ swz16<CH>(i * RPI + lrow_);  // the source chunk of this lane's LDS position
-            if (QSTR && 8 * sc >= Dt) sc = 0;                  // a chunk the rows do not have: any chunk will do
-            lanepart[i] = lrow_ * (int)rsb + (sc << 4);
-        }
-        const size_t hb = ((size_t)b * s.Hq + hk * G + g) * (PACK ? s.qhs : L);  // wave-uniform; workspace rows
-        // the head in the caller's tensors
-        const size_t hg = QSTR ? (size_t)b * s.q_bs + (size_t)(hk * G + g) * s.q_hs : ((size_t)b * s.Hq + hk * G + g) * s.qhs * D;
-        const char* qh = (const char*)(q + hg);
-        const char* gh = (const char*)(dout + hg);
-        if (cc * MQ + MQ <= L) {  // the whole chunk exists (wave-uniform)
-            const size_t cb = (size_t)(cc * MQ + w * IPW * RPI) * rsb;
-#pragma unroll
-            for (int i = 0; i < IPW; ++i) {
-                const unsigned off = (unsigned)lanepart[i % NLP] + (unsigned)(i * RPI) * rsb;
-                g2l16(qh + cb + off, &sm.q[buf][(w * IPW + i) * 1024]);
-                g2l16(gh + cb + off, &sm.g[buf][(w * IPW + i) * 1024]);
-            }
-        } else {  // last chunk of a ragged sequence: rows past the end shadow the last row
-#pragma unroll
-            for (int i = 0; i < IPW; ++i) {
-                const int rr = (w * IPW + i) * RPI + lrow_;
-                const int row = min(cc * MQ + rr, L - 1);
-                const unsigned off = (unsigned)row * rsb + (unsigned)(lanepart[i % NLP] - lrow_ * (int)rsb);
-                g2l16(qh + off, &sm.q[buf][(w * IPW + i) * 1024]);
-                g2l16(gh + off, &sm.g[buf][(w * IPW + i) * 1024]);
-            }
-        }
-        if (w < 2) {  // wave 0: the 64 rows' lse2, wave 1: their delta (one 4-byte direct load per lane)
-            const int row = min(cc * MQ + ln, L - 1);
-            const float* src = (w == 0 ? lse2 : delta) + hb + row;
-            float* dst = w == 0 ? sm.lse2[buf] : sm.delta[buf];
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                             (__attribute__((address_space(3))) void*)dst, 4, 0, 0);
-        }
-    };
-    // Per-lane LDS offsets.  Row-wise read of chunk row r16 (+16 qs + 32 qb), 16-byte chunk 4 ks + g4: the swizzle
-    // XORs the chunk bits, so the offset for k-step ks is roff0 ^ (ks << 6); likewise the transposing read of the
-    // 16-column block db sits at toff0 ^ (db << 5).  Only the two bases stay live across the kernel (registers
-    // are what this kernel is short of); the XORs are redone per query block.
-    const int roff0 = row16_lane_off<CH>(0);
-    const int toff0 = tr16_lane_off16<CH>(0);
-
-    // one step on LDS stage BUF (a compile-time constant: LDS addresses = lane register + immediate)
-    auto do_step = [&](auto bufc, int cc) __attribute__((always_inline)) {
-        constexpr int BUF = decltype(bufc)::value;
-        const char* qt = sm.q[BUF];
-        const char* gt = sm.g[BUF];
-        const int q0 = cc * MQ;
-
-        int nfar = 0;
-        if (GIST) nfar = nfar_of_chunk(s, cc);  // compact entries visible to this chunk: index < nfar
-
-#pragma unroll
-        for (int qb = 0; qb < MQ / 32; ++qb) {
-            const int qb0 = q0 + 32 * qb;  // first query row of the block
-            // every row left of every key of the wave: nothing to do (the gist phase never skips)
-            if (!GIST && UNIGIST_WINDOW_BLOCK_SKIPPED(key0, qb0)) continue;
-
-            // offsets of this query block; the XORs below touch bits 5..7 only, the block offset bits >= 13
-            int rb = roff0 + 32 * qb * ROWB, tb = toff0 + 32 * qb * ROWB;
-            asm volatile("" : "+v"(rb), "+v"(tb));  // opaque: the derived offsets are not hoisted out of the loop
-
-            // ---- S = Q K^T, dP = dO V^T for the two 16-row halves qs of the block and the two 16-key blocks kb:
-            // register i of sa[qs][kb] is query qb0 + 16 qs + 4 g4 + i, column = key[kb].  Every Q and dO fragment
-            // serves both key blocks.  The fragment reads are issued PF groups ahead of the MFMAs that consume them;
-            // the scheduling barriers keep the compiler from sinking them back to just before their use, where every
-            // MFMA would wait for a full LDS round trip.
-            // dP starts from -delta of its rows (the prepass stores delta negated), so dS = P (dP - delta) needs no
-            // subtraction afterwards.
-            f32x4 sa[2][2], dp[2][2];
-#pragma unroll
-            for (int qs = 0; qs < 2; ++qs) {
-                const f32x4 d4 = *(const f32x4*)(&sm.delta[BUF][32 * qb + 16 * qs + 4 * g4]);
-                dp[qs][0] = d4;
-                dp[qs][1] = d4;
-            }
-            {
-                constexpr int N = 2 * KS, PF = 1;  // group n: half n / KS, k-step n % KS
-                bf16x8 fq[N], fg[N];
-                auto fetch = [&](int n) __attribute__((always_inline)) {
-                    const int ro = (rb ^ ((n % KS) << 6)) + 16 * (n / KS) * ROWB;
-                    fq[n] = *(const bf16x8*)(qt + ro);
-                    fg[n] = *(const bf16x8*)(gt + ro);
-                };
-#pragma unroll
-                for (int n = 0; n < PF; ++n) fetch(n);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int n = 0; n < N; ++n) {
-                    if (n + PF < N) fetch(n + PF);
-                    const int qs = n / KS, ks = n % KS;
-#pragma unroll
-                    for (int kb = 0; kb < 2; ++kb) {
-                        sa[qs][kb] = mfma16(fq[n], kf[kb][ks], ks == 0 ? zero4() : sa[qs][kb]);
-                        dp[qs][kb] = mfma16(fg[n], vf[kb][ks], dp[qs][kb]);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            // ---- P and dS
-            bool masked;
-            if (GIST) masked = UNIGIST_GIST_BLOCK_MASKED(key0, qb0, nfar, L);
-            else masked = UNIGIST_WINDOW_BLOCK_MASKED(key0, qb0, hi_w0, L);
-            f32x4 l4[2];
-#pragma unroll
-            for (int qs = 0; qs < 2; ++qs) l4[qs] = *(const f32x4*)(&sm.lse2[BUF][32 * qb + 16 * qs + 4 * g4]);
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
-                for (int qs = 0; qs < 2; ++qs)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        sa[qs][kb][i] = __builtin_amdgcn_exp2f(fmaf(sa[qs][kb][i], c, -l4[qs][i]));
-                if (masked) {
-                    // bit t of vis: does query qb0 + t see this lane's key[kb]?  The visible queries are a range of
-                    // offsets (those inside the sequence; for a raw key those that still have it in their window),
-                    // cut at the diagonal.  This lane holds the offsets 16 qs + 4 g4 + i.
-                    unsigned vis;
-                    const unsigned inside = below_bits(L - qb0);
-                    if (GIST) {
-                        vis = key[kb] < nfar ? inside : 0u;
-                    } else {
-                        const int d0 = qb0 - key[kb];  // distance i - j of the block's first query to the key
-                        const int span = GEN ? span_j[kb] : s.W - 1;
-                        const unsigned win = gist_lane[kb] ? ~0u : below_bits(span - d0 + 1);
-                        vis = inside & win & ~below_bits(-d0);
-                    }
-                    vis >>= 4 * g4;
-#pragma unroll
-                    for (int qs = 0; qs < 2; ++qs)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            if (!((vis >> (16 * qs + i)) & 1u)) sa[qs][kb][i] = 0.f;
-                }
-#pragma unroll
-                for (int qs = 0; qs < 2; ++qs)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) dp[qs][kb][i] *= sa[qs][kb][i];
-            }
-            // ---- dV^T += dO^T P,  dK^T += Q^T dS : contraction slot 8 g4 + 4 qs + i is query 16 qs + 4 g4 + i of the
-            // block, on both operands; every dO^T and Q^T fragment serves both key blocks
-            bf16x8 pb[2], sb[2];
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-                pb[kb] = pack44(sa[0][kb], sa[1][kb]);
-                sb[kb] = pack44(dp[0][kb], dp[1][kb]);
-            }
-            {
-                constexpr int PF = 2;
-                bf16x8 fg[DB], fq[DB];
-                auto fetch = [&](int db) __attribute__((always_inline)) {
-                    const int to = tb ^ (db << 5);
-                    fg[db] = tr16_frag16<CH>(gt + to, 0);
-                    fq[db] = tr16_frag16<CH>(qt + to, 0);
-                };
-#pragma unroll
-                for (int db = 0; db < PF; ++db) fetch(db);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int db = 0; db < DB; ++db) {
-                    if (db + PF < DB) fetch(db + PF);
-#pragma unroll
-                    for (int kb = 0; kb < 2; ++kb) {
-                        avT[db][kb] = mfma16(fg[db], pb[kb], avT[db][kb]);
-                        akT[db][kb] = mfma16(fq[db], sb[kb], akT[db][kb]);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-        }
-    };
-
-    // Step t handles query chunk c_lo + t % nch of query head t / nch of the group; both walks (the chunk being
-    // computed, the chunk being fetched one step ahead) are kept as (head, chunk) counters instead of dividing.
-    int gi = 0, ci = c_lo;  // what the next issue() fetches
-    int cs = c_lo;          // what the next do_step() computes
-    auto next_issue = [&]() __attribute__((always_inline)) {
-        if (++ci > c_hi) {
-            ci = c_lo;
-            ++gi;
-        }
-    };
-    auto next_step = [&]() __attribute__((always_inline)) {
-        if (++cs > c_hi) cs = c_lo;
-    };
-    issue(gi, ci, 0);
-    next_issue();
-    for (int step = 0; step < nsteps; step += 2) {
-        wait_vmem();
-        __syncthreads();
-        if (step + 1 < nsteps) {
-            issue(gi, ci, 1);
-            next_issue();
-        }
-        do_step(std::integral_constant<int, 0>{}, cs);
-        next_step();
-        if (step + 1 < nsteps) {
-            wait_vmem();
-            __syncthreads();
-            if (step + 2 < nsteps) {
-                issue(gi, ci, 0);
-                next_issue();
-            }
-            do_step(std::integral_constant<int, 1>{}, cs);
-            next_step();
-        }
-    }
-
-    // ---- epilogue: register i of [db][kb] is d = 16 db + 4 g4 + i of key[kb]
-    if (GIST) {
-        // fp32 partials, transposed: [dK^T | dV^T][d][BNK keys]
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-            float* o = part + (((size_t)b * s.Hkv + hk) * nslots + slot) * (2 * D * BNK) + 32 * w + 16 * kb + r16;
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int d = 16 * db + 4 * g4 + i;
-                    o[(size_t)d * BNK] = akT[db][kb][i] * s.scale;
-                    o[(size_t)(D + d) * BNK] = avT[db][kb][i];
-                }
-        }
-    } else {
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-            bool added = false;
-            if (gist_lane[kb] && pl.n_gt > 0) {
-                // add what the gist phase collected for this row (zero if no chunk saw it from afar)
-                const int gi = count_always(s, key[kb]);  // its index in the compact list of sinks and gists
-                const int gt = gi / BNK;
-                if (gt < pl.n_gt && key[kb] < L) {
-                    const float* cp = comp + (((size_t)b * s.Hkv + hk) * pl.n_gt + gt) * (2 * D * BNK) + gi % BNK;
-#pragma unroll
-                    for (int db = 0; db < DB; ++db)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const int d = 16 * db + 4 * g4 + i;
-                            akT[db][kb][i] = akT[db][kb][i] * s.scale + cp[(size_t)d * BNK];
-                            avT[db][kb][i] += cp[(size_t)(D + d) * BNK];
-                        }
-                    added = true;
-                }
-            }
-            if (!added) {
-#pragma unroll
-                for (int db = 0; db < DB; ++db)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) akT[db][kb][i] *= s.scale;
-            }
-            if (key[kb] < L) {
-                const size_t base = (((size_t)b * s.Hkv + hk) * s.kvhs + key[kb]) * Dt + 4 * g4;
-#pragma unroll
-                for (int db = 0; db < DB; ++db) {
-                    if (QSTR && 16 * db + 4 * g4 >= Dt) continue;
-                    u32x2 a, bb;
-                    a[0] = pack_bf16x2(akT[db][kb][0], akT[db][kb][1]);
-                    a[1] = pack_bf16x2(akT[db][kb][2], akT[db][kb][3]);
-                    bb[0] = pack_bf16x2(avT[db][kb][0], avT[db][kb][1]);
-                    bb[1] = pack_bf16x2(avT[db][kb][2], avT[db][kb][3]);
-                    *(u32x2*)(dk + base + 16 * db) = a;
-                    *(u32x2*)(dv + base + 16 * db) = bb;
-                }
-            }
-        }
-    }
+// The same inside the joint launch (below): the partials and the window phase's sums of the gist rows (keep) stay in
+// fp32 for the reduction that follows.
+template <int D, bool GIST, bool GEN, bool PACK, bool QSTR>
+__device__ __forceinline__ void dkdv_part(DkdvSmem<D>& sm, int BLOCK0, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
+                                          const bf16_t* __restrict__ v, const float* __restrict__ lse2,
+                                          const bf16_t* __restrict__ dout, const float* __restrict__ delta,
+                                          bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, float* __restrict__ part,
+                                          float* __restrict__ keep, AttnShape s_arg,
+                                          std::conditional_t<PACK, BwdPlan, const BwdPlan&> pl,
+                                          const std::conditional_t<PACK, DocTab, NoDocs>& docs) {
+    constexpr bool JOINT = true;
+    const float* comp = nullptr;
+#include "dkdv_body.inc"
 }
 
 // ------------------------------------------------------------------ 3. sum the segments of each gist tile
+// FINISH = false: the sums go to comp, and the window phase adds them to its own.  FINISH = true (after the joint
+// launch): comp holds the window phase's sums of the gist rows; they are added and the rows of dk and dv written.
+template <int D, bool FINISH>
 __global__ __launch_bounds__(NT) void gist_reduce_kernel(const float* __restrict__ part, float* __restrict__ comp,
-                                                        BwdPlan pl, AttnShape s, int per_tile) {
-    // grid: x = slices of a tile's 2*D*BNK floats (four per thread, per_tile is a multiple of 4), y = tile,
-    // z = (b, hk).  The segments are added in ascending order, so the result does not depend on the launch.
+                                                        bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, BwdPlan pl,
+                                                        AttnShape s) {
+    // grid: x = slices of a tile's 2 D BNK floats (four per thread), y = tile, z = (b, hk).  The segments are
+    // added in ascending order, so the result does not depend on the launch.
+    constexpr int per_tile = 2 * D * BNK;
+    static_assert(per_tile % (4 * NT) == 0, "whole workgroups");
     const int gt = blockIdx.y;
     const int idx = 4 * (blockIdx.x * NT + threadIdx.x);
-    if (idx >= per_tile) return;
     const int cf = first_chunk_with_more_far(s, pl.NC, gt * BNK);
     const float* pp = part + (size_t)blockIdx.z * pl.slot0[pl.nseg] * per_tile;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     if (cf < pl.NC)  // the tile has a slot in every segment from that of its first chunk on
         for (int sg = cf / pl.segc; sg < pl.nseg; ++sg) acc += *(const f32x4*)(pp + (size_t)(pl.slot0[sg] + gt) * per_tile + idx);
-    *(f32x4*)(comp + ((size_t)blockIdx.z * pl.n_gt + gt) * per_tile + idx) = acc;
+    float* cp = comp + ((size_t)blockIdx.z * pl.n_gt + gt) * per_tile + idx;
+    if constexpr (FINISH) {
+        const int e = gt * BNK + idx / (2 * D), col = idx % D;  // entry of the compact list; column of dK or dV
+        if (e >= count_always(s, s.L) || col >= s.D) return;    // the last tile's missing entries; padding columns
+        acc = *(const f32x4*)cp + acc;
+        u32x2 r;
+        r[0] = pack_bf16x2(acc[0], acc[1]);
+        r[1] = pack_bf16x2(acc[2], acc[3]);
+        bf16_t* o = idx % (2 * D) < D ? dk : dv;
+        *(u32x2*)(o + ((size_t)blockIdx.z * s.kvhs + pos_of_always(s, e)) * s.D + col) = r;
+    } else {
+        *(f32x4*)cp = acc;
+    }
 }
 
 // The same for a packed launch.  grid: x = slot of comp (a document's slots are its (kv head, gist tile) pairs,
@@ -631,274 +254,52 @@ __global__ __launch_bounds__(NT, 2) void dq_kernel(const bf16_t* __restrict__ q,
                                                   const bf16_t* __restrict__ dout, const float* __restrict__ delta,
                                                   bf16_t* __restrict__ dq, AttnShape s_arg, int nq,
                                                   std::conditional_t<PACK, DocTab, NoDocs> docs) {
-    AttnShape s = s_arg;
-    if constexpr (!GEN) {
-        s.S = 0;
-        s.umode = 0;
-    }
-    int n = blockIdx.x;
-    if constexpr (PACK) {
-        const int d = doc_of_block(docs, n);
-        n -= docs.blk0[d];
-        s = doc_view(s, docs.len[d]);
-        nq = row_units(s.L, s.Hq / s.Hkv).per;
-        const size_t ro = (size_t)docs.c0[d] * (QSTR ? s.D : D);
-        const size_t qro = QSTR ? (size_t)docs.c0[d] * s.q_rs : ro;
-        q += qro;
-        k += ro;
-        v += ro;
-        dout += qro;
-        dq += qro;
-        lse2 += docs.c0[d];
-        delta += docs.c0[d];
-    }
-    constexpr int KS = D / 32, DB = D / 16, CH = D / 8;  // 16x16x32 MFMA: k-steps of 32, 16-row blocks of dQ^T
-    constexpr int RPI = 64 / CH;
-    constexpr int IPW = BNQ / RPI / 4;
+    constexpr int BLOCK0 = 0;
     __shared__ __attribute__((aligned(1024))) DqSmem<D> sm;
+#include "dq_body.inc"
+}
+template <int D, bool GEN, bool PACK, bool QSTR>
+__device__ __forceinline__ void dq_part(DqSmem<D>& sm, int BLOCK0, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
+                                        const bf16_t* __restrict__ v, const float* __restrict__ lse2,
+                                        const bf16_t* __restrict__ dout, const float* __restrict__ delta,
+                                        bf16_t* __restrict__ dq, AttnShape s_arg, int nq,
+                                        const std::conditional_t<PACK, DocTab, NoDocs>& docs) {
+#include "dq_body.inc"
+}
 
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int g4 = lane >> 4;  // with r16 = lane % 16: the lane's place in a 16x16x32 operand
-    // four units of 32 rows of one query head each, one per wave (plan.h), as in the forward
-    const int G = s.Hq / s.Hkv, NP = s.B * s.Hkv;
-    int pr, wt;
-    if ((NP & 7) == 0) {
-        const int mm = n >> 3;
-        pr = (n & 7) + 8 * (mm % (NP >> 3));
-        wt = nq - 1 - mm / (NP >> 3);
-    } else {
-        pr = n % NP;
-        wt = nq - 1 - n / NP;
-    }
-    const int L = s.L, rp1 = s.rp1;
-    const int nu = row_units(L, G).n;
-    const int u0 = wt * kUnitsPerWg;
-    const int wv = __builtin_amdgcn_readfirstlane(w);
-    const bool live = u0 + wv < nu;  // the last workgroup may have waves without a unit: they only stage
-    const int u = live ? u0 + wv : nu - 1;
-    const int b = pr / s.Hkv, hk = pr % s.Hkv, hq = hk * G + u % G;
-    const int i0 = u0 / G * kWaveRows;                                       // the workgroup's first and last row
-    const int i1 = min(L, (min(u0 + kUnitsPerWg, nu) - 1) / G * kWaveRows + kWaveRows) - 1;
-    const int wrow0 = u / G * kWaveRows;  // first row of the wave; the lane's two rows are wrow0 + 16 qb + r16
-    const int Dt = QSTR ? s.D : D;  // elements per row in memory (see dkdv_kernel)
-    const char* kbytes = (const char*)(k + ((size_t)b * s.Hkv + hk) * s.kvhs * Dt);
-    const char* vbytes = (const char*)(v + ((size_t)b * s.Hkv + hk) * s.kvhs * Dt);
-    const float c = s.scale * kLog2e;
+// ------------------------------------------------------------------ 2., 4. and 5. in one launch
+// The three heavy parts of a whole backward need nothing from each other (the window phase leaves its sums of the gist
+// rows in comp for the reduction that follows), so they run as one launch: workgroups 0 .. n_gist-1 are the gist
+// phase, the next n_win the window phase, the rest dQ, whose short walks come last.  What bounds a short backward is not
+// the chip but the longest workgroup of each of its launches: alone, a phase of 2 x 2047 tokens leaves half of the 512
+// workgroup slots empty.  Phases one by one / jointly (without the delta pass), us, 32/8 heads unless noted:
+//   1 head, 1024, D 64     37 /   19        2 x 4096, W 512, r 16  338 /  313
+//   2 x 512                88 /   55        1 x 8192           720 /  677
+//   2 x 2047              150 /  134        1 x 8192, D 64     317 /  287
+//   2048, W 1024          233 /  182        28/4 heads, 12000 1152 / 1088
+//   4096, W 512           248 /  215        4 x 8192, 16/4, D 64  597 / 549
+// From about 16K tokens on (dQ workgroups: 4096 at D = 128) the tails it fills are short, and phases that run side by
+// side share the L2s of each other's streams: 1972 / 1995 (16384), 6194 / 6466 (32768), 6651 / 6876 (65536, D 64).
+// The line lies at six rounds of dQ workgroups: 3072 at two workgroups per CU (D = 128), 4608 at three (D = 64).
+template <int D> bool run_jointly(long n_dq) { return n_dq <= 256 * 6 * (D <= 64 ? 3 : 2); }
 
-    // B operands Q and dO of this lane's two query rows, their lse * log2(e), and -delta in the 4 registers of an
-    // accumulator: dP starts from it (the MFMA adds its C operand for free), so dS = P (dP - delta) needs no
-    // subtraction.  The registers are made opaque so that they stay 4 registers instead of being rebuilt from one
-    // value at every use.
-    int qrow[2], span_q[2];
-    size_t rowoff[2];
-    bf16x8 qf[2][KS], gf[2][KS];
-    float ls[2];
-    f32x4 ndl[2];
-    f32x4 acc[DB][2];  // dQ^T: register i of acc[db][qb] is d = 16 db + 4 g4 + i, column = query qrow[qb]
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-        qrow[qb] = wrow0 + 16 * qb + (lane & 15);
-        const int qrow_ld = min(qrow[qb], L - 1);
-        span_q[qb] = qrow[qb] - win_lo(s, qrow[qb]);  // this row's window reaches span_q positions back
-        // element offset of the row in the caller's q, dout and dq
-        rowoff[qb] = QSTR ? (size_t)b * s.q_bs + (size_t)hq * s.q_hs + (size_t)qrow_ld * s.q_rs
-                          : (((size_t)b * s.Hq + hq) * s.qhs + qrow_ld) * D;
-        const size_t wrow = ((size_t)b * s.Hq + hq) * (PACK ? s.qhs : L) + qrow_ld;  // in the workspace
-        const bf16_t* qp = q + rowoff[qb] + 8 * g4;
-        const bf16_t* gp = dout + rowoff[qb] + 8 * g4;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            u32x4 zq = {0u, 0u, 0u, 0u}, zg = {0u, 0u, 0u, 0u};  // columns past the tensors' head dimension are zero
-            if (!QSTR || 32 * ks + 8 * g4 < Dt) {
-                zq = *(const u32x4*)(qp + 32 * ks);
-                zg = *(const u32x4*)(gp + 32 * ks);
-            }
-            qf[qb][ks] = __builtin_bit_cast(bf16x8, zq);
-            gf[qb][ks] = __builtin_bit_cast(bf16x8, zg);
-        }
-        ls[qb] = lse2[wrow];
-        const float dl = delta[wrow];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float x = dl;
-            asm volatile("" : "+v"(x));
-            ndl[qb][i] = x;
-        }
-#pragma unroll
-        for (int db = 0; db < DB; ++db) acc[db][qb] = zero4();
-    }
-
-    const RowWalk walk = row_walk(s, i0, i1, BNQ);
-    const int wstart = walk.wstart;                // first position of the window phase
-    const int nfar = walk.nfar;                    // sinks and gists strictly left of it
-    const int ngt = walk.ngt;
-    const int ntiles = ngt + walk.nwin;
-    const int lo_wlast = win_lo(s, wrow0 + 31);    // window start of the wave's last row
-    const int S = s.S;
-
-    // ---- staging (same scheme as the forward kernel)
-    const int lrow = lane / CH;
-    int choff[IPW];
-#pragma unroll
-    for (int i = 0; i < IPW; ++i) {
-        const int sc = (lane % CH) ^ swz16<CH>((wv * IPW + i) * RPI + lrow);
-        choff[i] = (!QSTR || 8 * sc < Dt) ? sc * 16 : 0;  // a chunk the rows do not have: any chunk will do
-    }
-    auto issue = [&](int it, int buf) {
-        // Tile row rr is, in the gist phase, the (it * BNQ + rr)-th always-visible position, clamped to the last far
-        // one; in the window phase position wstart + (it - ngt) * BNQ + rr, clamped to the last position.  The phase
-        // only selects wave-uniform parameters, so the per-lane arithmetic has no branch.
-        const bool gphase = it < ngt;
-        const int a = gphase ? it * BNQ : wstart + (it - ngt) * BNQ;
-        const int bnd = gphase ? nfar - 1 : L - 1;
-        const int first_gist = gphase ? S : 0x7fffffff;  // entries from here on are gists
-        const int gm = gphase ? rp1 : 1, go = gphase ? 1 : 0;
-#pragma unroll
-        for (int i = 0; i < IPW; ++i) {
-            const int rr = (wv * IPW + i) * RPI + lrow;
-            const int c = min(a + rr, bnd);
-            int row;
-            if constexpr (GEN)  // entry c >= S is gist c - S at S + (c - S)(r+1) + r; factors < 2^24 by the size limit
-                row = c < first_gist ? c : S + mul24(c - S + 1, rp1) - 1;
-            else
-                row = mul24(c + go, gm) - go;
-            const unsigned off = (unsigned)row * (unsigned)(Dt * 2) + (unsigned)choff[i];
-            g2l16(kbytes + off, &sm.k[buf][(wv * IPW + i) * 1024]);
-            g2l16(vbytes + off, &sm.v[buf][(wv * IPW + i) * 1024]);
-        }
-    };
-    int roff[KS];  // row-wise read of tile row r16 (+16, +32, +48), chunk 4 ks + g4
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) roff[ks] = row16_lane_off<CH>(ks);
-    int toff[DB];  // transposing read of K, 16-column block db
-#pragma unroll
-    for (int db = 0; db < DB; ++db) toff[db] = tr16_lane_off16<CH>(db);
-
-    auto tile_step = [&](auto bufc, int it) {
-        constexpr int BUF = decltype(bufc)::value;
-        const char* kt = sm.k[BUF];
-        const char* vt = sm.v[BUF];
-        const bool gist_tile = it < ngt;
-        const int j0 = row_step_first(walk, it, BNQ);
-        const int kind = row_step_kind(walk, it, BNQ, wrow0, wrow0 + 31, lo_wlast);
-        if (kind == STEP_SKIP) return;
-
-        const bool masked = kind == STEP_MASKED;
-        unsigned long long gm = 0ull;  // bit t: the key at offset t from j0 holds a sink or a gist
-        if (!gist_tile && masked) gm = __builtin_amdgcn_ballot_w64(is_always(s, j0 + lane));
-
-        // S^T, dP^T for the 32 keys of half kb2: register i of sa[kb][qb] is key j0 + 32 kb2 + 16 kb + 4 g4 + i, column =
-        // query qrow[qb].  Every K and V fragment serves both query blocks; the reads run PFS groups ahead of their
-        // MFMAs and the scheduling barriers keep them there.
-        auto sdp = [&](int kb2, f32x4 (&sa)[2][2], f32x4 (&dp)[2][2]) __attribute__((always_inline)) {
-            constexpr int N = 2 * KS;  // group n: key block n / KS, k-step n % KS
-            bf16x8 fk[N], fv[N];
-            auto fetch = [&](int n) __attribute__((always_inline)) {
-                const int o = (32 * kb2 + 16 * (n / KS)) * CH * 16 + roff[n % KS];
-                fk[n] = *(const bf16x8*)(kt + o);
-                fv[n] = *(const bf16x8*)(vt + o);
-            };
-#pragma unroll
-            for (int n = 0; n < PFS; ++n) fetch(n);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int n = 0; n < N; ++n) {
-                if (n + PFS < N) fetch(n + PFS);
-                const int kb = n / KS, ks = n % KS;
-#pragma unroll
-                for (int qb = 0; qb < 2; ++qb) {
-                    sa[kb][qb] = mfma16(fk[n], qf[qb][ks], ks == 0 ? zero4() : sa[kb][qb]);
-                    dp[kb][qb] = mfma16(fv[n], gf[qb][ks], ks == 0 ? ndl[qb] : dp[kb][qb]);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        };
-        // P = exp2(S c - lse), the mask, dS = P (dP - delta) (dP arrives with -delta in it): dp becomes dS
-        auto soft = [&](int kb2, f32x4 (&sa)[2][2], f32x4 (&dp)[2][2]) __attribute__((always_inline)) {
-#pragma unroll
-            for (int qb = 0; qb < 2; ++qb) {
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) sa[kb][qb][i] = __builtin_amdgcn_exp2f(fmaf(sa[kb][qb][i], c, -ls[qb]));
-                if (masked) {
-                    // bit t of vis: does query qrow[qb] see the key at offset t of this 32-key block?  Visible sets
-                    // are bit ranges (the tail of the compact list; the window) plus, in the window phase, the sinks
-                    // and gists.  This lane holds the offsets 16 kb + 4 g4 + i.
-                    unsigned vis;
-                    if (gist_tile) {
-                        vis = below_bits(nfar - j0 - 32 * kb2);
-                    } else {
-                        const int d0 = qrow[qb] - (j0 + 32 * kb2);  // offsets d0 - span_q .. d0: window; <= d0: causal
-                        vis = below_bits(d0 + 1) & (~below_bits(d0 - span_q[qb]) | (unsigned)(gm >> (32 * kb2)));
-                    }
-                    vis >>= 4 * g4;
-#pragma unroll
-                    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            if (!((vis >> (16 * kb + i)) & 1u)) sa[kb][qb][i] = 0.f;
-                }
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) dp[kb][qb][i] *= sa[kb][qb][i];
-            }
-        };
-        // dQ^T += K^T dS^T for half kb2: contraction slot 8 g4 + 4 kb + i is key 16 kb + 4 g4 + i of the half, on both
-        // operands
-        auto dqm = [&](int kb2, const bf16x8 (&sb)[2]) __attribute__((always_inline)) {
-            bf16x8 ft[DB];
-#pragma unroll
-            for (int db = 0; db < PFT; ++db) ft[db] = tr16_frag16<CH>(kt + toff[db], 32 * kb2);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int db = 0; db < DB; ++db) {
-                if (db + PFT < DB) ft[db + PFT] = tr16_frag16<CH>(kt + toff[db + PFT], 32 * kb2);
-                acc[db][0] = mfma16(ft[db], sb[0], acc[db][0]);
-                acc[db][1] = mfma16(ft[db], sb[1], acc[db][1]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        };
-#pragma unroll
-        for (int kb2 = 0; kb2 < 2; ++kb2) {
-            f32x4 sa[2][2], dp[2][2];
-            bf16x8 sb[2];
-            sdp(kb2, sa, dp);
-            soft(kb2, sa, dp);
-#pragma unroll
-            for (int qb = 0; qb < 2; ++qb) sb[qb] = pack44(dp[0][qb], dp[1][qb]);
-            dqm(kb2, sb);
-        }
-    };
-
-    issue(0, 0);
-    for (int it = 0; it < ntiles; it += 2) {
-        wait_vmem();
-        __syncthreads();
-        if (it + 1 < ntiles) issue(it + 1, 1);
-        tile_step(std::integral_constant<int, 0>{}, it);
-        if (it + 1 < ntiles) {
-            wait_vmem();
-            __syncthreads();
-            if (it + 2 < ntiles) issue(it + 2, 0);
-            tile_step(std::integral_constant<int, 1>{}, it + 1);
-        }
-    }
-
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb)
-        if (live && qrow[qb] < L) {
-            bf16_t* op = dq + rowoff[qb] + 4 * g4;
-#pragma unroll
-            for (int db = 0; db < DB; ++db) {
-                if (QSTR && 16 * db + 4 * g4 >= Dt) continue;
-                u32x2 w2;
-                w2[0] = pack_bf16x2(acc[db][qb][0] * s.scale, acc[db][qb][1] * s.scale);
-                w2[1] = pack_bf16x2(acc[db][qb][2] * s.scale, acc[db][qb][3] * s.scale);
-                *(u32x2*)(op + 16 * db) = w2;
-            }
-        }
+template <int D, bool GEN, bool QSTR>
+__global__ __launch_bounds__(NT, 2) void bwd_joint_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
+                                                         const bf16_t* __restrict__ v, const float* __restrict__ lse2,
+                                                         const bf16_t* __restrict__ dout, const float* __restrict__ delta,
+                                                         bf16_t* __restrict__ dq, bf16_t* __restrict__ dk,
+                                                         bf16_t* __restrict__ dv, float* __restrict__ part,
+                                                         float* __restrict__ comp, AttnShape s, BwdPlan pl, int n_gist,
+                                                         int n_win, int nq) {
+    static_assert(sizeof(DqSmem<D>) <= sizeof(DkdvSmem<D>), "one LDS block for both");
+    __shared__ __attribute__((aligned(1024))) char smem[sizeof(DkdvSmem<D>)];
+    const int n = blockIdx.x;
+    if (n < n_gist)
+        dkdv_part<D, true, GEN, false, QSTR>(*(DkdvSmem<D>*)smem, 0, q, k, v, lse2, dout, delta, dk, dv, part, comp, s, pl, NoDocs{});
+    else if (n < n_gist + n_win)
+        dkdv_part<D, false, GEN, false, QSTR>(*(DkdvSmem<D>*)smem, n_gist, q, k, v, lse2, dout, delta, dk, dv, part, comp, s, pl, NoDocs{});
+    else
+        dq_part<D, GEN, false, QSTR>(*(DqSmem<D>*)smem, n_gist + n_win, q, k, v, lse2, dout, delta, dq, s, nq, NoDocs{});
 }
 
 template <int D>
@@ -913,6 +314,7 @@ hipError_t bwd_launch(const bf16_t* q, const bf16_t* k, const bf16_t* v, const b
     float* part = (float*)(ws + pl.off_part);
     float* comp = (float*)(ws + pl.off_comp);
     hipError_t e;
+    const dim3 reduce_grid((2 * D * BNK / 4) / NT, std::max(pl.n_gt, 1), s.B * s.Hkv);
     if (stages & UNIGIST_BWD_DELTA) {
         constexpr int rows_per_blk = NT / (D / 8);
         const long nrows = (long)s.B * s.Hq * s.L;
@@ -920,8 +322,23 @@ hipError_t bwd_launch(const bf16_t* q, const bf16_t* k, const bf16_t* v, const b
             out, dout, lse, delta, lse2, nrows, s.L, s.qhs, s.Hq, s.q_bs, s.q_hs, s.q_rs, s.D);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
+    const int nq = row_units(s.L, s.Hq / s.Hkv).per;
+    const long nblk = (long)nq * s.Hkv * s.B, n_gist = (long)pl.slot0[pl.nseg] * s.Hkv * s.B,
+               n_win = (long)((s.L + BNK - 1) / BNK) * s.Hkv * s.B;
+    if (nblk > 0x7fffffffL) return hipErrorInvalidValue;
+    if (stages == UNIGIST_BWD_ALL && run_jointly<D>(nblk)) {
+        auto go = [&](auto kern) {
+            kern<<<dim3((unsigned)(n_gist + n_win + nblk)), NT, 0, st>>>(q, k, v, lse2, dout, delta, dq, dk, dv, part, comp, s,
+                                                                       pl, (int)n_gist, (int)n_win, nq);
+        };
+        if (qstr) gen ? go(bwd_joint_kernel<D, true, true>) : go(bwd_joint_kernel<D, false, true>);
+        else gen ? go(bwd_joint_kernel<D, true, false>) : go(bwd_joint_kernel<D, false, false>);
+        if ((e = hipGetLastError()) != hipSuccess || pl.n_gt == 0) return e;
+        gist_reduce_kernel<D, true><<<reduce_grid, NT, 0, st>>>(part, comp, dk, dv, pl, s);
+        return hipGetLastError();
+    }
     if (pl.n_gt > 0 && (stages & UNIGIST_BWD_DKDV_GIST)) {
-        const dim3 grid((unsigned)((long)pl.slot0[pl.nseg] * s.Hkv * s.B));
+        const dim3 grid((unsigned)n_gist);
         if (qstr) {
             if (gen) dkdv_kernel<D, true, true, false, true><<<grid, NT, 0, st>>>(q, k, v, lse2, dout, delta, dk, dv, part, comp, s, pl, NoDocs{});
             else dkdv_kernel<D, true, false, false, true><<<grid, NT, 0, st>>>(q, k, v, lse2, dout, delta, dk, dv, part, comp, s, pl, NoDocs{});
@@ -930,12 +347,11 @@ hipError_t bwd_launch(const bf16_t* q, const bf16_t* k, const bf16_t* v, const b
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if (pl.n_gt > 0 && (stages & UNIGIST_BWD_GIST_REDUCE)) {
-        const int per_tile = 2 * D * BNK;
-        gist_reduce_kernel<<<dim3((per_tile / 4 + NT - 1) / NT, pl.n_gt, s.B * s.Hkv), NT, 0, st>>>(part, comp, pl, s, per_tile);
+        gist_reduce_kernel<D, false><<<reduce_grid, NT, 0, st>>>(part, comp, dk, dv, pl, s);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if (stages & UNIGIST_BWD_DKDV_WINDOW) {
-        const dim3 grid((unsigned)((long)((s.L + BNK - 1) / BNK) * s.Hkv * s.B));
+        const dim3 grid((unsigned)n_win);
         if (qstr) {
             if (gen) dkdv_kernel<D, false, true, false, true><<<grid, NT, 0, st>>>(q, k, v, lse2, dout, delta, dk, dv, part, comp, s, pl, NoDocs{});
             else dkdv_kernel<D, false, false, false, true><<<grid, NT, 0, st>>>(q, k, v, lse2, dout, delta, dk, dv, part, comp, s, pl, NoDocs{});
@@ -944,9 +360,6 @@ hipError_t bwd_launch(const bf16_t* q, const bf16_t* k, const bf16_t* v, const b
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if (!(stages & UNIGIST_BWD_DQ)) return hipSuccess;
-    const int nq = row_units(s.L, s.Hq / s.Hkv).per;
-    const long nblk = (long)nq * s.Hkv * s.B;
-    if (nblk > 0x7fffffffL) return hipErrorInvalidValue;
     if (qstr) {
         if (gen) dq_kernel<D, true, false, true><<<dim3((unsigned)nblk), NT, 0, st>>>(q, k, v, lse2, dout, delta, dq, s, nq, NoDocs{});
         else dq_kernel<D, false, false, true><<<dim3((unsigned)nblk), NT, 0, st>>>(q, k, v, lse2, dout, delta, dq, s, nq, NoDocs{});

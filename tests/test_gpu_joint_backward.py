@@ -1,0 +1,56 @@
+"""A short backward runs its gist phase, window phase and dQ as one launch and writes the gist rows of dK and dV in the
+reduction behind it; run stage by stage it launches them one after the other.  Both against each other (and the joint one
+against the oracle where it is small): padded head dimensions, sinks, unit windows, launches without a gist phase, gist
+tiles that end inside the sequence, row counts on both sides of the rule that chooses."""
+import pytest
+import torch
+
+import paper_2509_15763_amd as u
+from paper_2509_15763_amd import synth
+from _parity import TOL_GRAD_BF16, oracle_fwd_bwd, rel_l2, to_np
+
+pytestmark = pytest.mark.gpu
+
+#  B, Hq, Hkv, L, D, r, W, sinks, mode
+SHAPES = [
+    (1, 2, 1, 1, 64, 4, 8, 0, 0),           # one row
+    (1, 4, 2, 300, 64, 4, 512, 0, 0),       # everything inside the window: no gist phase
+    (2, 4, 1, 777, 128, 4, 64, 0, 0),
+    (1, 7, 1, 1283, 96, 2, 33, 5, 0),       # padded columns, sinks, a group of seven
+    (1, 4, 4, 1000, 48, 3, 100, 0, 0),
+    (1, 8, 2, 1500, 128, 4, 20, 64, 1),     # window in units
+    (2, 4, 2, 901, 64, 1, 16, 3, 1),
+    (1, 1, 1, 1024, 64, 4, 128, 0, 0),
+]
+LARGE = [(1, 32, 8, 12288, 128, 8, 256, 0, 0), (1, 32, 8, 12289, 128, 8, 256, 0, 0),  # 3072 workgroups of dQ, and more
+         (1, 16, 16, 18432, 64, 16, 200, 0, 0), (1, 16, 16, 18561, 64, 16, 200, 0, 0)]  # 2304, 2336: D = 64, joint
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L,D,r,W,S,mode", SHAPES + LARGE)
+@pytest.mark.parametrize("strided", [False, True])
+def test_whole_against_stages(B, Hq, Hkv, L, D, r, W, S, mode, strided):
+    q, k, v, do = synth.attn_inputs(B, Hq, Hkv, L, D, seed=L)
+    qd, kd, vd, dod = (t.cuda() for t in (q, k, v, do))
+    kw = dict(sinks=S, window_mode=mode)
+    out, lse = u.attn_fwd(qd, kd, vd, r, W, **kw)
+    ws = torch.full((u.unigist_attn_bwd_workspace_ex(B, Hq, Hkv, L, D, r, W, S, mode, u.UNIGIST_BF16),), 255,
+                    device="cuda", dtype=torch.uint8)  # NaNs: whatever is read must have been written
+    want = tuple(torch.full_like(t, float("nan")) for t in (qd, kd, vd))
+    for stage in (1, 2, 4, 8, 16):
+        u.attn_bwd(qd, kd, vd, out, lse, dod, r, W, workspace=ws, stages=stage, grads=want, **kw)
+    ws.fill_(255)
+    if strided:
+        t4 = lambda t: t.transpose(1, 2).contiguous().transpose(1, 2)
+        got = u.attn_bwd(t4(qd), kd, vd, t4(out), lse, t4(dod), r, W, workspace=ws, **kw)
+    else:
+        got = tuple(torch.full_like(t, float("nan")) for t in (qd, kd, vd))
+        u.attn_bwd(qd, kd, vd, out, lse, dod, r, W, workspace=ws, grads=got, **kw)
+    assert torch.equal(got[0], want[0])
+    # the same sums; one rounding of 2^-24 more where a gist row is put together can move a bf16 result by 2^-8 in one
+    # of about 2^14 elements: 2^-8 / sqrt(2^14) = 3e-5
+    for a, b in zip(got[1:], want[1:]):
+        assert (a.float() - b.float()).norm() <= 3e-4 * b.float().norm() + 1e-6
+    if L <= 1600 and L > 4:
+        o, l, *grads = oracle_fwd_bwd(q, k, v, do, r, W, sinks=S, units=mode == 1)
+        for a, b in zip(got, grads):
+            assert rel_l2(to_np(a), b) <= TOL_GRAD_BF16
