@@ -374,6 +374,11 @@ unigist_status unigist_cache_ring_append(void* kc, void* vc, const void* k_new, 
                                          const int* t_old, const int* n_new, int cap, int* rows_out, int B, int Hkv,
                                          int D, int r, int W, int sinks, int window_mode, unigist_dtype dt,
                                          void* hip_stream);
+/* The same in one launch with the advance of the positions: t[b] (DEVICE, in/out) grows by n_new[b] for every sequence
+ * that is not reported as -1.  n_new may be null: every sequence appends. */
+unigist_status unigist_cache_ring_step(void* kc, void* vc, const void* k_new, const void* v_new, int new_rows, int* t,
+                                       const int* n_new, int cap, int* rows_out, int B, int Hkv, int D, int r, int W,
+                                       int sinks, int window_mode, unigist_dtype dt, void* hip_stream);
 
 /*
  * Chunk-wise prefill (Sec. 4.3: the prompt is encoded chunk by chunk with the training kernel, dropping

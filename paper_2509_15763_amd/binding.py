@@ -33,6 +33,7 @@ EXPORTS = [
     "unigist_prefill_chunk_view", "unigist_prefill_chunk_strided", "unigist_attn_fwd_strided", "unigist_attn_bwd_strided",
     "unigist_attn_fwd_varlen_strided", "unigist_attn_bwd_varlen_strided",
     "unigist_cache_ring_rows", "unigist_cache_to_ring", "unigist_cache_from_ring", "unigist_cache_ring_append",
+    "unigist_cache_ring_step",
     "unigist_decode_noalloc", "unigist_decode_noalloc_scratch_bytes", "unigist_debug_force_plain_alu",
     "unigist_window_start", "unigist_plan_row_tile", "unigist_bwd_plan_build", "unigist_plan_key_tile", "unigist_plan_gist_unit",
     "unigist_probe_read_rate",
@@ -149,8 +150,9 @@ def load():
     for fn in (lib.unigist_cache_to_ring, lib.unigist_cache_from_ring):
         fn.restype = ip
         fn.argtypes = [vp, vp, vp, vp, ip, vp, vp, ip, vp] + [ip] * 8 + [vp]
-    lib.unigist_cache_ring_append.restype = ip
-    lib.unigist_cache_ring_append.argtypes = [vp, vp, vp, vp, ip, vp, vp, ip, vp] + [ip] * 8 + [vp]
+    for fn in (lib.unigist_cache_ring_append, lib.unigist_cache_ring_step):
+        fn.restype = ip
+        fn.argtypes = [vp, vp, vp, vp, ip, vp, vp, ip, vp] + [ip] * 8 + [vp]
     lib.unigist_attn_fwd_varlen_strided.restype = ip
     lib.unigist_attn_fwd_varlen_strided.argtypes = [vp, vp, vp, vp, fp] + [ip] * 8 + [cup, ip] + [C.c_longlong] * 2 + [ip, vp]
     lib.unigist_attn_bwd_varlen_strided.restype = ip
@@ -442,6 +444,12 @@ def unigist_cache_ring_append(kc, vc, k_new, v_new, new_rows, t_old, n_new, cap,
                               window_mode, dt, stream=None) -> int:
     return load().unigist_cache_ring_append(kc, vc, k_new, v_new, new_rows, t_old, n_new, cap, rows_out, B, Hkv, D, r, W,
                                             sinks, window_mode, dt, stream)
+
+
+def unigist_cache_ring_step(kc, vc, k_new, v_new, new_rows, t, n_new, cap, rows_out, B, Hkv, D, r, W, sinks, window_mode,
+                            dt, stream=None) -> int:
+    return load().unigist_cache_ring_step(kc, vc, k_new, v_new, new_rows, t, n_new, cap, rows_out, B, Hkv, D, r, W, sinks,
+                                          window_mode, dt, stream)
 
 
 def unigist_prefill_chunk_view(q, kc, vc, out, lse, B, Hq, Hkv, C, q_rows, D, r, W, sinks, window_mode, p0, s, cap, dt,
@@ -961,8 +969,7 @@ class RingKVCache:
         dev = kc.device
         self.dt = UNIGIST_E4M3 if kc.dtype == torch.uint8 else _dt(kc)
         self.kc, self.vc = torch.empty_like(kc), torch.empty_like(vc)
-        self.t = torch.tensor(ragged.t, dtype=torch.int32).to(dev)
-        s = torch.tensor(ragged.s, dtype=torch.int32).to(dev)
+        self.t, s = torch.tensor([ragged.t, ragged.s], dtype=torch.int32).to(dev)  # one copy for both
         self.rows = torch.empty(self.B, dtype=torch.int32, device=dev)
         _check(unigist_cache_to_ring(kc.data_ptr(), vc.data_ptr(), s.data_ptr(), self.t.data_ptr(), self.cap,
                                      self.kc.data_ptr(), self.vc.data_ptr(), self.cap, self.rows.data_ptr(), self.B,
@@ -973,16 +980,14 @@ class RingKVCache:
         """k_new/v_new [B, Hkv, 1, D]: the next position of every sequence (of those with active[b] = 1, int32 [B] on
         the GPU).  -> rows in use per sequence (int32 [B] on the GPU, -1 for a sequence that does not fit)."""
         _dev(k_new, v_new, active)
-        if active is None:
-            active = torch.ones(self.B, dtype=torch.int32, device=self.kc.device)
-        _check(unigist_cache_ring_append(self.kc.data_ptr(), self.vc.data_ptr(), k_new.data_ptr(), v_new.data_ptr(),
-                                         k_new.shape[2], self.t.data_ptr(), active.data_ptr(), self.cap,
-                                         self.rows.data_ptr(), self.B, self.Hkv, self.D, self.r, self.W, self.sinks,
-                                         self.mode, self.dt, _stream()),
-               "unigist_cache_ring_append")
-        # in place, stream-ordered behind the kernel's read of t (the call can be captured in a graph); a sequence
-        # that did not fit (rows = -1) was left alone and does not advance
-        self.t.add_(active * (self.rows >= 0))
+        # t advances in place inside the launch (the call can be captured in a graph); a sequence that did not fit
+        # (rows = -1) was left alone and does not advance
+        _check(unigist_cache_ring_step(self.kc.data_ptr(), self.vc.data_ptr(), k_new.data_ptr(), v_new.data_ptr(),
+                                       k_new.shape[2], self.t.data_ptr(),
+                                       None if active is None else active.data_ptr(), self.cap, self.rows.data_ptr(),
+                                       self.B, self.Hkv, self.D, self.r, self.W, self.sinks, self.mode, self.dt,
+                                       _stream()),
+               "unigist_cache_ring_step")
         return self.rows
 
     def to_ragged(self, ragged: "RaggedKVCache"):

@@ -405,7 +405,22 @@ extern "C" unigist_status unigist_cache_ring_append(void* kc, void* vc, const vo
     if (st != UNIGIST_OK) return st;
     if (cap < 1 || new_rows < 1) return UNIGIST_EINVAL;
     if (!kc || !vc || !k_new || !v_new || !t_old || !n_new || !rows_out) return UNIGIST_EINVAL;
-    hipError_t e = launch_cache_ring_append(kc, vc, k_new, v_new, new_rows, t_old, n_new, cap, rows_out, B, Hkv, D,
+    hipError_t e = launch_cache_ring_append(kc, vc, k_new, v_new, new_rows, t_old, n_new, nullptr, cap, rows_out, B, Hkv, D,
+                                            r >= kMaxL ? kMaxL + 1 : r + 1, sinks > kMaxL ? kMaxL : sinks,
+                                            W > kMaxL ? kMaxL : W, window_mode == UNIGIST_WINDOW_UNITS, dt_bytes(dt), kMaxL,
+                                            (hipStream_t)hip_stream);
+    return e == hipSuccess ? UNIGIST_OK : UNIGIST_ELAUNCH;
+}
+
+extern "C" unigist_status unigist_cache_ring_step(void* kc, void* vc, const void* k_new, const void* v_new, int new_rows,
+                                                  int* t, const int* n_new, int cap, int* rows_out, int B, int Hkv, int D,
+                                                  int r, int W, int sinks, int window_mode, unigist_dtype dt,
+                                                  void* hip_stream) {
+    unigist_status st = check_ring(B, Hkv, D, r, W, sinks, window_mode, dt);
+    if (st != UNIGIST_OK) return st;
+    if (cap < 1 || new_rows < 1) return UNIGIST_EINVAL;
+    if (!kc || !vc || !k_new || !v_new || !t || !rows_out) return UNIGIST_EINVAL;
+    hipError_t e = launch_cache_ring_append(kc, vc, k_new, v_new, new_rows, t, n_new, t, cap, rows_out, B, Hkv, D,
                                             r >= kMaxL ? kMaxL + 1 : r + 1, sinks > kMaxL ? kMaxL : sinks,
                                             W > kMaxL ? kMaxL : W, window_mode == UNIGIST_WINDOW_UNITS, dt_bytes(dt), kMaxL,
                                             (hipStream_t)hip_stream);

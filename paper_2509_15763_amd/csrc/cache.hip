@@ -192,31 +192,17 @@ __global__ __launch_bounds__(256) void cache_ring_convert_kernel(const char* __r
     *(u32x4*)(vc_out + o) = *(const u32x4*)(vc_in + i);
 }
 
-// One token per active sequence, in place.  grid (Hkv, B), 64 lanes: lanes 0 .. cpr-1 move K, lanes 32 .. 32+cpr-1 V;
+// One (sequence, kv head): the new token at position t.  64 lanes: lanes 0 .. cpr-1 move K, lanes 32 .. 32+cpr-1 V;
 // a lane only ever touches its own 16-byte column of the rows, so its reads and writes are ordered by the program.
-__global__ __launch_bounds__(64) void cache_ring_append_kernel(char* __restrict__ kc, char* __restrict__ vc,
-                                                              const char* __restrict__ k_new, const char* __restrict__ v_new,
-                                                              int new_rows, const int* __restrict__ t_old_v,
-                                                              const int* __restrict__ n_new_v, int cap,
-                                                              int* __restrict__ rows_out_v, int Hkv, RingLay g, int row_bytes,
-                                                              int max_pos) {
+__device__ __forceinline__ void ring_append(char* kc, char* vc, const char* k_new, const char* v_new, int new_rows, int t,
+                                            int cap, int bh, const RingLay& g, int row_bytes) {
     const AttnShape& l = g.lay;
-    const int b = blockIdx.y, bh = b * Hkv + blockIdx.x;
-    const int t_old = t_old_v[b], act = n_new_v[b];
-    int rows = -1;
-    const bool ok0 = t_old >= -1 && (act == 0 || act == 1) && t_old < max_pos - act;
-    const int t = t_old + act;
-    if (ok0) {
-        rows = ring_rows(g, t);
-        if (rows > cap || ring_rows(g, t_old) > cap) rows = -1;
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) rows_out_v[b] = rows;
-    if (rows < 0 || act == 0) return;
     const int cpr = row_bytes / 16;
     const int lane = threadIdx.x & 31;
+    const bool is_k = (threadIdx.x & 63) < 32;
     if (lane >= cpr) return;
-    char* c = (threadIdx.x < 32 ? kc : vc) + (size_t)bh * cap * row_bytes + lane * 16;
-    const u32x4 nw = *(const u32x4*)((threadIdx.x < 32 ? k_new : v_new) + (size_t)bh * new_rows * row_bytes + lane * 16);
+    char* c = (is_k ? kc : vc) + (size_t)bh * cap * row_bytes + lane * 16;
+    const u32x4 nw = *(const u32x4*)((is_k ? k_new : v_new) + (size_t)bh * new_rows * row_bytes + lane * 16);
     auto row = [&](int n) { return (u32x4*)(c + (size_t)n * row_bytes); };
     if (!l.umode) {
         const int slot = t % g.W;
@@ -243,6 +229,34 @@ __global__ __launch_bounds__(64) void cache_ring_append_kernel(char* __restrict_
     for (int i = 0; i < u; ++i) *row(slot0 + i) = *row(base - 1 + i);
     *row(base - 1) = gist;
     *row(base) = nw;
+}
+
+// One token per active sequence (n_new_v null: of every sequence), in place.  One workgroup per sequence, one wave per kv
+// head (in turn, from 17 heads on).  t_next (null: not wanted; may be t_old_v) gets the sequences' new last positions,
+// which only a workgroup that holds all of a sequence's readers of t_old can write in place: a caller that advances its
+// positions itself spends a comparison, a product and a sum, three launches of 2 us each, on top of this one of 3 us.
+constexpr int kAppendWaves = 16;
+__global__ __launch_bounds__(64 * kAppendWaves) void cache_ring_append_kernel(
+    char* __restrict__ kc, char* __restrict__ vc, const char* __restrict__ k_new, const char* __restrict__ v_new, int new_rows,
+    const int* t_old_v, const int* __restrict__ n_new_v, int* t_next, int cap, int* __restrict__ rows_out_v, int Hkv,
+    RingLay g, int row_bytes, int max_pos) {
+    const int b = blockIdx.x;
+    const int t_old = t_old_v[b], act = n_new_v ? n_new_v[b] : 1;
+    int rows = -1;
+    const bool ok0 = t_old >= -1 && (act == 0 || act == 1) && t_old < max_pos - act;
+    const int t = t_old + act;
+    if (ok0) {
+        rows = ring_rows(g, t);
+        if (rows > cap || ring_rows(g, t_old) > cap) rows = -1;
+    }
+    __syncthreads();  // every wave has read t_old
+    if (threadIdx.x == 0) {
+        rows_out_v[b] = rows;
+        if (t_next) t_next[b] = rows < 0 ? t_old : t;
+    }
+    if (rows < 0 || act == 0) return;
+    for (int hk = threadIdx.x >> 6; hk < Hkv; hk += blockDim.x >> 6)
+        ring_append(kc, vc, k_new, v_new, new_rows, t, cap, b * Hkv + hk, g, row_bytes);
 }
 
 }  // namespace
@@ -277,11 +291,12 @@ hipError_t launch_cache_ring_convert(bool to_ring, const void* kc_in, const void
 }
 
 hipError_t launch_cache_ring_append(void* kc, void* vc, const void* k_new, const void* v_new, int new_rows, const int* t_old,
-                                    const int* n_new, int cap, int* rows_out, int B, int Hkv, int D, int rp1, int sinks,
-                                    int W, int umode, int elem_bytes, int max_pos, hipStream_t st) {
+                                    const int* n_new, int* t_next, int cap, int* rows_out, int B, int Hkv, int D, int rp1,
+                                    int sinks, int W, int umode, int elem_bytes, int max_pos, hipStream_t st) {
     const RingLay g = make_ring_lay(rp1, sinks, W, umode);
-    cache_ring_append_kernel<<<dim3(Hkv, B), 64, 0, st>>>((char*)kc, (char*)vc, (const char*)k_new, (const char*)v_new, new_rows,
-                                                          t_old, n_new, cap, rows_out, Hkv, g, D * elem_bytes, max_pos);
+    const int waves = Hkv < kAppendWaves ? Hkv : kAppendWaves;
+    cache_ring_append_kernel<<<B, 64 * waves, 0, st>>>((char*)kc, (char*)vc, (const char*)k_new, (const char*)v_new, new_rows,
+                                                       t_old, n_new, t_next, cap, rows_out, Hkv, g, D * elem_bytes, max_pos);
     return hipGetLastError();
 }
 
