@@ -1,0 +1,49 @@
+"""Slices of the split-K decode: lengths around the edges of a slice and of the kernel's 128-key iteration, sequences much
+shorter than the slab (slices without keys), up to 64 slices, every padded column count, both cache types, against
+float64."""
+import pytest
+import torch
+
+import paper_2509_15763_amd as u
+
+pytestmark = pytest.mark.gpu
+
+
+def _exact(q, k, v, n):
+    B, Hq, D = q.shape
+    G = Hq // k.shape[1]
+    out, lse = torch.zeros(B, Hq, D, dtype=torch.float64), torch.full((B, Hq), -float("inf"), dtype=torch.float64)
+    for b in range(B):
+        if n[b] == 0:
+            continue
+        kb, vb = (t[b, :, :n[b]].double().repeat_interleave(G, 0) for t in (k, v))
+        s = (kb @ q[b].double()[:, :, None])[..., 0] / D ** 0.5
+        lse[b] = torch.logsumexp(s, 1)
+        out[b] = (torch.softmax(s, 1)[:, None] @ vb)[:, 0]
+    return out, lse
+
+
+@pytest.mark.parametrize("G", [1, 4, 15, 17])  # 17: the vector kernel
+@pytest.mark.parametrize("D", [8, 32, 64, 80, 128])
+@pytest.mark.parametrize("Lk", [1, 127, 128, 129, 257, 1500, 9001])
+def test_lengths(G, D, Lk):
+    B, Hkv = 3, 1
+    gen = torch.Generator().manual_seed(Lk + D)
+    q = torch.randn(B, G * Hkv, D, generator=gen).bfloat16()
+    k, v = (torch.randn(B, Hkv, Lk, D, generator=gen).bfloat16() for _ in range(2))
+    for n in ([Lk] * 3, [0, min(Lk, 5), max(1, Lk // 3)], [min(Lk, 130), 1, Lk]):
+        sl = torch.tensor(n, dtype=torch.int32).cuda()
+        ws = torch.full((u.unigist_decode_workspace(B, G * Hkv, Hkv, Lk, D, u.UNIGIST_BF16),), 255, dtype=torch.uint8).cuda()
+        out, lse = u.decode(q.cuda(), k.cuda(), v.cuda(), sl, workspace=ws)  # the workspace starts as NaNs
+        o, l = _exact(q, k, v, n)
+        # bf16 P and result: 2^-9 each on values of size at most max |v| <= 5, against float64
+        assert (out.cpu().double() - o).abs().max() <= 2e-2
+        live = torch.isfinite(l)
+        assert torch.equal(torch.isfinite(lse.cpu()), live) and (lse.cpu().double()[live] - l[live]).abs().max() <= 1e-4
+    if D % 16 == 0:
+        one = torch.ones(Hkv).cuda()
+        k8, v8 = (u.quantize_e4m3(t.cuda(), one) for t in (k, v))
+        wide = lambda c: c.cpu().view(torch.float8_e4m3fn).float()
+        out, lse = u.decode_e4m3(q.cuda(), k8, v8, one, one, sl)
+        o, l = _exact(q, wide(k8), wide(v8), n)
+        assert (out.cpu().double() - o).abs().max() <= 2e-2 and (lse.cpu().double() - l).abs().max() <= 1e-4
