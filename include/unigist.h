@@ -101,8 +101,13 @@ unigist_status unigist_attn_fwd_ex(const void* q, const void* k, const void* v, 
  * dq [B,Hq,L,D], dk, dv [B,Hkv,L,D] (dt): out; dk and dv are summed over the
  * Hq/Hkv query heads sharing a kv head.  No atomics are used, so results are
  * bitwise reproducible run to run.
- * workspace: device scratch of at least unigist_attn_bwd_workspace(...) bytes,
- * 256-byte aligned, contents undefined on entry and exit.
+ * workspace: device scratch, 256-byte aligned, contents undefined on entry and exit.
+ * unigist_attn_bwd_workspace(...) bytes give the fastest plan.  Short sequences spread their gist phase over more
+ * partial sums than they need (32/8 heads, D = 128: 64 MB for 4096 tokens at W = 512 instead of 24, 64 for 2 x 2047 at
+ * W = 128 instead of 18, 10 for 1024 instead of 4.5), and the size falls where a longer sequence needs no such help.  A
+ * smaller workspace, down to what the longest segments take -- which grows with L -- is served with longer segments: a
+ * buffer sized for the longest of a caller's sequences serves the shorter ones too.  Below that: UNIGIST_EINVAL.  The
+ * sums are the same, grouped differently.
  */
 unigist_status unigist_attn_bwd(const void* q, const void* k, const void* v, const void* out,
                                 const float* lse, const void* dout, void* dq, void* dk, void* dv,
@@ -113,13 +118,14 @@ unigist_status unigist_attn_bwd(const void* q, const void* k, const void* v, con
 /*
  * The same backward, restricted to some of its stream-ordered stages (for per-kernel timing and
  * debugging).  `stages` is a bit mask; the stages depend on each other in this order, so a caller
- * running them one by one must keep the order and the same workspace:
+ * running them one by one must keep the order and the same workspace, of the same size:
  *   UNIGIST_BWD_DELTA        delta_i = dO_i . O_i                      (Sec. 4.1 softmax backward)
  *   UNIGIST_BWD_DKDV_GIST    dK/dV of the pairs whose gist lies left of the query's window phase
  *   UNIGIST_BWD_GIST_REDUCE  fixed-order sum of that phase's partial results
  *   UNIGIST_BWD_DKDV_WINDOW  dK/dV of the window phase, adds the gist phase, writes dk and dv
  *   UNIGIST_BWD_DQ           writes dq
- * unigist_attn_bwd is this call with UNIGIST_BWD_ALL.  Masks other than UNIGIST_BWD_ALL are
+ * unigist_attn_bwd is this call with UNIGIST_BWD_ALL, which leaves the workspace undefined: it is no start for single
+ * stages.  Masks other than UNIGIST_BWD_ALL are
  * supported for bf16 only (UNIGIST_EUNSUPPORTED otherwise); stages == 0 is UNIGIST_EINVAL.
  */
 enum {
@@ -136,7 +142,7 @@ unigist_status unigist_attn_bwd_stages(const void* q, const void* k, const void*
                                        unigist_dtype dt, void* workspace, size_t workspace_bytes,
                                        unsigned stages, void* hip_stream);
 
-/* Bytes of workspace unigist_attn_bwd needs for this shape (0 on invalid arguments). */
+/* Bytes of workspace for unigist_attn_bwd at its fastest for this shape (0 on invalid arguments). */
 size_t unigist_attn_bwd_workspace(int B, int Hq, int Hkv, int L, int D, int r, int W,
                                   unigist_dtype dt);
 
@@ -192,7 +198,7 @@ unigist_status unigist_attn_bwd_strided(const void* q, const void* k, const void
  * those events; the streams themselves are created by the first such backward call on a device, which therefore
  * has to happen outside a capture).
  * workspace: size from unigist_attn_bwd_varlen_workspace, 256-byte aligned.  bf16: two floats per (head, token)
- * plus the gist-phase partial sums of every document; fp32: one slice per stream, each sized for the longest
+ * plus the gist-phase partial sums of every document (and a smaller one is taken like unigist_attn_bwd's); fp32: one slice per stream, each sized for the longest
  * document.
  */
 unigist_status unigist_attn_fwd_varlen(const void* q, const void* k, const void* v, void* out, float* lse,

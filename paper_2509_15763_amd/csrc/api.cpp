@@ -47,6 +47,13 @@ unigist_status check_attn(int B, int Hq, int Hkv, int L, int D, int r, int W, un
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// Workspace of a backward: the plain-ALU kernels keep delta there and nothing else.  A bf16 call takes any workspace from
+// bwd_least_workspace up (the plain-ALU kernels may be forced at any time, so theirs has to fit too).
+size_t bwd_simple_workspace(const AttnShape& s) { return align256((size_t)s.B * s.Hq * s.L * sizeof(float)); }
+size_t bwd_least_workspace(const AttnShape& s, unigist_dtype dt) {
+    return std::max(bwd_simple_workspace(s), dt == UNIGIST_BF16 ? bwd_mfma_least_workspace(s) : 0);
+}
+
 }  // namespace
 
 extern "C" const char* unigist_status_str(unigist_status s) {
@@ -147,15 +154,14 @@ extern "C" unigist_status unigist_attn_bwd_strided(const void* q, const void* k,
     if (!q || !k || !v || !out || !lse || !dout || !dq || !dk || !dv || !workspace) return UNIGIST_EINVAL;
     if ((st = check_qstrides(q, out, L, D, q_batch_stride, q_head_stride, q_row_stride, dt)) != UNIGIST_OK) return st;
     if ((st = check_qstrides(dout, dq, L, D, q_batch_stride, q_head_stride, q_row_stride, dt)) != UNIGIST_OK) return st;
-    if (workspace_bytes < unigist_attn_bwd_workspace_ex(B, Hq, Hkv, L, D, r, W, sinks, window_mode, dt))
-        return UNIGIST_EINVAL;
-    if (((uintptr_t)workspace & 255) != 0) return UNIGIST_EINVAL;
     AttnShape s = make_shape(B, Hq, Hkv, L, D, r, W, sinks, window_mode);
+    if (workspace_bytes < bwd_least_workspace(s, dt)) return UNIGIST_EINVAL;
+    if (((uintptr_t)workspace & 255) != 0) return UNIGIST_EINVAL;
     s.q_bs = q_batch_stride;
     s.q_hs = q_head_stride;
     s.q_rs = (int)q_row_stride;
-    return launch_bwd_mfma(q, k, v, out, lse, dout, dq, dk, dv, workspace, s, UNIGIST_BWD_ALL, (hipStream_t)hip_stream) ==
-                   hipSuccess
+    return launch_bwd_mfma(q, k, v, out, lse, dout, dq, dk, dv, workspace, workspace_bytes, s, UNIGIST_BWD_ALL,
+                           (hipStream_t)hip_stream) == hipSuccess
                ? UNIGIST_OK
                : UNIGIST_ELAUNCH;
 }
@@ -169,9 +175,7 @@ extern "C" size_t unigist_attn_bwd_workspace_ex(int B, int Hq, int Hkv, int L, i
                                                 int window_mode, unigist_dtype dt) {
     if (check_attn(B, Hq, Hkv, L, D, r, W, dt, sinks, window_mode) != UNIGIST_OK) return 0;
     const AttnShape s = make_shape(B, Hq, Hkv, L, D, r, W, sinks, window_mode);
-    size_t delta = align256((size_t)B * Hq * L * sizeof(float));
-    size_t mfma = dt == UNIGIST_BF16 ? bwd_mfma_workspace(s) : 0;
-    return delta > mfma ? delta : mfma;
+    return std::max(bwd_simple_workspace(s), dt == UNIGIST_BF16 ? bwd_mfma_workspace(s) : 0);
 }
 
 extern "C" unigist_status unigist_attn_bwd_stages(const void* q, const void* k, const void* v, const void* out,
@@ -192,14 +196,13 @@ extern "C" unigist_status unigist_attn_bwd_ex(const void* q, const void* k, cons
     if (st != UNIGIST_OK) return st;
     if (!q || !k || !v || !out || !lse || !dout || !dq || !dk || !dv || !workspace) return UNIGIST_EINVAL;
     if (stages == 0 || (stages & ~(unsigned)UNIGIST_BWD_ALL)) return UNIGIST_EINVAL;
-    if (workspace_bytes < unigist_attn_bwd_workspace_ex(B, Hq, Hkv, L, D, r, W, sinks, window_mode, dt))
-        return UNIGIST_EINVAL;
-    if (((uintptr_t)workspace & 255) != 0) return UNIGIST_EINVAL;
     const AttnShape s = make_shape(B, Hq, Hkv, L, D, r, W, sinks, window_mode);
+    if (workspace_bytes < bwd_least_workspace(s, dt)) return UNIGIST_EINVAL;
+    if (((uintptr_t)workspace & 255) != 0) return UNIGIST_EINVAL;
     hipStream_t stream = (hipStream_t)hip_stream;
     hipError_t e;
     if (dt == UNIGIST_BF16 && !plain_alu_forced()) {
-        e = launch_bwd_mfma(q, k, v, out, lse, dout, dq, dk, dv, workspace, s, stages, stream);
+        e = launch_bwd_mfma(q, k, v, out, lse, dout, dq, dk, dv, workspace, workspace_bytes, s, stages, stream);
     } else {
         if (stages != UNIGIST_BWD_ALL) return UNIGIST_EUNSUPPORTED;
         e = launch_bwd_simple(q, k, v, out, lse, dout, dq, dk, dv, (float*)workspace, s, dt, stream);
@@ -590,6 +593,32 @@ AttnShape doc_shape(int Hq, int Hkv, int T, int D, int r, int W, int sinks, int 
     return s;
 }
 
+constexpr int kLanes = 4;  // streams the fp32 kernels spread the documents over (helper_lanes)
+
+// workspace of a packed backward: what the size query answers, or the least that a call takes (0: the pack is too large)
+size_t varlen_need(int Hq, int Hkv, int T, int D, int r, int W, int sinks, int window_mode, const int* cu, int ndocs,
+                   unigist_dtype dt, bool least) {
+    // document-by-document path: one slice per lane, each large enough for the longest document that lane may get
+    size_t need = 256;
+    for (int d = 0; d < ndocs; ++d) {
+        const int len = cu[d + 1] - cu[d];
+        if (len == 0) continue;
+        const AttnShape s = make_shape(1, Hq, Hkv, len, D, r, W, sinks, window_mode);
+        need = std::max(need, least ? bwd_least_workspace(s, dt)
+                                    : std::max(bwd_simple_workspace(s), dt == UNIGIST_BF16 ? bwd_mfma_workspace(s) : 0));
+    }
+    need = align256(need) * kLanes;
+    if (dt == UNIGIST_BF16) {
+        // single-launch path: delta and lse2 of the whole pack plus every document's gist partial sums.  The larger
+        // of the two is asked for, so that the debug switch to the plain-ALU kernels needs no other buffer.
+        const AttnShape s = doc_shape(Hq, Hkv, T, D, r, W, sinks, window_mode, T);
+        const size_t pack = least ? bwd_mfma_pack_least_workspace(s, cu, ndocs) : bwd_mfma_pack_workspace(s, cu, ndocs);
+        if (pack == 0) return 0;
+        need = std::max(need, pack);
+    }
+    return need;
+}
+
 size_t elem_bytes(unigist_dtype dt) { return dt == UNIGIST_BF16 ? 2 : 4; }
 
 // The bf16 kernels take a whole pack in one launch (launch_*_mfma_pack).  The fp32 kernels run document by
@@ -599,8 +628,6 @@ size_t elem_bytes(unigist_dtype dt) { return dt == UNIGIST_BF16 ? 2 : 4; }
 // state this library holds.  The helpers wait for the caller's stream before their first kernel and the
 // caller's stream waits for them after their last one, so to the caller the call still behaves like work
 // enqueued on its stream.  If the helpers cannot be created everything goes to the caller's stream.
-constexpr int kLanes = 4;
-
 struct Lanes {
     bool tried = false, ok = false;
     hipStream_t st[kLanes - 1];
@@ -732,13 +759,13 @@ extern "C" unigist_status unigist_attn_bwd_varlen_strided(const void* q, const v
     if (!q || !k || !v || !out || !lse || !dout || !dq || !dk || !dv || !workspace) return UNIGIST_EINVAL;
     if ((st = check_qstrides(q, out, T, D, 0, q_head_stride, q_row_stride, dt)) != UNIGIST_OK) return st;
     if ((st = check_qstrides(dout, dq, T, D, 0, q_head_stride, q_row_stride, dt)) != UNIGIST_OK) return st;
-    const size_t need = unigist_attn_bwd_varlen_workspace_ex(Hq, Hkv, T, D, r, W, sinks, window_mode, cu_seqlens, ndocs, dt);
+    const size_t need = varlen_need(Hq, Hkv, T, D, r, W, sinks, window_mode, cu_seqlens, ndocs, dt, true);
     if (workspace_bytes < need) return UNIGIST_EINVAL;
     if (((uintptr_t)workspace & 255) != 0) return UNIGIST_EINVAL;
     AttnShape s = doc_shape(Hq, Hkv, T, D, r, W, sinks, window_mode, T);
     s.q_hs = q_head_stride;
     s.q_rs = (int)q_row_stride;
-    return launch_bwd_mfma_pack(q, k, v, out, lse, dout, dq, dk, dv, workspace, s, cu_seqlens, ndocs,
+    return launch_bwd_mfma_pack(q, k, v, out, lse, dout, dq, dk, dv, workspace, workspace_bytes, s, cu_seqlens, ndocs,
                                 (hipStream_t)hip_stream) == hipSuccess
                ? UNIGIST_OK
                : UNIGIST_ELAUNCH;
@@ -753,23 +780,7 @@ extern "C" size_t unigist_attn_bwd_varlen_workspace_ex(int Hq, int Hkv, int T, i
                                                        int window_mode, const int* cu_seqlens, int ndocs,
                                                        unigist_dtype dt) {
     if (check_docs(Hq, Hkv, T, D, r, W, sinks, window_mode, cu_seqlens, ndocs, dt) != UNIGIST_OK) return 0;
-    // document-by-document path: one slice per lane, each large enough for the longest document that lane may get
-    size_t need = 256;
-    for (int d = 0; d < ndocs; ++d) {
-        const int len = cu_seqlens[d + 1] - cu_seqlens[d];
-        if (len == 0) continue;
-        const size_t n = unigist_attn_bwd_workspace_ex(1, Hq, Hkv, len, D, r, W, sinks, window_mode, dt);
-        if (n > need) need = n;
-    }
-    need = align256(need) * kLanes;
-    if (dt == UNIGIST_BF16) {
-        // single-launch path: delta and lse2 of the whole pack plus every document's gist partial sums.  The larger
-        // of the two is asked for, so that the debug switch to the plain-ALU kernels needs no other buffer.
-        const size_t pack = bwd_mfma_pack_workspace(doc_shape(Hq, Hkv, T, D, r, W, sinks, window_mode, T), cu_seqlens, ndocs);
-        if (pack == 0) return 0;
-        need = std::max(need, pack);
-    }
-    return need;
+    return varlen_need(Hq, Hkv, T, D, r, W, sinks, window_mode, cu_seqlens, ndocs, dt, false);
 }
 
 extern "C" unigist_status unigist_attn_bwd_varlen(const void* q, const void* k, const void* v, const void* out,
@@ -790,12 +801,12 @@ extern "C" unigist_status unigist_attn_bwd_varlen_ex(const void* q, const void* 
     unigist_status st = check_docs(Hq, Hkv, T, D, r, W, sinks, window_mode, cu_seqlens, ndocs, dt);
     if (st != UNIGIST_OK) return st;
     if (!q || !k || !v || !out || !lse || !dout || !dq || !dk || !dv || !workspace) return UNIGIST_EINVAL;
-    const size_t need = unigist_attn_bwd_varlen_workspace_ex(Hq, Hkv, T, D, r, W, sinks, window_mode, cu_seqlens, ndocs, dt);
+    const size_t need = varlen_need(Hq, Hkv, T, D, r, W, sinks, window_mode, cu_seqlens, ndocs, dt, true);
     if (workspace_bytes < need) return UNIGIST_EINVAL;
     if (((uintptr_t)workspace & 255) != 0) return UNIGIST_EINVAL;
     if (dt == UNIGIST_BF16 && !plain_alu_forced()) {  // one launch per kernel, the workgroups look their document up
         const AttnShape s = doc_shape(Hq, Hkv, T, D, r, W, sinks, window_mode, T);
-        return launch_bwd_mfma_pack(q, k, v, out, lse, dout, dq, dk, dv, workspace, s, cu_seqlens, ndocs,
+        return launch_bwd_mfma_pack(q, k, v, out, lse, dout, dq, dk, dv, workspace, workspace_bytes, s, cu_seqlens, ndocs,
                                     (hipStream_t)hip_stream) == hipSuccess
                    ? UNIGIST_OK
                    : UNIGIST_ELAUNCH;
@@ -803,7 +814,7 @@ extern "C" unigist_status unigist_attn_bwd_varlen_ex(const void* q, const void* 
     size_t slice = 256;
     for (int d = 0; d < ndocs; ++d) {
         const int len = cu_seqlens[d + 1] - cu_seqlens[d];
-        if (len > 0) slice = std::max(slice, align256(unigist_attn_bwd_workspace_ex(1, Hq, Hkv, len, D, r, W, sinks, window_mode, dt)));
+        if (len > 0) slice = std::max(slice, bwd_simple_workspace(make_shape(1, Hq, Hkv, len, D, r, W, sinks, window_mode)));
     }
     const size_t eb = elem_bytes(dt);
     // the documents of one lane run one after the other on its stream and share that lane's workspace slice

@@ -75,12 +75,18 @@ int pick_segc(long steps) {
     if (steps >= slots * 8 / 2) return 8;
     return steps >= slots * 4 / 2 ? 4 : 2;
 }
+// The longest segments a launch takes for want of room.  A workspace for them is all that a call insists on: it grows with
+// the sequence, where the one for pick_segc's shrinks at each of its lines (32/8 heads, W 512: 74 MB at 3520 rows, 42 MB
+// at 3521), and a buffer sized for the longest of a caller's sequences has to serve the shorter ones.
+int roomiest_segc(long steps) { return std::max(pick_segc(steps), 16); }
 
-BwdPlan make_plan(const AttnShape& s) {
+long launch_steps(const AttnShape& s) { return gist_chunk_steps(s) * s.B * s.Hkv; }
+
+// plan and workspace layout for segments of segc chunks, without the launch order
+BwdPlan sized_plan(const AttnShape& s, int segc) {
     BwdPlan p;
-    plan_counts(s, p, pick_segc(gist_chunk_steps(s) * s.B * s.Hkv));
+    plan_counts(s, p, segc);
     plan_slots(s, p);
-    plan_order(s, p);
     const size_t a = 255;
     size_t off = ((size_t)s.B * s.Hq * s.L * sizeof(float) + a) & ~a;
     p.off_lse2 = off;  // lse * log2(e), written by the delta pass
@@ -91,6 +97,16 @@ BwdPlan make_plan(const AttnShape& s) {
     p.off_comp = off;  // their sums over the segments: one block per (batch, kv head, compact tile)
     off += (size_t)s.B * s.Hkv * p.n_gt * 2 * padded_head_dim(s.D) * BNK * sizeof(float);
     p.total = (off + a) & ~a;
+    return p;
+}
+
+// the plan of a launch whose workspace has `room` bytes: pick_segc's, or the first doubling of it that fits
+BwdPlan make_plan(const AttnShape& s, size_t room = SIZE_MAX) {
+    const long steps = launch_steps(s);
+    int segc = pick_segc(steps);
+    BwdPlan p = sized_plan(s, segc);
+    while (p.total > room && segc < roomiest_segc(steps)) p = sized_plan(s, segc *= 2);
+    plan_order(s, p);
     return p;
 }
 
@@ -329,9 +345,9 @@ __global__ __launch_bounds__(NT, 2) void bwd_joint_kernel(const bf16_t* __restri
 
 template <int D>
 hipError_t bwd_launch(const bf16_t* q, const bf16_t* k, const bf16_t* v, const bf16_t* out, const float* lse,
-                      const bf16_t* dout, bf16_t* dq, bf16_t* dk, bf16_t* dv, char* ws, const AttnShape& s,
-                      unsigned stages, hipStream_t st) {
-    const BwdPlan pl = make_plan(s);
+                      const bf16_t* dout, bf16_t* dq, bf16_t* dk, bf16_t* dv, char* ws, size_t room,
+                      const AttnShape& s, unsigned stages, hipStream_t st) {
+    const BwdPlan pl = make_plan(s, room);
     const bool gen = s.S != 0 || s.umode != 0;
     const bool qstr = s.q_rs != 0;  // q, out, dout, dq with the caller's explicit strides
     float* delta = (float*)ws;
@@ -401,15 +417,10 @@ struct PackPlan {
     size_t off_lse2, off_part, off_comp, total;
 };
 
-PackPlan make_pack_plan(const AttnShape& s, const int* cu, int ndocs) {
+// the plan for segments of segc chunks; order = the non-empty documents, longest first
+PackPlan sized_pack_plan(const AttnShape& s, const int* cu, const std::vector<int>& order, int segc) {
     PackPlan pp;
-    std::vector<int> order;
-    for (int d = 0; d < ndocs; ++d)
-        if (cu[d + 1] > cu[d]) order.push_back(d);
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cu[a + 1] - cu[a] > cu[b + 1] - cu[b]; });
-    long steps = 0;
-    for (int d : order) steps += gist_chunk_steps(doc_view(s, cu[d + 1] - cu[d]));
-    pp.segc = pick_segc(steps * s.Hkv);
+    pp.segc = segc;
     size_t nslot_part = 0, nslot_comp = 0;
     for (int d : order) {
         BwdPlan pl;
@@ -435,11 +446,26 @@ PackPlan make_pack_plan(const AttnShape& s, const int* cu, int ndocs) {
     return pp;
 }
 
+// the plan for a workspace of `room` bytes, like make_plan's (room 0: the least that a call insists on)
+PackPlan make_pack_plan(const AttnShape& s, const int* cu, int ndocs, size_t room) {
+    std::vector<int> order;
+    for (int d = 0; d < ndocs; ++d)
+        if (cu[d + 1] > cu[d]) order.push_back(d);
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cu[a + 1] - cu[a] > cu[b + 1] - cu[b]; });
+    long steps = 0;
+    for (int d : order) steps += gist_chunk_steps(doc_view(s, cu[d + 1] - cu[d]));
+    steps *= s.Hkv;
+    int segc = room == 0 ? roomiest_segc(steps) : pick_segc(steps);
+    PackPlan pp = sized_pack_plan(s, cu, order, segc);
+    while (pp.total > room && segc < roomiest_segc(steps)) pp = sized_pack_plan(s, cu, order, segc *= 2);
+    return pp;
+}
+
 template <int D>
 hipError_t bwd_launch_pack(const bf16_t* q, const bf16_t* k, const bf16_t* v, const bf16_t* out, const float* lse,
-                           const bf16_t* dout, bf16_t* dq, bf16_t* dk, bf16_t* dv, char* ws, const AttnShape& s,
+                           const bf16_t* dout, bf16_t* dq, bf16_t* dk, bf16_t* dv, char* ws, size_t room, const AttnShape& s,
                            const int* cu, int ndocs, hipStream_t st) {
-    const PackPlan pp = make_pack_plan(s, cu, ndocs);
+    const PackPlan pp = make_pack_plan(s, cu, ndocs, room);
     if (pp.total == 0) return hipErrorInvalidValue;
     float* delta = (float*)ws;
     float* lse2 = (float*)(ws + pp.off_lse2);
@@ -518,11 +544,13 @@ hipError_t bwd_launch_pack(const bf16_t* q, const bf16_t* k, const bf16_t* v, co
 
 }  // namespace
 
-size_t bwd_mfma_workspace(const AttnShape& s) { return make_plan(s).total; }
+size_t bwd_mfma_workspace(const AttnShape& s) { return sized_plan(s, pick_segc(launch_steps(s))).total; }
+size_t bwd_mfma_least_workspace(const AttnShape& s) { return sized_plan(s, roomiest_segc(launch_steps(s))).total; }
 
 BwdPlan make_bwd_plan(const AttnShape& s) { return make_plan(s); }
 
-size_t bwd_mfma_pack_workspace(const AttnShape& s, const int* cu, int ndocs) { return make_pack_plan(s, cu, ndocs).total; }
+size_t bwd_mfma_pack_workspace(const AttnShape& s, const int* cu, int ndocs) { return make_pack_plan(s, cu, ndocs, SIZE_MAX).total; }
+size_t bwd_mfma_pack_least_workspace(const AttnShape& s, const int* cu, int ndocs) { return make_pack_plan(s, cu, ndocs, 0).total; }
 
 // A head dimension below the one the kernels are built for goes through the instantiations for explicit strides of
 // q, out, dout and dq, with the strides of the dense layout.
@@ -536,25 +564,25 @@ static AttnShape with_dense_strides_if_padded(AttnShape s) {
 }
 
 hipError_t launch_bwd_mfma_pack(const void* q, const void* k, const void* v, const void* out, const float* lse,
-                                const void* dout, void* dq, void* dk, void* dv, void* ws, const AttnShape& s_in,
-                                const int* cu, int ndocs, hipStream_t st) {
+                                const void* dout, void* dq, void* dk, void* dv, void* ws, size_t room,
+                                const AttnShape& s_in, const int* cu, int ndocs, hipStream_t st) {
     const AttnShape s = with_dense_strides_if_padded(s_in);
     if (s.D <= 64)
         return bwd_launch_pack<64>((const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (const bf16_t*)out, lse,
-                                   (const bf16_t*)dout, (bf16_t*)dq, (bf16_t*)dk, (bf16_t*)dv, (char*)ws, s, cu, ndocs, st);
+                                   (const bf16_t*)dout, (bf16_t*)dq, (bf16_t*)dk, (bf16_t*)dv, (char*)ws, room, s, cu, ndocs, st);
     return bwd_launch_pack<128>((const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (const bf16_t*)out, lse,
-                                (const bf16_t*)dout, (bf16_t*)dq, (bf16_t*)dk, (bf16_t*)dv, (char*)ws, s, cu, ndocs, st);
+                                (const bf16_t*)dout, (bf16_t*)dq, (bf16_t*)dk, (bf16_t*)dv, (char*)ws, room, s, cu, ndocs, st);
 }
 
 hipError_t launch_bwd_mfma(const void* q, const void* k, const void* v, const void* out, const float* lse,
-                           const void* dout, void* dq, void* dk, void* dv, void* ws, const AttnShape& s_in,
-                           unsigned stages, hipStream_t st) {
+                           const void* dout, void* dq, void* dk, void* dv, void* ws, size_t room,
+                           const AttnShape& s_in, unsigned stages, hipStream_t st) {
     const AttnShape s = with_dense_strides_if_padded(s_in);
     if (s.D <= 64)
         return bwd_launch<64>((const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (const bf16_t*)out, lse,
-                              (const bf16_t*)dout, (bf16_t*)dq, (bf16_t*)dk, (bf16_t*)dv, (char*)ws, s, stages, st);
+                              (const bf16_t*)dout, (bf16_t*)dq, (bf16_t*)dk, (bf16_t*)dv, (char*)ws, room, s, stages, st);
     return bwd_launch<128>((const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (const bf16_t*)out, lse,
-                           (const bf16_t*)dout, (bf16_t*)dq, (bf16_t*)dk, (bf16_t*)dv, (char*)ws, s, stages, st);
+                           (const bf16_t*)dout, (bf16_t*)dq, (bf16_t*)dk, (bf16_t*)dv, (char*)ws, room, s, stages, st);
 }
 
 }  // namespace unigist

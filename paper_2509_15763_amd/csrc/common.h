@@ -210,15 +210,19 @@ hipError_t launch_fwd_mfma_pack(const void* q, const void* k, const void* v, voi
 // chunk-wise prefill with per-sequence states (s: the launch's shape, see seq_view; cap = s.kv_rows)
 hipError_t launch_fwd_mfma_ragged(const void* q, const void* k, const void* v, void* out, float* lse,
                                   const AttnShape& s, const RaggedSeqs& seqs, hipStream_t st);
+// ws: bwd_mfma_workspace bytes for the fastest plan; with fewer (`room`), but at least bwd_mfma_least_workspace, longer
+// gist-phase segments are taken
 size_t bwd_mfma_workspace(const AttnShape& s);
+size_t bwd_mfma_least_workspace(const AttnShape& s);
 hipError_t launch_bwd_mfma(const void* q, const void* k, const void* v, const void* out, const float* lse,
-                           const void* dout, void* dq, void* dk, void* dv, void* ws,
+                           const void* dout, void* dq, void* dk, void* dv, void* ws, size_t room,
                            const AttnShape& s, unsigned stages, hipStream_t st);
-// packed documents (see launch_fwd_mfma_pack); ws: bwd_mfma_pack_workspace bytes (0: the pack is too large)
+// packed documents (see launch_fwd_mfma_pack); ws: bwd_mfma_pack_workspace bytes (0: the pack is too large), or fewer as above
 size_t bwd_mfma_pack_workspace(const AttnShape& s, const int* cu, int ndocs);
+size_t bwd_mfma_pack_least_workspace(const AttnShape& s, const int* cu, int ndocs);
 hipError_t launch_bwd_mfma_pack(const void* q, const void* k, const void* v, const void* out, const float* lse,
-                                const void* dout, void* dq, void* dk, void* dv, void* ws, const AttnShape& s,
-                                const int* cu, int ndocs, hipStream_t st);
+                                const void* dout, void* dq, void* dk, void* dv, void* ws, size_t room,
+                                const AttnShape& s, const int* cu, int ndocs, hipStream_t st);
 bool decode_grouped(int Hq, int Hkv, unigist_dtype dt);
 int decode_num_splits(int B, int Hq, int Hkv, int Lk, unigist_dtype dt);
 hipError_t launch_cache_update(const void* kc_in, const void* vc_in, int s_old, int t_old, int cap_in,

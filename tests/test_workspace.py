@@ -1,0 +1,79 @@
+"""The least workspace a backward takes: the one for gist-phase segments of 16 query chunks (32 in launches of many rounds),
+which grows with the sequence, whatever shorter segments the plan of a large enough workspace has.  Probed through the
+entry points with pointers that are never dereferenced: a call with too small a workspace is refused before anything is
+launched, any other ends at the launch where there is no GPU."""
+import pytest
+import torch
+
+import paper_2509_15763_amd as u
+
+pytestmark = pytest.mark.skipif(torch.cuda.is_available(), reason="an accepted call would launch")
+FAKE = 0x1000
+EINVAL = 1
+
+
+def _a(x):
+    return (x + 255) & ~255
+
+
+def _least_accepted(call, at_most):
+    """Smallest workspace that `call` does not refuse."""
+    lo, hi = 0, at_most
+    while lo < hi:
+        mid = (lo + hi) // 2
+        lo, hi = (mid + 1, hi) if call(mid) == EINVAL else (lo, mid)
+    return lo
+
+
+def _sums(L, r, W, segc):
+    """(slots, reduced tiles, chunk steps) per kv head for segments of segc chunks: a chunk c of 64 rows sees the gists left
+    of its window's 128-key tile from afar, a segment has a slot for each 128 gists its last chunk sees."""
+    NC = -(-L // 64)
+    tiles = [-(-(max(0, 64 * c - min(W, L) + 1) // 128 * 128 // (r + 1)) // 128) for c in range(NC)]
+    while -(-NC // segc) > 32:
+        segc *= 2
+    return sum(tiles[min(NC, s + segc) - 1] for s in range(0, NC, segc)), tiles[-1], sum(tiles)
+
+
+def _least_by_rule(B, Hq, Hkv, docs, D, r, W):
+    steps = sum(_sums(L, r, W, 16)[2] for L in docs) * B * Hkv
+    segc = 32 if steps >= 512 * 32 * 5 else 16
+    block = 2 * (64 if D <= 64 else 128) * 128 * 4
+    part = sum(_sums(L, r, W, segc)[0] for L in docs) * B * Hkv * block
+    comp = sum(_sums(L, r, W, segc)[1] for L in docs) * B * Hkv * block
+    return 2 * _a(B * Hq * sum(docs) * 4) + part + comp
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,D,r,W", [(1, 32, 8, 128, 4, 512), (2, 32, 8, 128, 4, 128), (1, 8, 1, 64, 2, 64), (1, 28, 4, 96, 8, 900)])
+def test_backward_takes_what_segments_of_16_need(B, Hq, Hkv, D, r, W):
+    last = 0
+    for L in list(range(1, 12000, 331)) + [2047, 3520, 3521, 4864, 4865, 8192, 8193, 32768, 70000]:
+        shape = (B, Hq, Hkv, L, D, r, W, u.UNIGIST_BF16)
+        query = u.unigist_attn_bwd_workspace(*shape)
+        got = _least_accepted(lambda n: u.unigist_attn_bwd(*([FAKE] * 9), *shape, FAKE, n), query)
+        assert got == _least_by_rule(B, Hq, Hkv, [L], D, r, W) <= query, L
+        sd = (L * Hq * D, D, Hq * D)
+        strided = lambda n: u.unigist_attn_bwd_strided(*([FAKE] * 9), B, Hq, Hkv, L, D, r, W, 0, 0, *sd, u.UNIGIST_BF16, FAKE, n)
+        assert strided(got) != EINVAL and strided(got - 1) == EINVAL
+
+
+@pytest.mark.parametrize("sinks,mode", [(0, 0), (70, 0), (5, 1)])
+def test_a_buffer_for_the_longest_sequence_serves_the_shorter_ones(sinks, mode):
+    W = 512 if mode == 0 else 100
+    lengths = [100, 1024, 2047, 3000, 3520, 3521, 4000, 4864, 4865, 6000, 8192, 8193, 12000, 40000]
+    for a, longer in enumerate(lengths):
+        n = u.unigist_attn_bwd_workspace_ex(1, 32, 8, longer, 128, 4, W, sinks, mode, u.UNIGIST_BF16)
+        for L in lengths[:a + 1]:
+            assert u.unigist_attn_bwd_ex(*([FAKE] * 9), 1, 32, 8, L, 128, 4, W, sinks, mode, u.UNIGIST_BF16, FAKE, n, 31) != EINVAL
+
+
+@pytest.mark.parametrize("docs", [[2047], [300, 4096, 1, 5000], [3520] * 3, [8193, 100], [1024] * 70, [32768]])
+def test_packs(docs):
+    Hq, Hkv, D, r, W = 32, 8, 128, 4, 512
+    cu = [sum(docs[:i]) for i in range(len(docs) + 1)]
+    query = u.unigist_attn_bwd_varlen_workspace(Hq, Hkv, cu[-1], D, r, W, cu, u.UNIGIST_BF16)
+    call = lambda n: u.unigist_attn_bwd_varlen(*([FAKE] * 9), Hq, Hkv, cu[-1], D, r, W, cu, u.UNIGIST_BF16, FAKE, n)
+    got = _least_accepted(call, query)
+    # the pack's own need, or four slices for its longest document taken alone
+    alone = max(_least_by_rule(1, Hq, Hkv, [L], D, r, W) for L in docs)
+    assert got == max(_a(_least_by_rule(1, Hq, Hkv, docs, D, r, W)), 4 * _a(alone)) <= query
