@@ -254,7 +254,9 @@ unigist_status unigist_attn_bwd_varlen_strided(const void* q, const void* k, con
  *            NULL means Lk_max for all.
  *   out [B,Hq,D] (dt): out.  lse [B,Hq] float: out, may be NULL.
  * Split-K over the keys with a log-sum-exp combine (FlashDecoding style).
- * workspace: at least unigist_decode_workspace(...) bytes, 256-byte aligned.
+ * workspace: unigist_decode_workspace(...) bytes, 256-byte aligned.  The size is larger for a batch of up to 64
+ * (sequence, kv head) pairs, whose slices are shorter, than for the next larger ones; such a batch is served with longer
+ * slices from a workspace without room for the short ones.  Too small for those as well: UNIGIST_EINVAL.
  */
 unigist_status unigist_decode(const void* q, const void* kcache, const void* vcache, void* out,
                               float* lse, int B, int Hq, int Hkv, int Lk_max, const int* seqlens,

@@ -221,8 +221,7 @@ extern "C" unigist_status unigist_attn_bwd(const void* q, const void* k, const v
 extern "C" size_t unigist_decode_workspace(int B, int Hq, int Hkv, int Lk_max, int D, unigist_dtype dt) {
     if (B < 1 || Hq < 1 || Hkv < 1 || Lk_max < 1 || Hq % Hkv != 0) return 0;
     if (!head_dim_ok(D, dt) || (dt != UNIGIST_BF16 && dt != UNIGIST_F32)) return 0;
-    const int ns = decode_num_splits(B, Hq, Hkv, Lk_max, dt);
-    return align256((size_t)B * Hq * ns * (padded_head_dim(D) + 2) * sizeof(float));
+    return decode_split_bytes(B, Hq, decode_num_splits(B, Hq, Hkv, Lk_max, D, dt, SIZE_MAX), D);
 }
 
 extern "C" unigist_status unigist_decode(const void* q, const void* kcache, const void* vcache, void* out,
@@ -235,10 +234,10 @@ extern "C" unigist_status unigist_decode(const void* q, const void* kcache, cons
     if (!head_dim_ok(D, dt)) return UNIGIST_EUNSUPPORTED;
     if (B > 65535 || Hq > 65535) return UNIGIST_EUNSUPPORTED;
     if (!q || !kcache || !vcache || !out || !workspace) return UNIGIST_EINVAL;
-    if (workspace_bytes < unigist_decode_workspace(B, Hq, Hkv, Lk_max, D, dt)) return UNIGIST_EINVAL;
+    if (workspace_bytes < decode_split_bytes(B, Hq, decode_least_splits(B, Hq, Hkv, Lk_max, dt), D)) return UNIGIST_EINVAL;
     if (((uintptr_t)workspace & 255) != 0) return UNIGIST_EINVAL;
     hipError_t e = launch_decode(q, kcache, vcache, out, lse, B, Hq, Hkv, Lk_max, seqlens, D, dt,
-                                 (float*)workspace, (hipStream_t)hip_stream);
+                                 (float*)workspace, workspace_bytes, (hipStream_t)hip_stream);
     return e == hipSuccess ? UNIGIST_OK : UNIGIST_ELAUNCH;
 }
 
@@ -262,11 +261,11 @@ extern "C" unigist_status unigist_decode_e4m3(const void* q, const void* kcache,
     if (!head_dim_ok(D, UNIGIST_E4M3)) return UNIGIST_EUNSUPPORTED;
     if (B > 65535 || Hq > 65535) return UNIGIST_EUNSUPPORTED;
     if (!q || !kcache || !vcache || !k_scale || !v_scale || !out || !workspace) return UNIGIST_EINVAL;
-    if (workspace_bytes < unigist_decode_workspace(B, Hq, Hkv, Lk_max, D, UNIGIST_BF16)) return UNIGIST_EINVAL;
+    if (workspace_bytes < decode_split_bytes(B, Hq, decode_least_splits(B, Hq, Hkv, Lk_max, UNIGIST_BF16), D)) return UNIGIST_EINVAL;
     if (((uintptr_t)workspace & 255) != 0) return UNIGIST_EINVAL;
     if (((uintptr_t)kcache & 15) != 0 || ((uintptr_t)vcache & 15) != 0 || ((uintptr_t)q & 15) != 0) return UNIGIST_EINVAL;
     hipError_t e = launch_decode_fp8(q, kcache, vcache, k_scale, v_scale, out, lse, B, Hq, Hkv, Lk_max, seqlens, D,
-                                     (float*)workspace, (hipStream_t)hip_stream);
+                                     (float*)workspace, workspace_bytes, (hipStream_t)hip_stream);
     return e == hipSuccess ? UNIGIST_OK : UNIGIST_ELAUNCH;
 }
 

@@ -224,7 +224,13 @@ hipError_t launch_bwd_mfma_pack(const void* q, const void* k, const void* v, con
                                 const void* dout, void* dq, void* dk, void* dv, void* ws, size_t room,
                                 const AttnShape& s, const int* cu, int ndocs, hipStream_t st);
 bool decode_grouped(int Hq, int Hkv, unigist_dtype dt);
-int decode_num_splits(int B, int Hq, int Hkv, int Lk, unigist_dtype dt);
+// slices per sequence of a decode whose workspace has `room` bytes, and the fewest that a call insists on room for
+int decode_num_splits(int B, int Hq, int Hkv, int Lk, int D, unigist_dtype dt, size_t room);
+int decode_least_splits(int B, int Hq, int Hkv, int Lk, unigist_dtype dt);
+// bytes of n slices' partial results (m, l and an accumulator each)
+inline size_t decode_split_bytes(int B, int Hq, int n, int D) {
+    return ((size_t)B * Hq * n * (padded_head_dim(D) + 2) * sizeof(float) + 255) & ~(size_t)255;
+}
 hipError_t launch_cache_update(const void* kc_in, const void* vc_in, int s_old, int t_old, int cap_in,
                                const void* k_new, const void* v_new, int n_new, int new_rows,
                                void* kc_out, void* vc_out, int s_new, int cap_out,
@@ -243,11 +249,11 @@ hipError_t launch_cache_ring_append(void* kc, void* vc, const void* k_new, const
                                     int sinks, int W, int umode, int elem_bytes, int max_pos, hipStream_t st);
 hipError_t launch_decode(const void* q, const void* kc, const void* vc, void* out, float* lse,
                          int B, int Hq, int Hkv, int Lk, const int* seqlens, int D, unigist_dtype dt,
-                         float* ws, hipStream_t st);
+                         float* ws, size_t room, hipStream_t st);
 // bf16 queries over a cache of E4M3 codes with one scale per kv head (device arrays of Hkv floats)
 hipError_t launch_decode_fp8(const void* q, const void* kc, const void* vc, const float* k_scale, const float* v_scale,
                              void* out, float* lse, int B, int Hq, int Hkv, int Lk, const int* seqlens, int D,
-                             float* ws, hipStream_t st);
+                             float* ws, size_t room, hipStream_t st);
 // the first `rows` rows of every [cap, D] slab of E4M3 codes -> bf16 (exact), slabs of `rows` rows; BH slabs
 hipError_t launch_widen_e4m3(const void* codes, void* y, int BH, int cap, int rows, int D, hipStream_t st);
 // y = e4m3(x / scale[head]) for x [B, H, n, D] (bf16 or fp32), 16 elements per lane

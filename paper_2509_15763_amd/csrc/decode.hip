@@ -504,10 +504,10 @@ __global__ __launch_bounds__(kThreads, E4M3 ? 4 : 3) void decode_split_mfma_kern
 template <typename TQ, typename T, int D>
 hipError_t decode_launch(const void* q, const void* kc, const void* vc, const float* k_scale, const float* v_scale,
                          void* out, float* lse, int B, int Hq, int Hkv, int Lk, const int* seqlens, int Dt, float* ws,
-                         hipStream_t st) {
+                         size_t room, hipStream_t st) {
     constexpr int U = kUnroll;
     constexpr unigist_dtype dt = std::is_same<TQ, float>::value ? UNIGIST_F32 : UNIGIST_BF16;
-    const int nsplit = decode_num_splits(B, Hq, Hkv, Lk, dt);
+    const int nsplit = decode_num_splits(B, Hq, Hkv, Lk, Dt, dt, room);
     const float scale = 1.0f / sqrtf((float)Dt);
     if (decode_grouped(Hq, Hkv, dt) && Hq / Hkv == 4) {
         dim3 grid(nsplit, Hkv, B);
@@ -539,14 +539,16 @@ bool decode_grouped(int Hq, int Hkv, unigist_dtype dt) {
 // small price per slice for the partial results the combine kernel has to merge, and never slices shorter than
 // 256 keys -- 128, one iteration of the kernel, where up to 64 (sequence, head) units leave most of the chip idle: 1500 keys
 // x 8 kv heads 9.8 -> 8.4 us, 300 keys 9.3 -> 8.2 (both kernels).  Measured on batches of 1 to 256 sequences: one round is best up to 64 (sequence, head) units, two up
-// to 256 units, four beyond.
-int decode_num_splits(int B, int Hq, int Hkv, int Lk, unigist_dtype dt) {
-    const long units = (long)B * (decode_grouped(Hq, Hkv, dt) ? Hkv : Hq);
+// to 256 units, four beyond.  A workspace too small for the shorter slices (whose size would otherwise fall where a batch
+// passes 64 units, so that a loop that sized its buffer for 9 to 12 sequences could not run 8) is served with 256 keys.
+namespace {
+long decode_units(int B, int Hq, int Hkv, unigist_dtype dt) { return (long)B * (decode_grouped(Hq, Hkv, dt) ? Hkv : Hq); }
+
+int best_splits(long units, int Lk, int min_keys) {
     const long target = units <= 64 ? 256 : units <= 256 ? 512 : 1024;
     long nmax = (target + units - 1) / units;
     if (nmax < 4) nmax = 4;
     if (nmax > 64) nmax = 64;
-    const int min_keys = units <= 64 ? 128 : 256;
     const long cap = (Lk + min_keys - 1) / min_keys;
     if (nmax > cap) nmax = cap;
     if (nmax < 1) nmax = 1;
@@ -563,19 +565,28 @@ int decode_num_splits(int B, int Hq, int Hkv, int Lk, unigist_dtype dt) {
     }
     return best;
 }
+}  // namespace
+
+int decode_least_splits(int B, int Hq, int Hkv, int Lk, unigist_dtype dt) { return best_splits(decode_units(B, Hq, Hkv, dt), Lk, 256); }
+
+int decode_num_splits(int B, int Hq, int Hkv, int Lk, int D, unigist_dtype dt, size_t room) {
+    const long units = decode_units(B, Hq, Hkv, dt);
+    const int n = best_splits(units, Lk, units <= 64 ? 128 : 256);  // at least as many as with 256 keys
+    return decode_split_bytes(B, Hq, n, D) <= room ? n : decode_least_splits(B, Hq, Hkv, Lk, dt);
+}
 
 namespace {
 // bf16 queries over a bf16 or E4M3 cache: the matrix-core kernel when the group fits its columns, else one
 // workgroup per query head with the vector kernel
 template <bool E4M3>
 hipError_t decode_bf16q(const void* q, const void* kc, const void* vc, const float* k_scale, const float* v_scale, void* out,
-                        float* lse, int B, int Hq, int Hkv, int Lk, const int* seqlens, int D, float* ws, hipStream_t st) {
+                        float* lse, int B, int Hq, int Hkv, int Lk, const int* seqlens, int D, float* ws, size_t room, hipStream_t st) {
     if (!decode_grouped(Hq, Hkv, UNIGIST_BF16)) {
         using T = std::conditional_t<E4M3, fp8_t, bf16_t>;
-        return D <= 64 ? decode_launch<bf16_t, T, 64>(q, kc, vc, k_scale, v_scale, out, lse, B, Hq, Hkv, Lk, seqlens, D, ws, st)
-                       : decode_launch<bf16_t, T, 128>(q, kc, vc, k_scale, v_scale, out, lse, B, Hq, Hkv, Lk, seqlens, D, ws, st);
+        return D <= 64 ? decode_launch<bf16_t, T, 64>(q, kc, vc, k_scale, v_scale, out, lse, B, Hq, Hkv, Lk, seqlens, D, ws, room, st)
+                       : decode_launch<bf16_t, T, 128>(q, kc, vc, k_scale, v_scale, out, lse, B, Hq, Hkv, Lk, seqlens, D, ws, room, st);
     }
-    const int nsplit = decode_num_splits(B, Hq, Hkv, Lk, UNIGIST_BF16);
+    const int nsplit = decode_num_splits(B, Hq, Hkv, Lk, D, UNIGIST_BF16, room);
     const float scale = 1.0f / sqrtf((float)D);
     const dim3 grid(nsplit, Hkv, B);
     if (D <= 64)
@@ -593,17 +604,18 @@ hipError_t decode_bf16q(const void* q, const void* kc, const void* vc, const flo
 }  // namespace
 
 hipError_t launch_decode(const void* q, const void* kc, const void* vc, void* out, float* lse, int B, int Hq,
-                         int Hkv, int Lk, const int* seqlens, int D, unigist_dtype dt, float* ws, hipStream_t st) {
+                         int Hkv, int Lk, const int* seqlens, int D, unigist_dtype dt, float* ws, size_t room,
+                         hipStream_t st) {
     if (dt == UNIGIST_F32)
-        return D <= 64 ? decode_launch<float, float, 64>(q, kc, vc, nullptr, nullptr, out, lse, B, Hq, Hkv, Lk, seqlens, D, ws, st)
-                       : decode_launch<float, float, 128>(q, kc, vc, nullptr, nullptr, out, lse, B, Hq, Hkv, Lk, seqlens, D, ws, st);
-    return decode_bf16q<false>(q, kc, vc, nullptr, nullptr, out, lse, B, Hq, Hkv, Lk, seqlens, D, ws, st);
+        return D <= 64 ? decode_launch<float, float, 64>(q, kc, vc, nullptr, nullptr, out, lse, B, Hq, Hkv, Lk, seqlens, D, ws, room, st)
+                       : decode_launch<float, float, 128>(q, kc, vc, nullptr, nullptr, out, lse, B, Hq, Hkv, Lk, seqlens, D, ws, room, st);
+    return decode_bf16q<false>(q, kc, vc, nullptr, nullptr, out, lse, B, Hq, Hkv, Lk, seqlens, D, ws, room, st);
 }
 
 hipError_t launch_decode_fp8(const void* q, const void* kc, const void* vc, const float* k_scale, const float* v_scale,
                              void* out, float* lse, int B, int Hq, int Hkv, int Lk, const int* seqlens, int D,
-                             float* ws, hipStream_t st) {
-    return decode_bf16q<true>(q, kc, vc, k_scale, v_scale, out, lse, B, Hq, Hkv, Lk, seqlens, D, ws, st);
+                             float* ws, size_t room, hipStream_t st) {
+    return decode_bf16q<true>(q, kc, vc, k_scale, v_scale, out, lse, B, Hq, Hkv, Lk, seqlens, D, ws, room, st);
 }
 
 // ---------------------------------------------------------------------------------------------

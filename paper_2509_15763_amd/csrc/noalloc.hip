@@ -58,6 +58,6 @@ extern "C" unigist_status unigist_decode_noalloc(const void* q, const void* kcac
     // The split kernel writes the (m, l, acc) slot of every (sequence, head, slice) -- also of an empty slice --
     // before the combine kernel reads it, so nothing of the previous call's contents has to be cleared.
     hipError_t e = launch_decode(q, kcache, vcache, out, lse, B, Hq, Hkv, Lk_max, seqlens, D, dt, (float*)ws,
-                                 (hipStream_t)hip_stream);
+                                 kScratchBytes, (hipStream_t)hip_stream);
     return e == hipSuccess ? UNIGIST_OK : UNIGIST_ELAUNCH;
 }

@@ -1,11 +1,12 @@
-"""Backwards in the least workspace a call takes (gist-phase segments of 16 query chunks): the gradients of the full-size
-workspace up to the grouping of fp32 sums, and nothing written behind the buffer."""
+"""Backwards and decodes in the least workspace a call takes (gist-phase segments of 16 query chunks, slices of 256 keys): the
+results of the full-size workspace up to the grouping of fp32 sums, and nothing written behind the buffer."""
 import pytest
 import torch
 
 import paper_2509_15763_amd as u
 from paper_2509_15763_amd import synth
-from test_workspace import _least_by_rule
+from test_gpu_decode_slices import _exact
+from test_workspace import _decode_least_by_rule, _least_by_rule
 
 pytestmark = pytest.mark.gpu
 
@@ -74,4 +75,28 @@ def test_pack(docs):
         u.unigist_debug_force_plain_alu(0)
     for a, b in zip(plain, want):
         assert (a.float() - b.float()).norm() <= 1e-2 * b.float().norm()  # two bf16 implementations
+    assert bool((behind == 255).all())
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,Lk,D", [(8, 32, 8, 200, 128), (1, 8, 1, 1500, 64), (1, 34, 2, 500, 96)])
+def test_decode(B, Hq, Hkv, Lk, D):
+    gen = torch.Generator().manual_seed(Lk)
+    q = torch.randn(B, Hq, D, generator=gen).bfloat16()
+    k, v = (torch.randn(B, Hkv, Lk, D, generator=gen).bfloat16() for _ in range(2))
+    n = [max(1, Lk - 60 * b) for b in range(B)]
+    sl = torch.tensor(n, dtype=torch.int32).cuda()
+    least = _decode_least_by_rule(B, Hq, Hkv, Lk, D, Hq // Hkv <= 15)
+    assert least < u.unigist_decode_workspace(B, Hq, Hkv, Lk, D, u.UNIGIST_BF16)
+    ws, behind = _guarded(least)
+    o, l = _exact(q, k, v, n)
+    # bf16 P and result: 2^-9 each on values of size at most max |v| <= 5, against float64
+    out, lse = u.decode(q.cuda(), k.cuda(), v.cuda(), sl, workspace=ws)
+    assert (out.cpu().double() - o).abs().max() <= 2e-2 and (lse.cpu().double() - l).abs().max() <= 1e-4
+    ws.fill_(255)
+    one = torch.ones(Hkv).cuda()
+    k8, v8 = (u.quantize_e4m3(t.cuda(), one) for t in (k, v))
+    wide = lambda c: c.cpu().view(torch.float8_e4m3fn).float()
+    out, lse = u.decode_e4m3(q.cuda(), k8, v8, one, one, sl, workspace=ws)
+    o, l = _exact(q, wide(k8), wide(v8), n)
+    assert (out.cpu().double() - o).abs().max() <= 2e-2 and (lse.cpu().double() - l).abs().max() <= 1e-4
     assert bool((behind == 255).all())

@@ -77,3 +77,30 @@ def test_packs(docs):
     # the pack's own need, or four slices for its longest document taken alone
     alone = max(_least_by_rule(1, Hq, Hkv, [L], D, r, W) for L in docs)
     assert got == max(_a(_least_by_rule(1, Hq, Hkv, docs, D, r, W)), 4 * _a(alone)) <= query
+
+
+def _decode_least_by_rule(B, Hq, Hkv, Lk, D, grouped):
+    """Slices of at least 256 keys, in rounds of 256 workgroups."""
+    units = B * (Hkv if grouped else Hq)
+    target = 256 if units <= 64 else 512 if units <= 256 else 1024
+    most = max(1, min(64, max(4, -(-target // units)), -(-Lk // 256)))
+    cost = lambda n: -(-units * n // 256) * 256 / (units * n) * (1 + 0.01 * n) * (1.05 if units * n < target else 1.0)
+    n = min(range(1, most + 1), key=cost)
+    return _a(B * Hq * n * ((64 if D <= 64 else 128) + 2) * 4)
+
+
+@pytest.mark.parametrize("Hq,Hkv,D", [(32, 8, 128), (8, 1, 64), (16, 16, 96), (34, 2, 128)])  # the last: the vector kernel
+@pytest.mark.parametrize("Lk", [1, 129, 200, 500, 1500, 9001])
+def test_decode_takes_what_slices_of_256_keys_need(Hq, Hkv, D, Lk):
+    sizes = []
+    for B in range(1, 40):
+        query = u.unigist_decode_workspace(B, Hq, Hkv, Lk, D, u.UNIGIST_BF16)
+        call = lambda n: u.unigist_decode(*([FAKE] * 4), None, B, Hq, Hkv, Lk, None, D, u.UNIGIST_BF16, FAKE, n)
+        call8 = lambda n: u.unigist_decode_e4m3(*([FAKE] * 6), None, B, Hq, Hkv, Lk, None, D, FAKE, n)
+        least = _decode_least_by_rule(B, Hq, Hkv, Lk, D, Hq // Hkv <= 15)
+        assert _least_accepted(call, query) == least <= query
+        assert call8(least) != EINVAL and call8(least - 1) == EINVAL
+        sizes.append((query, least))
+    if (Hq, Hkv, Lk) == (32, 8, 200):
+        # one slice of 256 keys per sequence from 9 sequences on: a buffer for any of those batches serves 8
+        assert all(sizes[7][1] <= q < sizes[7][0] for q, _ in sizes[8:12])
