@@ -275,8 +275,8 @@ size_t unigist_decode_workspace(int B, int Hq, int Hkv, int Lk_max, int D, unigi
  * A problem for which unigist_decode_workspace(...) exceeds that size is refused with UNIGIST_ESCRATCH and
  * nothing is launched (the benchmark's serving shape, 64 sequences x 32 heads x 17 408 keys, needs 2.1 MB).
  * All calls on one GPU share the array: calls that may overlap there (different streams, different host threads)
- * race on it and must be ordered by the caller; calls on one stream are ordered by the stream.  Nothing of an
- * earlier call's contents is read: every slot is written before it is used.
+ * race on it and must be ordered by the caller; calls on one stream are ordered by the stream.  No
+ * earlier call's contents enter a result: every slot is written before it is used.
  */
 #define UNIGIST_DECODE_NOALLOC_SCRATCH_BYTES (8u << 20)
 unigist_status unigist_decode_noalloc(const void* q, const void* kcache, const void* vcache, void* out,

@@ -55,8 +55,9 @@ extern "C" unigist_status unigist_decode_noalloc(const void* q, const void* kcac
     if (need > kScratchBytes) return UNIGIST_ESCRATCH;
     void* ws = scratch_of_current_device();
     if (!ws) return UNIGIST_ELAUNCH;
-    // The split kernel writes the (m, l, acc) slot of every (sequence, head, slice) -- also of an empty slice --
-    // before the combine kernel reads it, so nothing of the previous call's contents has to be cleared.
+    // The split kernel writes (m, l) of every (sequence, head, slice) and the accumulator of every slice with keys; the
+    // combine kernel may load the accumulator of one without, but leaves it out of the sum.  So nothing of the previous
+    // call's contents has to be cleared.
     hipError_t e = launch_decode(q, kcache, vcache, out, lse, B, Hq, Hkv, Lk_max, seqlens, D, dt, (float*)ws,
                                  kScratchBytes, (hipStream_t)hip_stream);
     return e == hipSuccess ? UNIGIST_OK : UNIGIST_ELAUNCH;

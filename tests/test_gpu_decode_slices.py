@@ -47,3 +47,36 @@ def test_lengths(G, D, Lk):
         out, lse = u.decode_e4m3(q.cuda(), k8, v8, one, one, sl)
         o, l = _exact(q, wide(k8), wide(v8), n)
         assert (out.cpu().double() - o).abs().max() <= 2e-2 and (lse.cpu().double() - l).abs().max() <= 1e-4
+
+
+@pytest.mark.parametrize("dt", [torch.bfloat16, torch.float32, "e4m3"])
+@pytest.mark.parametrize("G", [4, 17])  # 17: the vector kernel
+def test_infinities_and_nan_in_a_slice_without_weight(G, dt):
+    # one key holds all the weight, the others' underflows to zero (scores 256 and -1024), and 0 * inf is NaN: what a row
+    # holds reaches the result whether it shares a slice with that key (10) or not (700, 990)
+    Lk, D, n = 1000, 64, 995
+    q = torch.full((1, G, D), 4.0)
+    k = torch.full((1, 1, Lk, D), -32.0)
+    k[:, :, 0] = 8.0
+    v = torch.randn(1, 1, Lk, D, generator=torch.Generator().manual_seed(G)).to(torch.float8_e4m3fn).float()
+    nan = float("nan")
+    bad = {(10, 1): nan, (700, 5): nan, (990, 7): nan}
+    if dt != "e4m3":  # which has no infinities
+        bad |= {(10, 2): float("inf"), (700, 3): float("inf"), (990, 60): -float("inf")}
+    for (row, col), x in bad.items():
+        v[:, :, row, col] = x
+    v[:, :, n:] = nan  # behind the sequence: never read into the result
+    sl = torch.tensor([n], dtype=torch.int32).cuda()
+    if dt == "e4m3":
+        one = torch.ones(1).cuda()
+        codes = [t.to(torch.float8_e4m3fn).view(torch.uint8).cuda() for t in (k, v)]
+        out, lse = u.decode_e4m3(q.bfloat16().cuda(), *codes, one, one, sl)
+    else:
+        out, lse = u.decode(*(t.to(dt).cuda() for t in (q, k, v)), sl)
+    o, l = _exact(q, k, v, [n])
+    assert torch.equal(o.isnan()[0].any(0).nonzero()[:, 0], torch.tensor(sorted(c for _, c in bad)))
+    assert torch.equal(out.cpu().isnan(), o.isnan())
+    ok = ~o.isnan()
+    # the result is the first row, rounded to bf16 at most
+    assert (out.cpu().double() - o)[ok].abs().max() <= 2.0 ** -8 * o[ok].abs().max()
+    assert (lse.cpu().double() - l).abs().max() <= 1e-3  # fp32 around 256
