@@ -100,7 +100,7 @@ unigist_status unigist_attn_fwd_ex(const void* q, const void* k, const void* v, 
  * q, k, v, out, lse: the forward's inputs and outputs (in).  dout: in.
  * dq [B,Hq,L,D], dk, dv [B,Hkv,L,D] (dt): out; dk and dv are summed over the
  * Hq/Hkv query heads sharing a kv head.  No atomics are used, so results are
- * bitwise reproducible run to run.
+ * bitwise reproducible run to run.  dq may take q's or dout's place in memory.
  * workspace: device scratch, 256-byte aligned, contents undefined on entry and exit.
  * unigist_attn_bwd_workspace(...) bytes give the fastest plan.  Short sequences spread their gist phase over more
  * partial sums than they need (32/8 heads, D = 128: 64 MB for 4096 tokens at W = 512 instead of 24, 64 for 2 x 2047 at

@@ -324,6 +324,16 @@ __device__ __forceinline__ void dq_part(DqSmem<D>& sm, int BLOCK0, const bf16_t*
 // The line lies at six rounds of dQ workgroups: 3072 at two workgroups per CU (D = 128), 4608 at three (D = 64).
 template <int D> bool run_jointly(long n_dq) { return n_dq <= 256 * 6 * (D <= 64 ? 3 : 2); }
 
+// A dq that shares memory with q or dout, which its own workgroups have read before they write, is written too early there
+// for the other phases: such calls keep the launches apart.
+bool dq_on_its_inputs(const bf16_t* q, const bf16_t* dout, const bf16_t* dq, const AttnShape& s) {
+    const long long rows = s.q_rs ? s.q_rs : s.D, heads = s.q_rs ? s.q_hs : (long long)s.qhs * s.D,
+                    batches = s.q_rs ? s.q_bs : heads * s.Hq;
+    const uintptr_t bytes = 2 * (uintptr_t)((s.B - 1) * batches + (s.Hq - 1) * heads + (s.L - 1) * rows + s.D);
+    auto meets = [&](const bf16_t* x) { return (uintptr_t)x < (uintptr_t)dq + bytes && (uintptr_t)dq < (uintptr_t)x + bytes; };
+    return meets(q) || meets(dout);
+}
+
 template <int D, bool GEN, bool QSTR>
 __global__ __launch_bounds__(NT, 2) void bwd_joint_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                          const bf16_t* __restrict__ v, const float* __restrict__ lse2,
@@ -367,7 +377,7 @@ hipError_t bwd_launch(const bf16_t* q, const bf16_t* k, const bf16_t* v, const b
     const long nblk = (long)nq * s.Hkv * s.B, n_gist = (long)pl.slot0[pl.nseg] * s.Hkv * s.B,
                n_win = (long)((s.L + BNK - 1) / BNK) * s.Hkv * s.B;
     if (nblk > 0x7fffffffL) return hipErrorInvalidValue;
-    if (stages == UNIGIST_BWD_ALL && run_jointly<D>(nblk)) {
+    if (stages == UNIGIST_BWD_ALL && run_jointly<D>(nblk) && !dq_on_its_inputs(q, dout, dq, s)) {
         auto go = [&](auto kern) {
             kern<<<dim3((unsigned)(n_gist + n_win + nblk)), NT, 0, st>>>(q, k, v, lse2, dout, delta, dq, dk, dv, part, comp, s,
                                                                        pl, (int)n_gist, (int)n_win, nq);

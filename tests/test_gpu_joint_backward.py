@@ -54,3 +54,26 @@ def test_whole_against_stages(B, Hq, Hkv, L, D, r, W, S, mode, strided):
         o, l, *grads = oracle_fwd_bwd(q, k, v, do, r, W, sinks=S, units=mode == 1)
         for a, b in zip(got, grads):
             assert rel_l2(to_np(a), b) <= TOL_GRAD_BF16
+
+
+@pytest.mark.parametrize("strided", [False, True])
+@pytest.mark.parametrize("onto", ["q", "dout"])
+@pytest.mark.parametrize("B,Hq,Hkv,L,D,r,W", [(2, 32, 8, 2047, 128, 4, 128), (1, 7, 1, 1283, 64, 2, 33)])
+def test_dq_in_place_of_its_inputs(B, Hq, Hkv, L, D, r, W, onto, strided):
+    # every row of q and dout is read by the two dK/dV phases as well, so dq has to be written behind them
+    lay = (lambda t: t.transpose(1, 2).contiguous().transpose(1, 2)) if strided else (lambda t: t.contiguous())
+    q, k, v, do = (t.cuda() for t in synth.attn_inputs(B, Hq, Hkv, L, D, seed=L))
+    q, do = lay(q), lay(do)
+    out, lse = u.attn_fwd(q, k, v, r, W)
+    want = u.attn_bwd(q, k, v, out, lse, do, r, W)
+    ws = torch.empty(u.unigist_attn_bwd_workspace(B, Hq, Hkv, L, D, r, W, u.UNIGIST_BF16), device="cuda", dtype=torch.uint8)
+    dk, dv = torch.empty_like(k), torch.empty_like(v)
+    dq = q if onto == "q" else do
+    st = q.stride() if strided else (Hq * L * D, L * D, D)
+    assert u.unigist_attn_bwd_strided(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(), do.data_ptr(),
+                                      dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), B, Hq, Hkv, L, D, r, W, 0, 0, *st[:3],
+                                      u.UNIGIST_BF16, ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream) == 0
+    assert torch.equal(dq, want[0])
+    # the same sums, put together in separate launches (as in test_whole_against_stages)
+    for a, b in zip((dk, dv), want[1:]):
+        assert (a.float() - b.float()).norm() <= 3e-4 * b.float().norm()
