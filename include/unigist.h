@@ -519,23 +519,36 @@ void unigist_blockmap_free(unigist_blockmap* m);
 
 /*
  * The tile walks exactly as the kernels take them (Sec. 4.2: the visible blocks follow from r and W in closed form).
- * unigist_blockmap_build above and the three calls below evaluate, on the HOST, the very functions the kernels
+ * unigist_blockmap_build above and the calls below evaluate, on the HOST, the very functions the kernels
  * call for every decision about which tiles to visit, which to skip and which need the in-tile mask, so that the
  * walks can be checked against the mask rule pair by pair without a GPU.  Step kinds: 0 = not visited (no pair of
  * it is visible), 1 = visited without mask (every pair of it is visible), 2 = visited with the in-tile mask.
  *
- * Row side (forward: 128 query rows per workgroup, 32 keys per step; dQ: 128 rows, 64 keys; a wave owns 32 rows).
- * Query tile `tile` first walks n_gist_steps steps over the first nfar entries of the compact list of sinks and
+ * Row side (forward: 32 keys per step; dQ: 64).  A wave owns 32 query rows of one query head, a workgroup has four
+ * waves.  With G = Hq / Hkv query heads per kv head, the (row block, head) pairs of a kv head are numbered heads first,
+ * and group `group` of its n_groups workgroups takes the four pairs from 4 group on: with G = 4 the same 32 rows of four
+ * heads, with G = 1 four row blocks (128 rows) of one.  Wave w has the rows row0[w] .. row0[w] + 31 (below L) of head
+ * head[w] of the group; head[w] = -1: the last workgroup has no work for it (it shadows the last pair).  i0, i1: first
+ * and last row of the workgroup.
+ * All four waves first walk n_gist_steps steps over the first nfar entries of the compact list of sinks and
  * gists (entry c < sinks is position c, gist g is position sinks + (r+1) g + r; all of them lie left of wstart and
  * are visible to every row; only the last step can hold fewer than Bn entries, hence its mask), then
  * n_window_steps steps over the positions wstart, wstart + Bn, ... .  kind (optional, kind_capacity entries
- * available): [Bm / 32 waves][n_gist_steps + n_window_steps].
+ * available): [4 waves][n_gist_steps + n_window_steps].  unigist_plan_row_tile is the walk at G = 1, where a workgroup
+ * is a tile of Bm = 128 rows.  G < 1 or a group outside 0 .. n_groups - 1: UNIGIST_EINVAL.
  */
 typedef enum { UNIGIST_WALK_FWD = 0, UNIGIST_WALK_DQ = 1 } unigist_walk_kernel;
 typedef struct unigist_row_tile_plan {
     int Bm, Bn, rows_per_wave;
     int wstart, nfar, n_gist_steps, n_window_steps;
 } unigist_row_tile_plan;
+typedef struct unigist_row_group_plan {
+    int n_groups, Bn, i0, i1;
+    int wstart, nfar, n_gist_steps, n_window_steps;
+    int head[4], row0[4];
+} unigist_row_group_plan;
+unigist_status unigist_plan_row_group(int L, int r, int W, int sinks, int window_mode, int G, int kernel, int group,
+                                      unigist_row_group_plan* out, int kind_capacity, signed char* kind);
 unigist_status unigist_plan_row_tile(int L, int r, int W, int sinks, int window_mode, int kernel, int tile,
                                      unigist_row_tile_plan* out, int kind_capacity, signed char* kind);
 /*
@@ -578,7 +591,9 @@ unigist_status unigist_plan_key_tile(int B, int Hq, int Hkv, int L, int D, int r
 unigist_status unigist_plan_gist_unit(int B, int Hq, int Hkv, int L, int D, int r, int W, int sinks, int window_mode,
                                       int unit, int* seg, int* tile);
 
-/* Tile sizes the forward / backward kernels use for head dim D (for the live-tile report). */
+/* Tile for a live-tile report: bf16, the 128 rows x 32 keys that a forward workgroup steps through where every query
+ * head has its own kv head; fp32, the rows of a workgroup of the plain-ALU kernels.  With G query heads per kv head a
+ * bf16 workgroup spans 32 rows (G a multiple of four) and up to 64 otherwise (unigist_plan_row_group). */
 void unigist_tile_sizes(int D, unigist_dtype dt, int* Bm, int* Bn);
 
 /*

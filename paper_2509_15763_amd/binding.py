@@ -35,7 +35,7 @@ EXPORTS = [
     "unigist_cache_ring_rows", "unigist_cache_to_ring", "unigist_cache_from_ring", "unigist_cache_ring_append",
     "unigist_cache_ring_step",
     "unigist_decode_noalloc", "unigist_decode_noalloc_scratch_bytes", "unigist_debug_force_plain_alu",
-    "unigist_window_start", "unigist_plan_row_tile", "unigist_bwd_plan_build", "unigist_plan_key_tile", "unigist_plan_gist_unit",
+    "unigist_window_start", "unigist_plan_row_tile", "unigist_plan_row_group", "unigist_bwd_plan_build", "unigist_plan_key_tile", "unigist_plan_gist_unit",
     "unigist_probe_read_rate",
 ]
 
@@ -54,6 +54,11 @@ class _BlockMap(C.Structure):
 
 class _RowTilePlan(C.Structure):
     _fields_ = [(n, C.c_int) for n in ("Bm", "Bn", "rows_per_wave", "wstart", "nfar", "n_gist_steps", "n_window_steps")]
+
+
+class _RowGroupPlan(C.Structure):
+    _fields_ = [(n, C.c_int) for n in ("n_groups", "Bn", "i0", "i1", "wstart", "nfar", "n_gist_steps", "n_window_steps")] + \
+               [("head", C.c_int * 4), ("row0", C.c_int * 4)]
 
 
 class _BwdPlan(C.Structure):
@@ -115,6 +120,8 @@ def load():
     lib.unigist_decode_noalloc.argtypes = [vp, vp, vp, vp, fp, ip, ip, ip, ip, vp, ip, ip, vp]
     lib.unigist_plan_row_tile.restype = ip
     lib.unigist_plan_row_tile.argtypes = [ip] * 7 + [C.POINTER(_RowTilePlan), ip, vp]
+    lib.unigist_plan_row_group.restype = ip
+    lib.unigist_plan_row_group.argtypes = [ip] * 8 + [C.POINTER(_RowGroupPlan), ip, vp]
     lib.unigist_bwd_plan_build.restype = ip
     lib.unigist_bwd_plan_build.argtypes = [ip] * 9 + [C.POINTER(_BwdPlan)]
     lib.unigist_plan_gist_unit.restype = ip
@@ -323,8 +330,8 @@ UNIGIST_WALK_FWD, UNIGIST_WALK_DQ = 0, 1
 
 
 def unigist_plan_row_tile(L, r, W, sinks, window_mode, kernel, tile) -> dict:
-    """The forward (kernel = UNIGIST_WALK_FWD) or dQ walk of query tile `tile`, as a dict; "kind" is an int8 numpy
-    array [waves, steps] (0 skipped, 1 no mask, 2 masked)."""
+    """The forward (kernel = UNIGIST_WALK_FWD) or dQ walk of query tile `tile` where every query head has its own kv head,
+    as a dict; "kind" is an int8 numpy array [waves, steps] (0 skipped, 1 no mask, 2 masked)."""
     import numpy as np
     p = _RowTilePlan()
     _check(load().unigist_plan_row_tile(L, r, W, sinks, window_mode, kernel, tile, C.byref(p), 0, None),
@@ -336,6 +343,19 @@ def unigist_plan_row_tile(L, r, W, sinks, window_mode, kernel, tile) -> dict:
     d = {n: getattr(p, n) for n, _ in _RowTilePlan._fields_}
     d["kind"] = kind
     return d
+
+
+def unigist_plan_row_group(L, r, W, sinks, window_mode, G, kernel, group) -> dict:
+    """The forward or dQ walk of workgroup `group` of a kv head with G query heads, as a dict; "kind" is an int8 numpy array
+    [4, steps], "head" the waves' query heads inside the group (-1: no work), "row0" their first rows."""
+    import numpy as np
+    p = _RowGroupPlan()
+    args = (L, r, W, sinks, window_mode, G, kernel, group, C.byref(p))
+    _check(load().unigist_plan_row_group(*args, 0, None), "unigist_plan_row_group")
+    kind = np.zeros((4, p.n_gist_steps + p.n_window_steps), dtype=np.int8)
+    _check(load().unigist_plan_row_group(*args, kind.size, kind.ctypes.data), "unigist_plan_row_group")
+    d = {n: getattr(p, n) for n, _ in _RowGroupPlan._fields_ if n not in ("head", "row0")}
+    return {**d, "head": list(p.head), "row0": list(p.row0), "kind": kind}
 
 
 def unigist_bwd_plan_build(B, Hq, Hkv, L, D, r, W, sinks=0, window_mode=UNIGIST_WINDOW_SLIDING) -> dict:

@@ -138,15 +138,13 @@ __global__ __launch_bounds__(NT, 3) void fwd_mfma_kernel(const bf16_t* __restric
     // by the positions s0 .. L-1 (training: everything from position 0, no compact rows).
     const int L = s.L, rp1 = s.rp1, Dt = s.D;
     const int qpos0 = s.qpos0, s0 = s.s0, ngb = s.ngb;
-    const int nu = row_units(s.Lq, G).n;
-    const int u0 = wt * kUnitsPerWg;
     const int wv = __builtin_amdgcn_readfirstlane(w);
-    const bool live = u0 + wv < nu;          // the last workgroup may have waves without a unit: they only stage
-    const int u = live ? u0 + wv : nu - 1;
-    const int hq = hk * G + u % G;
-    const int i0 = qpos0 + u0 / G * kWaveRows;                                // the workgroup's first and last row
-    const int i1 = min(L, qpos0 + (min(u0 + kUnitsPerWg, nu) - 1) / G * kWaveRows + kWaveRows) - 1;
-    const int wrow0 = qpos0 + u / G * kWaveRows;  // first row of the wave
+    const RowGroup grp = row_group(s.Lq, G, wt);
+    const RowWave unit = row_wave(s.Lq, G, wt, wv);
+    const bool live = unit.live;
+    const int hq = hk * G + unit.head;
+    const int i0 = qpos0 + grp.i0, i1 = qpos0 + grp.i1;  // the workgroup's first and last row
+    const int wrow0 = qpos0 + unit.row0;                 // first row of the wave
     int qrow[2], qrow_ld[2];                 // this lane's two query rows (16-row blocks qb = 0, 1)
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {

@@ -63,7 +63,7 @@ extern "C" unigist_status unigist_blockmap_build_ex(int L, int r, int W, int sin
     for (int t = 0; t < m->n_qtiles; ++t) {
         const int i0 = (int)((int64_t)t * Bm);
         const int i1 = (int)(imin(L, (int64_t)i0 + Bm) - 1);
-        const RowWalk w = row_walk(s, i0, i1, Bn);  // the walk of the tile's rows, as the forward and dQ kernels take it
+        const RowWalk w = row_walk(s, i0, i1, Bn);  // as the forward and dQ kernels walk a workgroup with these rows
         m->win_first[t] = w.wstart / Bn;
         m->win_last[t] = i1 / Bn;
         m->n_far_gists[t] = w.nfar;
@@ -120,32 +120,62 @@ extern "C" void unigist_blockmap_free(unigist_blockmap* m) {
 }
 
 // ---------------------------------------------------------------- the kernels' walks, step by step
+// kinds of the steps of one wave, whose first row is row0
+static void wave_kinds(const AttnShape& s, const RowWalk& w, int Bn, int row0, signed char* kind) {
+    const int lo_last = win_lo(s, row0 + kWaveRows - 1);  // as the kernels compute it (rows past L included)
+    for (int it = 0; it < w.steps(); ++it) kind[it] = (signed char)row_step_kind(w, it, Bn, row0, row0 + kWaveRows - 1, lo_last);
+}
+
+extern "C" unigist_status unigist_plan_row_group(int L, int r, int W, int sinks, int window_mode, int G, int kernel, int group,
+                                                 unigist_row_group_plan* out, int kind_capacity, signed char* kind) {
+    if (!out || !shape_ok(L, r, W, sinks, window_mode) || G < 1) return UNIGIST_EINVAL;
+    if (kernel != UNIGIST_WALK_FWD && kernel != UNIGIST_WALK_DQ) return UNIGIST_EINVAL;
+    if (((int64_t)L + kWaveRows - 1) / kWaveRows * G > 0x7fffffff - kUnitsPerWg) return UNIGIST_EUNSUPPORTED;
+    const int Bn = kernel == UNIGIST_WALK_FWD ? kFwdBn : kDqBn;
+    const RowUnits units = row_units(L, G);
+    if (group < 0 || group >= units.per) return UNIGIST_EINVAL;
+    const AttnShape s = make_shape(1, G, 1, L, 64, r, W, sinks, window_mode);
+    const RowGroup g = row_group(L, G, group);
+    const RowWalk w = row_walk(s, g.i0, g.i1, Bn);
+    out->n_groups = units.per;
+    out->Bn = Bn;
+    out->i0 = g.i0;
+    out->i1 = g.i1;
+    out->wstart = w.wstart;
+    out->nfar = w.nfar;
+    out->n_gist_steps = w.ngt;
+    out->n_window_steps = w.nwin;
+    for (int wv = 0; wv < kUnitsPerWg; ++wv) {
+        const RowWave u = row_wave(L, G, group, wv);
+        out->head[wv] = u.live ? u.head : -1;
+        out->row0[wv] = u.row0;
+    }
+    if (!kind) return UNIGIST_OK;  // the counts only
+    if (kind_capacity < kUnitsPerWg * w.steps()) return UNIGIST_EINVAL;
+    for (int wv = 0; wv < kUnitsPerWg; ++wv) wave_kinds(s, w, Bn, out->row0[wv], kind + wv * w.steps());
+    return UNIGIST_OK;
+}
+
+// four row blocks of one head: the workgroups of a group of one
 extern "C" unigist_status unigist_plan_row_tile(int L, int r, int W, int sinks, int window_mode, int kernel, int tile,
                                                 unigist_row_tile_plan* out, int kind_capacity, signed char* kind) {
     if (!out || !shape_ok(L, r, W, sinks, window_mode)) return UNIGIST_EINVAL;
     if (kernel != UNIGIST_WALK_FWD && kernel != UNIGIST_WALK_DQ) return UNIGIST_EINVAL;
-    const int Bm = kernel == UNIGIST_WALK_FWD ? kFwdBm : kDqBm, Bn = kernel == UNIGIST_WALK_FWD ? kFwdBn : kDqBn;
-    const int nq = (L + Bm - 1) / Bm;
-    if (tile < 0 || tile >= nq) return UNIGIST_EINVAL;
+    if (tile < 0 || tile >= row_units(L, 1).per) return UNIGIST_EINVAL;
     const AttnShape s = make_shape(1, 1, 1, L, 64, r, W, sinks, window_mode);
-    const int i0 = tile * Bm, i1 = (int)imin(L, (int64_t)i0 + Bm) - 1;
-    const RowWalk w = row_walk(s, i0, i1, Bn);
-    out->Bm = Bm;
+    const int Bn = kernel == UNIGIST_WALK_FWD ? kFwdBn : kDqBn;
+    const RowGroup g = row_group(L, 1, tile);
+    const RowWalk w = row_walk(s, g.i0, g.i1, Bn);
+    out->Bm = kUnitsPerWg * kWaveRows;
     out->Bn = Bn;
     out->rows_per_wave = kWaveRows;
     out->wstart = w.wstart;
     out->nfar = w.nfar;
     out->n_gist_steps = w.ngt;
     out->n_window_steps = w.nwin;
-    const int nsteps = w.ngt + w.nwin, nwaves = Bm / kWaveRows;
     if (!kind) return UNIGIST_OK;  // the counts only
-    if (kind_capacity < nwaves * nsteps) return UNIGIST_EINVAL;
-    for (int wv = 0; wv < nwaves; ++wv) {
-        const int wrow0 = i0 + kWaveRows * wv;
-        const int lo_wlast = win_lo(s, wrow0 + kWaveRows - 1);  // as the kernels compute it (rows past L included)
-        for (int it = 0; it < nsteps; ++it)
-            kind[wv * nsteps + it] = (signed char)row_step_kind(w, it, Bn, wrow0, wrow0 + kWaveRows - 1, lo_wlast);
-    }
+    if (kind_capacity < kUnitsPerWg * w.steps()) return UNIGIST_EINVAL;
+    for (int wv = 0; wv < kUnitsPerWg; ++wv) wave_kinds(s, w, Bn, g.i0 + kWaveRows * wv, kind + wv * w.steps());
     return UNIGIST_OK;
 }
 

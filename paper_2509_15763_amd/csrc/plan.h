@@ -5,7 +5,7 @@
 // same functions (unigist_plan_*, unigist_blockmap_build) so that the walk can be checked pair by pair on the CPU.
 //
 // Two walks cover every visible pair exactly once each:
-//   row side (forward, dQ): a tile of query rows walks the compact list of sinks and gists left of its window
+//   row side (forward, dQ): the query rows of a workgroup walk the compact list of sinks and gists left of its window
 //     phase ("gist phase", all of them visible to every row), then the contiguous key steps from the window's first
 //     step to the diagonal ("window phase");
 //   key side (dK/dV): a query chunk c of MQ rows reaches the compact entries left of far(c) in the gist phase (one
@@ -21,9 +21,8 @@ namespace unigist {
 enum StepKind { STEP_SKIP = 0, STEP_FULL = 1, STEP_MASKED = 2 };  // not visited / every pair visible / in-tile mask
 
 // ------------------------------------------------------------------------------------------ row side
-constexpr int kFwdBm = 128, kFwdBn = 32;  // forward: query rows per workgroup, keys per step
-constexpr int kDqBm = 128, kDqBn = 64;    // dQ
-constexpr int kWaveRows = 32;             // query rows per wave in both
+constexpr int kFwdBn = 32, kDqBn = 64;  // keys per step: forward, dQ
+constexpr int kWaveRows = 32;           // query rows per wave in both
 
 // A row-side workgroup is four waves, and a wave takes one unit: the kWaveRows rows of one row block of one query
 // head.  The units of a kv head are numbered heads first (unit = row block * G + head of the group), and a workgroup
@@ -41,6 +40,33 @@ __host__ __device__ inline RowUnits row_units(int rows, int G) {
     u.n = (rows + kWaveRows - 1) / kWaveRows * G;
     u.per = (u.n + kUnitsPerWg - 1) / kUnitsPerWg;
     return u;
+}
+// Workgroup wg (0 .. per - 1) of a kv head with `rows` query rows: its rows from the first to the last.
+struct RowGroup {
+    int i0, i1;
+};
+__host__ __device__ inline RowGroup row_group(int rows, int G, int wg) {
+    const int nu = row_units(rows, G).n, u0 = wg * kUnitsPerWg, u1 = u0 + kUnitsPerWg < nu ? u0 + kUnitsPerWg : nu;
+    RowGroup g;
+    g.i0 = u0 / G * kWaveRows;
+    g.i1 = (u1 - 1) / G * kWaveRows + kWaveRows - 1;
+    if (g.i1 > rows - 1) g.i1 = rows - 1;
+    return g;
+}
+// Its wave: a query head of the group and the first of its kWaveRows rows (of which those below `rows` exist).  The last
+// workgroup may have waves without a unit (live = false): they shadow the last one and only stage.
+struct RowWave {
+    int head, row0;
+    bool live;
+};
+__host__ __device__ inline RowWave row_wave(int rows, int G, int wg, int wave) {
+    const int nu = row_units(rows, G).n, u = wg * kUnitsPerWg + wave;
+    RowWave w;
+    w.live = u < nu;
+    const int v = w.live ? u : nu - 1;
+    w.head = v % G;
+    w.row0 = v / G * kWaveRows;
+    return w;
 }
 
 struct RowWalk {

@@ -38,6 +38,20 @@ static void walk_plans(const Shape& s) {
         CHECK(unigist_plan_row_tile(s.L, s.r, s.W, s.sinks, s.mode, kernel, nq, &p, 0, nullptr) == UNIGIST_EINVAL);
         CHECK(unigist_plan_row_tile(s.L, s.r, s.W, s.sinks, s.mode, kernel, -1, &p, 0, nullptr) == UNIGIST_EINVAL);
     }
+    for (int G : {s.Hq / s.Hkv, 1, 3, 4}) {
+        unigist_row_group_plan p;
+        int n_groups = 1;
+        for (int g = 0; g < n_groups; ++g) {
+            CHECK(unigist_plan_row_group(s.L, s.r, s.W, s.sinks, s.mode, G, g & 1, g, &p, 0, nullptr) == UNIGIST_OK);
+            n_groups = p.n_groups;
+            const int n = 4 * (p.n_gist_steps + p.n_window_steps);
+            std::vector<signed char> kind(n);
+            CHECK(unigist_plan_row_group(s.L, s.r, s.W, s.sinks, s.mode, G, g & 1, g, &p, n, kind.data()) == UNIGIST_OK);
+            CHECK(unigist_plan_row_group(s.L, s.r, s.W, s.sinks, s.mode, G, g & 1, g, &p, n - 1, kind.data()) == UNIGIST_EINVAL);
+        }
+        CHECK(unigist_plan_row_group(s.L, s.r, s.W, s.sinks, s.mode, G, 0, n_groups, &p, 0, nullptr) == UNIGIST_EINVAL);
+        CHECK(unigist_plan_row_group(s.L, s.r, s.W, s.sinks, s.mode, G, 0, -1, &p, 0, nullptr) == UNIGIST_EINVAL);
+    }
     unigist_bwd_plan bp;
     CHECK(unigist_bwd_plan_build(s.B, s.Hq, s.Hkv, s.L, s.D, s.r, s.W, s.sinks, s.mode, &bp) == UNIGIST_OK);
     CHECK(bp.workspace_bytes == unigist_attn_bwd_workspace_ex(s.B, s.Hq, s.Hkv, s.L, s.D, s.r, s.W, s.sinks, s.mode, UNIGIST_BF16));
