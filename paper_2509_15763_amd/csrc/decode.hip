@@ -218,14 +218,55 @@ __global__ __launch_bounds__(kThreads) void decode_split_kernel(const TQ* __rest
     }
 }
 
-// Merges the slices of one (sequence, query head).  The kernel is nothing but latency, and most of it the round trip to
-// partials that other XCDs have just written: every wave takes each kWaves-th slice and has all its loads in flight at
-// once (the accumulators of up to kBatch slices and, one slice per lane, the references of all), where a loop that
-// first looks for the maximum and then sums pays two trips.  A slice without keys has m = -inf and leaves its accumulator
-// unwritten: what is loaded of it may be anything, NaN included, and must not enter the sum.  A slice with keys enters it
-// also with a weight that has underflowed to zero, so that its infinities and NaN reach the result as they would inside
-// one slice.
-// At most 64 slices.  Slice kernel + this, us: 8000 keys x 8 kv heads 27.6 -> 14.8, 20000 keys x 1 kv head 42.0 -> 16.6.
+// Merge of the slices of one (sequence, query head).  Both kernels are nothing but latency, and most of it the round trip to
+// partials that other XCDs have just written, so all loads of a wave are in flight at once; a loop that first looks for
+// the maximum and then sums pays two trips.  A slice without keys has m = -inf and leaves its accumulator unwritten: what
+// is loaded of it may be anything, NaN included, and must not enter the sum.  A slice with keys enters it also with a
+// weight that has underflowed to zero, so that its infinities and NaN reach the result as they would inside one slice.  A
+// sequence of zero keys (outside the contract) gets the empty sum, not NaN; columns from Dt on are not in the tensors.
+
+// Up to kFewSlices slices: a wave has them all in flight by itself.  Three more waves and their merge through LDS cost a batch
+// that the slice kernel fills by itself 2.4 us (slice kernel + combine, us, four waves / one: 128 sequences of up to 500
+// E4M3 rows at D = 64 17.7 / 15.1, 256 of 300 bf16 rows at D = 128 69.5 / 64.6, 32 of 1100 33.1 / 32.4).  With more
+// slices the second trip costs more than that (five slices 14.9 / 15.6, 24 11.8 / 14.3).
+constexpr int kFewSlices = 4;
+template <typename T, int D>
+__global__ __launch_bounds__(64) void decode_combine_few_kernel(const float* __restrict__ ws, T* __restrict__ out,
+                                                               float* __restrict__ lse, int nsplit, int Dt) {
+    constexpr int C = D / 64;  // columns per lane
+    const int bh = blockIdx.x, lane = threadIdx.x;
+    const float* p = ws + (size_t)bh * nsplit * (D + 2);
+    f32x2 ml[kFewSlices];
+    float x[kFewSlices][C];
+#pragma unroll
+    for (int s = 0; s < kFewSlices; ++s) {
+        const float* ps = p + (size_t)min(s, nsplit - 1) * (D + 2);
+        ml[s] = *(const f32x2*)ps;
+#pragma unroll
+        for (int c = 0; c < C; ++c) x[s][c] = ps[2 + 64 * c + lane];
+    }
+    float mm = -INFINITY, ll = 0.f, a[C];
+#pragma unroll
+    for (int s = 0; s < kFewSlices; ++s) mm = fmaxf(mm, ml[s][0]);  // the last one again where there are fewer
+#pragma unroll
+    for (int c = 0; c < C; ++c) a[c] = 0.f;
+#pragma unroll
+    for (int s = 0; s < kFewSlices; ++s)
+        if (s < nsplit && ml[s][0] != -INFINITY) {
+            const float w = __expf(ml[s][0] - mm);
+            ll += w * ml[s][1];
+#pragma unroll
+            for (int c = 0; c < C; ++c) a[c] += w * x[s][c];
+        }
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+        if (64 * c + lane < Dt) Elem<T>::store(out + (size_t)bh * Dt + 64 * c + lane, mm == -INFINITY ? 0.f : a[c] / ll);
+    if (lse && lane == 0) lse[bh] = mm == -INFINITY ? -INFINITY : mm + __logf(ll);
+}
+
+// More slices, up to 64: four waves, each taking every fourth slice (the accumulators of up to kBatch slices and, one slice
+// per lane, the references of all are in flight).
+// Slice kernel + this, us: 8000 keys x 8 kv heads 27.6 -> 14.8, 20000 keys x 1 kv head 42.0 -> 16.6.
 template <typename T, int D>
 __global__ __launch_bounds__(256) void decode_combine_kernel(const float* __restrict__ ws, T* __restrict__ out,
                                                             float* __restrict__ lse, int nsplit, int Dt) {
@@ -271,11 +312,18 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const float* __rest
     for (int c = 0; c < C; ++c) part[w][64 * c + lane] = a[c];
     __syncthreads();
     const int d = threadIdx.x;
-    if (d >= Dt) return;  // columns the tensors do not have
-    float r = 0.f;  // a sequence of zero keys (outside the contract): the empty sum, not NaN
+    if (d >= Dt) return;
+    float r = 0.f;
     if (mm != -INFINITY) r = ((part[0][d] + part[1][d]) + (part[2][d] + part[3][d])) / ll;
     Elem<T>::store(out + (size_t)bh * Dt + d, r);
     if (lse && d == 0) lse[bh] = mm == -INFINITY ? -INFINITY : mm + __logf(ll);
+}
+
+template <typename T, int D>
+hipError_t launch_combine(const float* ws, T* out, float* lse, int BH, int nsplit, int Dt, hipStream_t st) {
+    if (nsplit <= kFewSlices) decode_combine_few_kernel<T, D><<<BH, 64, 0, st>>>(ws, out, lse, nsplit, Dt);
+    else decode_combine_kernel<T, D><<<BH, 256, 0, st>>>(ws, out, lse, nsplit, Dt);
+    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -524,8 +572,7 @@ hipError_t decode_launch(const void* q, const void* kc, const void* vc, const fl
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    decode_combine_kernel<TQ, D><<<B * Hq, 256, 0, st>>>(ws, (TQ*)out, lse, nsplit, Dt);
-    return hipGetLastError();
+    return launch_combine<TQ, D>(ws, (TQ*)out, lse, B * Hq, nsplit, Dt, st);
 }
 
 }  // namespace
@@ -601,9 +648,8 @@ hipError_t decode_bf16q(const void* q, const void* kc, const void* vc, const flo
                                                                        seqlens, k_scale, v_scale, ws, Hq, Hkv, Lk, nsplit, scale, D);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (D <= 64) decode_combine_kernel<bf16_t, 64><<<B * Hq, 256, 0, st>>>(ws, (bf16_t*)out, lse, nsplit, D);
-    else decode_combine_kernel<bf16_t, 128><<<B * Hq, 256, 0, st>>>(ws, (bf16_t*)out, lse, nsplit, D);
-    return hipGetLastError();
+    return D <= 64 ? launch_combine<bf16_t, 64>(ws, (bf16_t*)out, lse, B * Hq, nsplit, D, st)
+                   : launch_combine<bf16_t, 128>(ws, (bf16_t*)out, lse, B * Hq, nsplit, D, st);
 }
 }  // namespace
 

@@ -49,20 +49,23 @@ def test_lengths(G, D, Lk):
         assert (out.cpu().double() - o).abs().max() <= 2e-2 and (lse.cpu().double() - l).abs().max() <= 1e-4
 
 
+@pytest.mark.parametrize("Lk,slices", [(500, 4), (1000, 8)])  # either combine kernel
 @pytest.mark.parametrize("dt", [torch.bfloat16, torch.float32, "e4m3"])
 @pytest.mark.parametrize("G", [4, 17])  # 17: the vector kernel
-def test_infinities_and_nan_in_a_slice_without_weight(G, dt):
+def test_infinities_and_nan_in_a_slice_without_weight(G, dt, Lk, slices):
     # one key holds all the weight, the others' underflows to zero (scores 256 and -1024), and 0 * inf is NaN: what a row
-    # holds reaches the result whether it shares a slice with that key (10) or not (700, 990)
-    Lk, D, n = 1000, 64, 995
+    # holds reaches the result whether it shares a slice with that key (10) or not (Lk - 10, Lk - 200)
+    D, n = 64, Lk - 5
+    if G == 4:
+        assert u.unigist_decode_workspace(1, G, 1, Lk, D, u.UNIGIST_BF16) == -(-G * slices * (D + 2) * 4 // 256) * 256
     q = torch.full((1, G, D), 4.0)
     k = torch.full((1, 1, Lk, D), -32.0)
     k[:, :, 0] = 8.0
     v = torch.randn(1, 1, Lk, D, generator=torch.Generator().manual_seed(G)).to(torch.float8_e4m3fn).float()
     nan = float("nan")
-    bad = {(10, 1): nan, (700, 5): nan, (990, 7): nan}
+    bad = {(10, 1): nan, (Lk - 200, 5): nan, (Lk - 10, 7): nan}
     if dt != "e4m3":  # which has no infinities
-        bad |= {(10, 2): float("inf"), (700, 3): float("inf"), (990, 60): -float("inf")}
+        bad |= {(10, 2): float("inf"), (Lk - 200, 3): float("inf"), (Lk - 10, 60): -float("inf")}
     for (row, col), x in bad.items():
         v[:, :, row, col] = x
     v[:, :, n:] = nan  # behind the sequence: never read into the result
@@ -80,3 +83,23 @@ def test_infinities_and_nan_in_a_slice_without_weight(G, dt):
     # the result is the first row, rounded to bf16 at most
     assert (out.cpu().double() - o)[ok].abs().max() <= 2.0 ** -8 * o[ok].abs().max()
     assert (lse.cpu().double() - l).abs().max() <= 1e-3  # fp32 around 256
+
+
+@pytest.mark.parametrize("dt", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("D", [8, 64, 72, 128])
+@pytest.mark.parametrize("Lk,slices", [(256, 2), (384, 3), (512, 4), (513, 5)])
+def test_few_slices(dt, D, Lk, slices):
+    # up to four slices are merged by one wave; the middle sequences leave one or more of them empty
+    B, G = 4, 4
+    assert u.unigist_decode_workspace(B, G, 1, Lk, D, u.UNIGIST_BF16) == -(-B * G * slices * ((64 if D <= 64 else 128) + 2) * 4 // 256) * 256
+    gen = torch.Generator().manual_seed(Lk + D)
+    q = torch.randn(B, G, D, generator=gen).bfloat16()
+    k, v = (torch.randn(B, 1, Lk, D, generator=gen).bfloat16() for _ in range(2))
+    n = [Lk, 130, 0, 1]
+    ws = torch.full((u.unigist_decode_workspace(B, G, 1, Lk, D, u.UNIGIST_F32),), 255, dtype=torch.uint8).cuda()  # NaNs
+    out, lse = u.decode(*(t.to(dt).cuda() for t in (q, k, v)), torch.tensor(n, dtype=torch.int32).cuda(), workspace=ws)
+    o, l = _exact(q, k, v, n)
+    # bf16: P and result rounded to 2^-9 each on values of size at most max |v| <= 5; fp32: sums of up to 513 terms
+    assert (out.cpu().double() - o).abs().max() <= (2e-2 if dt == torch.bfloat16 else 2e-5)
+    live = torch.isfinite(l)
+    assert torch.equal(torch.isfinite(lse.cpu()), live) and (lse.cpu().double()[live] - l[live]).abs().max() <= 1e-4
