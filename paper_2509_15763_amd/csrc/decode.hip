@@ -266,7 +266,8 @@ __global__ __launch_bounds__(64) void decode_combine_few_kernel(const float* __r
 
 // More slices, up to 64: four waves, each taking every fourth slice (the accumulators of up to kBatch slices and, one slice
 // per lane, the references of all are in flight).
-// Slice kernel + this, us: 8000 keys x 8 kv heads 27.6 -> 14.8, 20000 keys x 1 kv head 42.0 -> 16.6.
+// Slice kernel + this, us, against a combine kernel that loops over the slices twice: 8000 keys x 8 kv heads 27.6 -> 15.5,
+// 20000 keys x 1 kv head 42.1 -> 17.6 (with the slice kernel as it now is 13.8 and 15.6).
 template <typename T, int D>
 __global__ __launch_bounds__(256) void decode_combine_kernel(const float* __restrict__ ws, T* __restrict__ out,
                                                             float* __restrict__ lse, int nsplit, int Dt) {
@@ -336,7 +337,9 @@ hipError_t launch_combine(const float* ws, T* out, float* lse, int BH, int nspli
 //                 free as long as Q uses the same one).  bf16: load t takes the 16 bytes at 64 t + 16 g4, so the four
 //                 lanes of a row read 64 contiguous bytes per instruction; with D/4 contiguous elements per lane every
 //                 16 bytes of an instruction lay in another 64-byte segment, and the loads' address processing cost
-//                 6 to 8 % (us: 64 x 17408 keys 782 -> 742, 100 x 3000 247 -> 229, 24 x 20000 ragged 229 -> 214).
+//                 5 to 12 % (slice kernel + combine, us, 32/8 heads, D = 128: 1500 keys 9.3 -> 8.9, 4 x 1500 14.1 -> 12.4, 100 x
+//                 3000 227 -> 215, 24 x 20000 ragged 218 -> 204; 64 x 17408, near the memory's rate, 752 -> 737; nothing at
+//                 D = 64, where a row is 128 bytes).
 //                 E4M3: the lane's D/4 codes are two loads that the next lane continues; 64 t + 16 g4 gained nothing.
 //                 B = Q^T: column = query head of the group (columns >= G are zero), in registers;
 //   softmax       a head is a column spread over four lanes, each holding 4 of every 16 keys; its running
@@ -345,9 +348,12 @@ hipError_t launch_combine(const float* ws, T* out, float* lse, int BH, int nspli
 //                 wave widens its 32 V rows to bf16 into a private swizzled tile and reads it back transposed.
 // The four waves' partial (m, l, O) are merged through LDS and written to the workspace like the other kernels'.
 // Four workgroups per CU for the 8-bit cache (at D = 128 the compiler's own choice, 130 VGPRs, allows three; a wave has half
-// the bytes in flight that it has for bf16): 16 sequences of up to 9001 keys 48.6 -> 44.3 us.
+// the bytes in flight that it has for bf16): 64 ragged sequences of up to 3000 keys 54.5 -> 51.9 us, 128 x 1500 at D = 96
+// and 16/4 heads 38.1 -> 35.9; 16 ragged of up to 9001, 64 x 17408 and all launches of few workgroups unchanged.  For a
+// bf16 cache none is asked for: three, which the registers allow without asking, cost 2 to 4 % of a launch of few slices (us
+// with / without: 4 x 1500 keys 12.9 / 12.5, 8000 14.6 / 14.0) and 1.5 % of 64 x 17408 (750 / 738).
 template <int D, bool E4M3>
-__global__ __launch_bounds__(kThreads, E4M3 ? 4 : 3) void decode_split_mfma_kernel(const bf16_t* __restrict__ q,
+__global__ __launch_bounds__(kThreads, E4M3 ? 4 : 1) void decode_split_mfma_kernel(const bf16_t* __restrict__ q,
                                                                          const uint8_t* __restrict__ kc,
                                                                          const uint8_t* __restrict__ vc,
                                                                          const int* __restrict__ seqlens,
@@ -588,9 +594,9 @@ bool decode_grouped(int Hq, int Hkv, unigist_dtype dt) {
 // with the number of rounds of 256 workgroups times the slice length: the split is chosen to fill whole rounds
 // (a batch of 48 sequences x 8 kv heads = 384 workgroups would leave half of the second round idle), with a
 // small price per slice for the partial results the combine kernel has to merge, and never slices shorter than
-// 256 keys -- 128, one iteration of the kernel, where up to 64 (sequence, head) units leave most of the chip idle: 1500 keys
-// x 8 kv heads 9.8 -> 8.4 us, 300 keys 9.3 -> 8.2 (both kernels).  Measured on batches of 1 to 256 sequences: one round is best up to 64 (sequence, head) units, two up
-// to 256 units, four beyond.  A workspace too small for the shorter slices (whose size would otherwise fall where a batch
+// 256 keys -- 128, one iteration of the kernel, where up to 64 (sequence, head) units leave most of the chip idle: both
+// kernels for 1500 keys x 8 kv heads 10.5 -> 8.9 us, 300 keys 8.9 -> 7.6, 8 x 500 keys 11.1 -> 9.6.  Measured on batches of
+// 1 to 256 sequences: one round is best up to 64 (sequence, head) units, two up to 256 units, four beyond.  A workspace too small for the shorter slices (whose size would otherwise fall where a batch
 // passes 64 units, so that a loop that sized its buffer for 9 to 12 sequences could not run 8) is served with 256 keys.
 namespace {
 long decode_units(int B, int Hq, int Hkv, unigist_dtype dt) { return (long)B * (decode_grouped(Hq, Hkv, dt) ? Hkv : Hq); }
