@@ -549,6 +549,11 @@ typedef struct unigist_row_group_plan {
 } unigist_row_group_plan;
 unigist_status unigist_plan_row_group(int L, int r, int W, int sinks, int window_mode, int G, int kernel, int group,
                                       unigist_row_group_plan* out, int kind_capacity, signed char* kind);
+/*
+ * Launch order of those workgroups: workgroup n (0 .. n_groups * B * Hkv - 1) of a dense launch over L rows handles group
+ * *group of (batch, kv head) pair *pair = b * Hkv + h.  Every (pair, group) occurs exactly once.
+ */
+unigist_status unigist_plan_row_slot(int B, int Hq, int Hkv, int L, int n, int* pair, int* group);
 unigist_status unigist_plan_row_tile(int L, int r, int W, int sinks, int window_mode, int kernel, int tile,
                                      unigist_row_tile_plan* out, int kind_capacity, signed char* kind);
 /*

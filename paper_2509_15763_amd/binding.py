@@ -35,7 +35,7 @@ EXPORTS = [
     "unigist_cache_ring_rows", "unigist_cache_to_ring", "unigist_cache_from_ring", "unigist_cache_ring_append",
     "unigist_cache_ring_step",
     "unigist_decode_noalloc", "unigist_decode_noalloc_scratch_bytes", "unigist_debug_force_plain_alu",
-    "unigist_window_start", "unigist_plan_row_tile", "unigist_plan_row_group", "unigist_bwd_plan_build", "unigist_plan_key_tile", "unigist_plan_gist_unit",
+    "unigist_window_start", "unigist_plan_row_tile", "unigist_plan_row_group", "unigist_plan_row_slot", "unigist_bwd_plan_build", "unigist_plan_key_tile", "unigist_plan_gist_unit",
     "unigist_probe_read_rate",
 ]
 
@@ -120,6 +120,8 @@ def load():
     lib.unigist_decode_noalloc.argtypes = [vp, vp, vp, vp, fp, ip, ip, ip, ip, vp, ip, ip, vp]
     lib.unigist_plan_row_tile.restype = ip
     lib.unigist_plan_row_tile.argtypes = [ip] * 7 + [C.POINTER(_RowTilePlan), ip, vp]
+    lib.unigist_plan_row_slot.restype = ip
+    lib.unigist_plan_row_slot.argtypes = [ip] * 5 + [C.POINTER(ip), C.POINTER(ip)]
     lib.unigist_plan_row_group.restype = ip
     lib.unigist_plan_row_group.argtypes = [ip] * 8 + [C.POINTER(_RowGroupPlan), ip, vp]
     lib.unigist_bwd_plan_build.restype = ip
@@ -356,6 +358,13 @@ def unigist_plan_row_group(L, r, W, sinks, window_mode, G, kernel, group) -> dic
     _check(load().unigist_plan_row_group(*args, kind.size, kind.ctypes.data), "unigist_plan_row_group")
     d = {n: getattr(p, n) for n, _ in _RowGroupPlan._fields_ if n not in ("head", "row0")}
     return {**d, "head": list(p.head), "row0": list(p.row0), "kind": kind}
+
+
+def unigist_plan_row_slot(B, Hq, Hkv, L, n):
+    """-> ((batch, kv head) pair, group) of workgroup n of a forward or dQ launch."""
+    pair, group = C.c_int(), C.c_int()
+    _check(load().unigist_plan_row_slot(B, Hq, Hkv, L, n, C.byref(pair), C.byref(group)), "unigist_plan_row_slot")
+    return pair.value, group.value
 
 
 def unigist_bwd_plan_build(B, Hq, Hkv, L, D, r, W, sinks=0, window_mode=UNIGIST_WINDOW_SLIDING) -> dict:

@@ -98,20 +98,11 @@ __global__ __launch_bounds__(NT, 3) void fwd_mfma_kernel(const bf16_t* __restric
     const int lane = tid & 63, w = tid >> 6;
     const int r16 = lane & 15, g4 = lane >> 4;  // MFMA 16x16x32: lane = (row or column r16, k-group g4)
 
-    // ---- which (batch, kv head) and which four units of it (plan.h: a unit is 32 rows of one query head): a kv head
-    // stays on one XCD, long walks first
+    // ---- which (batch, kv head) and which four units of it (plan.h: a unit is 32 rows of one query head)
     const int G = s.Hq / s.Hkv;
-    const int NP = s.B * s.Hkv;
-    int pr, wt;
-    if ((NP & 7) == 0) {
-        const int mm = n >> 3;
-        pr = (n & 7) + 8 * (mm % (NP >> 3));
-        wt = nq - 1 - mm / (NP >> 3);
-    } else {
-        pr = n % NP;
-        wt = nq - 1 - n / NP;
-    }
-    const int b = pr / s.Hkv, hk = pr % s.Hkv;
+    const RowSlot slot = row_slot(n, s.B * s.Hkv, nq, G);
+    const int wt = slot.wg;
+    const int b = slot.pair / s.Hkv, hk = slot.pair % s.Hkv;
     if constexpr (MODE == RAGGED) {
         // The sequence's state comes from device memory, so it is checked here: a workgroup of a sequence whose
         // state is invalid, or whose units lie past the sequence's rows, leaves (the whole workgroup, before any

@@ -156,6 +156,20 @@ extern "C" unigist_status unigist_plan_row_group(int L, int r, int W, int sinks,
     return UNIGIST_OK;
 }
 
+extern "C" unigist_status unigist_plan_row_slot(int B, int Hq, int Hkv, int L, int n, int* pair, int* group) {
+    if (!pair || !group || B < 1 || Hq < 1 || Hkv < 1 || Hq % Hkv != 0 || L < 1 || L > kMaxL) return UNIGIST_EINVAL;
+    const int G = Hq / Hkv;
+    const int64_t NP = (int64_t)B * Hkv;
+    if (((int64_t)L + kWaveRows - 1) / kWaveRows * G > 0x7fffffff - kUnitsPerWg) return UNIGIST_EUNSUPPORTED;
+    const int per = row_units(L, G).per;
+    if (per * NP > 0x7fffffff) return UNIGIST_EUNSUPPORTED;
+    if (n < 0 || n >= per * NP) return UNIGIST_EINVAL;
+    const RowSlot r = row_slot(n, (int)NP, per, G);
+    *pair = r.pair;
+    *group = r.wg;
+    return UNIGIST_OK;
+}
+
 // four row blocks of one head: the workgroups of a group of one
 extern "C" unigist_status unigist_plan_row_tile(int L, int r, int W, int sinks, int window_mode, int kernel, int tile,
                                                 unigist_row_tile_plan* out, int kind_capacity, signed char* kind) {

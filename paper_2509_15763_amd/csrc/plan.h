@@ -53,6 +53,28 @@ __host__ __device__ inline RowGroup row_group(int rows, int G, int wg) {
     if (g.i1 > rows - 1) g.i1 = rows - 1;
     return g;
 }
+// Workgroup n of a launch with `per` workgroups for each of NP (batch, kv head) pairs -> pair and workgroup of the pair, the
+// longest walks first.  The G workgroups that share 128 query rows follow each other, so that one finds the keys that
+// another has brought into the L2 (the 32 rows of every pair in turn instead cost batches of short chunks up to a quarter:
+// 64 sequences x 128 rows over 9000 positions, 32/8 heads 493 us, bunched 381; 75 x 256 rows, 16/4 heads 525 / 509; dQ of
+// 64 x 512 rows read 580 MB, bunched 372).  Workgroup ids go round-robin over the 8 XCDs: where n % 8 can select the pair,
+// its workgroups stay on one XCD.  Where it cannot, the workgroups of a bunch lie on different XCDs, and that pays from
+// about 192 pairs on, whose rounds keep one pair's workgroups far apart (us, plain / bunched: 102 pairs 288 / 300, 132 185
+// / 191, 231 403 / 395, 300 526 / 510, 455 451 / 412).
+constexpr int kBunchPairs = 192;
+struct RowSlot {
+    int pair, wg;
+};
+__host__ __device__ inline RowSlot row_slot(int n, int NP, int per, int G) {
+    const bool by_xcd = (NP & 7) == 0;
+    const int P = by_xcd ? NP >> 3 : NP, m = by_xcd ? n >> 3 : n;  // m: place among the P pairs that share the XCD, or all
+    const int w = by_xcd || NP >= kBunchPairs ? G : 1;             // workgroups that follow each other
+    const int bunch = m / (w * P), left = per - w * bunch, width = left < w ? left : w, i = m - w * bunch * P;
+    RowSlot r;
+    r.pair = by_xcd ? (n & 7) + 8 * (i / width) : i / width;
+    r.wg = left - 1 - i % width;
+    return r;
+}
 // Its wave: a query head of the group and the first of its kWaveRows rows (of which those below `rows` exist).  The last
 // workgroup may have waves without a unit (live = false): they shadow the last one and only stage.
 struct RowWave {

@@ -52,6 +52,12 @@ static void walk_plans(const Shape& s) {
         CHECK(unigist_plan_row_group(s.L, s.r, s.W, s.sinks, s.mode, G, 0, n_groups, &p, 0, nullptr) == UNIGIST_EINVAL);
         CHECK(unigist_plan_row_group(s.L, s.r, s.W, s.sinks, s.mode, G, 0, -1, &p, 0, nullptr) == UNIGIST_EINVAL);
     }
+    {
+        int pair = -1, group = -1;
+        CHECK(unigist_plan_row_slot(s.B, s.Hq, s.Hkv, s.L, 0, &pair, &group) == UNIGIST_OK && pair >= 0 && group >= 0);
+        CHECK(unigist_plan_row_slot(s.B, s.Hq, s.Hkv, s.L, -1, &pair, &group) == UNIGIST_EINVAL);
+        CHECK(unigist_plan_row_slot(s.B, s.Hq, s.Hkv, s.L, 0, nullptr, &group) == UNIGIST_EINVAL);
+    }
     unigist_bwd_plan bp;
     CHECK(unigist_bwd_plan_build(s.B, s.Hq, s.Hkv, s.L, s.D, s.r, s.W, s.sinks, s.mode, &bp) == UNIGIST_OK);
     CHECK(bp.workspace_bytes == unigist_attn_bwd_workspace_ex(s.B, s.Hq, s.Hkv, s.L, s.D, s.r, s.W, s.sinks, s.mode, UNIGIST_BF16));

@@ -72,7 +72,30 @@ def test_group_of_one_is_the_row_tile():
             assert (a["kind"][live] == b["kind"][live]).all()
 
 
+@pytest.mark.parametrize("L", [1, 100, 128, 300, 777])
+@pytest.mark.parametrize("B,Hq,Hkv", [(1, 1, 1), (1, 32, 8), (3, 28, 4), (32, 32, 8), (2, 16, 16), (5, 12, 3), (40, 8, 8), (65, 28, 7),
+                                      (191, 4, 1), (193, 4, 1), (9, 24, 8)])
+def test_launch_order(B, Hq, Hkv, L):
+    G, NP = Hq // Hkv, B * Hkv
+    per = -(-(-(-L // 32) * G) // 4)
+    order = [u.unigist_plan_row_slot(B, Hq, Hkv, L, n) for n in range(NP * per)]
+    assert len(set(order)) == NP * per
+    assert all(0 <= pair < NP and 0 <= group < per for pair, group in order)
+    if NP % 8 == 0:  # a pair stays on one XCD
+        assert all(pair % 8 == n % 8 for n, (pair, _) in enumerate(order))
+    # one after the other on the XCD (or in the launch): the groups of a bunch, longest walk first, then the next pair
+    lanes = [order[x::8] for x in range(8)] if NP % 8 == 0 else [order]
+    w = G if NP % 8 == 0 or NP >= 192 else 1
+    for lane in lanes:
+        pairs = sorted({pair for pair, _ in lane})
+        want = [(pair, group) for top in range(per, 0, -w) for pair in pairs for group in range(top - 1, max(top - w, 0) - 1, -1)]
+        assert lane == want
+
+
 def test_arguments():
+    for bad in [(0, 4, 1, 10, 0), (1, 4, 3, 10, 0), (1, 4, 1, 0, 0), (1, 4, 1, 100, 4), (1, 4, 1, 100, -1)]:
+        with pytest.raises(u.UnigistError):
+            u.unigist_plan_row_slot(*bad)
     assert u.load().unigist_plan_row_group(100, 4, 8, 0, 0, 4, 0, 0, None, 0, None) == 1
     for bad in [(0, 4, 8, 0, 0, 4, 0, 0), (100, 4, 8, 0, 0, 0, 0, 0), (100, 4, 8, 0, 0, 4, 2, 0), (100, 4, 8, 0, 0, 4, 0, 4),
                 (100, 4, 8, 0, 0, 4, 0, -1), (100, 4, 8, 0, 2, 4, 0, 0)]:
