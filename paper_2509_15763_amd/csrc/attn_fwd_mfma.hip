@@ -412,19 +412,22 @@ __global__ __launch_bounds__(NT, 3) void fwd_mfma_kernel(const bf16_t* __restric
 // Unused LDS to ask for so that two workgroups share a CU instead of three, where that ends a launch earlier.  At
 // D = 128 the time in which a CU finishes one, two or three workgroups that run together is about 0.52 : 0.66 : 1
 // (4096-row chunks of the 32/8-head layer over 24K tokens: 145, 184, 278 us): two at a time are as fast per workgroup
-// as three, and when all walks are about equally long a launch ends with its last, partly filled round.  So 1024
-// workgroups take 3 + 1 per CU (measured 408 us) or 2 + 2 (367 us).  Walks of different lengths (a whole sequence
-// from its first token) fill the last round by themselves and keep three.
+// as three, and when all walks are about equally long a launch ends with its last, partly filled round: 1024 workgroups
+// take 3 + 1 per CU or 2 + 2.  Three / two per CU, us, prefill chunks over P positions:
+//   by workgroups (32/8 heads, P 65K, W 1024, r 4)      768   648 /  730     784   835 /  790     896   929 /  802
+//     1024   953 /  858     1152   982 / 1148     2304  1898 / 2060     2560  2112 / 2230     4096  3480 / 3707
+//   by steps of a walk (1024 workgroups, no gists)      18    59.4 / 61.9    33    87 /  89       65   140.8 / 141.4
+//     with gists 74  310 / 282      103  258 / 234
+//   by workgroups nq that share a pair's keys (P 9000)  nq 2  218 /  239     4     219 /  233     8    184 /  188
+//     16  187 /  190      32  191 /  184      64  205 /  189;   1 (P 9000, 800 workgroups)  229 /  201
+// So: the second round only (by the third the workgroups of a CU have drifted apart and fill each other's tails); walks long
+// enough to matter; and not where a few workgroups share a pair's keys, which then come from memory: a third workgroup
+// hides that.  Walks of different lengths (a whole sequence from its first token) fill the last round by themselves.
 unsigned lds_for_two_per_cu(const AttnShape& s, int nq, long nblk) {
-    if (s.D <= 64) return 0;
+    if (s.D <= 64 || nblk <= 3 * 256 || nblk > 4 * 256 || (nq > 1 && nq < 32)) return 0;
     const int first = row_walk(s, s.qpos0, s.qpos0 + std::min(kWaveRows, s.Lq) - 1, BN).steps();
     const int last = row_walk(s, s.L - 1, s.L - 1, BN).steps();
-    if (nq > 1 && first < 0.75 * last) return 0;
-    auto cost = [nblk](int per_cu, double full_round) {
-        const long rem = nblk % (256 * per_cu);
-        return (double)(nblk / (256 * per_cu)) * full_round + (rem == 0 ? 0. : rem <= 256 ? 0.52 : rem <= 512 ? 0.66 : 1.);
-    };
-    return cost(2, 0.66) < 0.97 * cost(3, 1.) ? 24 * 1024 : 0;
+    return last < 64 || (nq > 1 && first < 0.75 * last) ? 0 : 24 * 1024;
 }
 
 hipError_t launch_fwd_mfma(const void* q, const void* k, const void* v, void* out, float* lse, const AttnShape& s,
