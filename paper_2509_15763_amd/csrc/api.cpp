@@ -407,7 +407,7 @@ extern "C" unigist_status unigist_cache_ring_append(void* kc, void* vc, const vo
     if (st != UNIGIST_OK) return st;
     if (cap < 1 || new_rows < 1) return UNIGIST_EINVAL;
     if (!kc || !vc || !k_new || !v_new || !t_old || !n_new || !rows_out) return UNIGIST_EINVAL;
-    hipError_t e = launch_cache_ring_append(kc, vc, k_new, v_new, new_rows, t_old, n_new, nullptr, cap, rows_out, B, Hkv, D,
+    hipError_t e = launch_cache_ring_append(kc, vc, k_new, v_new, new_rows, t_old, n_new, cap, rows_out, B, Hkv, D,
                                             r >= kMaxL ? kMaxL + 1 : r + 1, sinks > kMaxL ? kMaxL : sinks,
                                             W > kMaxL ? kMaxL : W, window_mode == UNIGIST_WINDOW_UNITS, dt_bytes(dt), kMaxL,
                                             (hipStream_t)hip_stream);
@@ -422,10 +422,10 @@ extern "C" unigist_status unigist_cache_ring_step(void* kc, void* vc, const void
     if (st != UNIGIST_OK) return st;
     if (cap < 1 || new_rows < 1) return UNIGIST_EINVAL;
     if (!kc || !vc || !k_new || !v_new || !t || !rows_out) return UNIGIST_EINVAL;
-    hipError_t e = launch_cache_ring_append(kc, vc, k_new, v_new, new_rows, t, n_new, t, cap, rows_out, B, Hkv, D,
-                                            r >= kMaxL ? kMaxL + 1 : r + 1, sinks > kMaxL ? kMaxL : sinks,
-                                            W > kMaxL ? kMaxL : W, window_mode == UNIGIST_WINDOW_UNITS, dt_bytes(dt), kMaxL,
-                                            (hipStream_t)hip_stream);
+    hipError_t e = launch_cache_ring_step(kc, vc, k_new, v_new, new_rows, t, n_new, cap, rows_out, B, Hkv, D,
+                                          r >= kMaxL ? kMaxL + 1 : r + 1, sinks > kMaxL ? kMaxL : sinks,
+                                          W > kMaxL ? kMaxL : W, window_mode == UNIGIST_WINDOW_UNITS, dt_bytes(dt), kMaxL,
+                                          (hipStream_t)hip_stream);
     return e == hipSuccess ? UNIGIST_OK : UNIGIST_ELAUNCH;
 }
 

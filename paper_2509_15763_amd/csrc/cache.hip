@@ -231,32 +231,55 @@ __device__ __forceinline__ void ring_append(char* kc, char* vc, const char* k_ne
     *row(base) = nw;
 }
 
-// One token per active sequence (n_new_v null: of every sequence), in place.  One workgroup per sequence, one wave per kv
-// head (in turn, from 17 heads on).  t_next (null: not wanted; may be t_old_v) gets the sequences' new last positions,
-// which only a workgroup that holds all of a sequence's readers of t_old can write in place: a caller that advances its
-// positions itself spends a comparison, a product and a sum, three launches of 2 us each, on top of this one of 3 us.
-constexpr int kAppendWaves = 16;
-__global__ __launch_bounds__(64 * kAppendWaves) void cache_ring_append_kernel(
-    char* __restrict__ kc, char* __restrict__ vc, const char* __restrict__ k_new, const char* __restrict__ v_new, int new_rows,
-    const int* t_old_v, const int* __restrict__ n_new_v, int* t_next, int cap, int* __restrict__ rows_out_v, int Hkv,
-    RingLay g, int row_bytes, int max_pos) {
-    const int b = blockIdx.x;
-    const int t_old = t_old_v[b], act = n_new_v ? n_new_v[b] : 1;
-    int rows = -1;
-    const bool ok0 = t_old >= -1 && (act == 0 || act == 1) && t_old < max_pos - act;
-    const int t = t_old + act;
-    if (ok0) {
-        rows = ring_rows(g, t);
-        if (rows > cap || ring_rows(g, t_old) > cap) rows = -1;
+// the sequence's position after the append and its rows then (-1: an invalid state, or it does not fit)
+struct RingStep {
+    int t, rows;
+};
+__device__ __forceinline__ RingStep ring_step(const RingLay& g, int t_old, int act, int cap, int max_pos) {
+    RingStep r;
+    r.t = t_old + act;
+    r.rows = -1;
+    if (t_old >= -1 && (act == 0 || act == 1) && t_old < max_pos - act) {
+        r.rows = ring_rows(g, r.t);
+        if (r.rows > cap || ring_rows(g, t_old) > cap) r.rows = -1;
     }
+    return r;
+}
+
+// One token per active sequence, in place.  grid (Hkv, B), one wave.
+__global__ __launch_bounds__(64) void cache_ring_append_kernel(char* __restrict__ kc, char* __restrict__ vc,
+                                                              const char* __restrict__ k_new, const char* __restrict__ v_new,
+                                                              int new_rows, const int* __restrict__ t_old_v,
+                                                              const int* __restrict__ n_new_v, int cap,
+                                                              int* __restrict__ rows_out_v, int Hkv, RingLay g, int row_bytes,
+                                                              int max_pos) {
+    const int b = blockIdx.y, act = n_new_v[b];
+    const RingStep r = ring_step(g, t_old_v[b], act, cap, max_pos);
+    if (blockIdx.x == 0 && threadIdx.x == 0) rows_out_v[b] = r.rows;
+    if (r.rows < 0 || act == 0) return;
+    ring_append(kc, vc, k_new, v_new, new_rows, r.t, cap, b * Hkv + blockIdx.x, g, row_bytes);
+}
+
+// The same (n_new_v null: for every sequence) with the advance of the positions t_v, which only a workgroup that holds all
+// of a sequence's readers can write in place: grid B, one wave per kv head (in turn, from 17 heads on).  Slower than the
+// other by itself (us: 64 sequences x 8 kv heads 2.1 / 2.8, x 32 2.6 / 3.9, a unit of 8 rows moved for 16 x 40 3.9 / 9.1), but a
+// caller that advances its positions itself spends a comparison, a product and a sum on top, three launches of 2 us each.
+constexpr int kStepWaves = 16;
+__global__ __launch_bounds__(64 * kStepWaves) void cache_ring_step_kernel(
+    char* __restrict__ kc, char* __restrict__ vc, const char* __restrict__ k_new, const char* __restrict__ v_new, int new_rows,
+    int* t_v, const int* __restrict__ n_new_v, int cap, int* __restrict__ rows_out_v, int Hkv, RingLay g, int row_bytes,
+    int max_pos) {
+    const int b = blockIdx.x;
+    const int t_old = t_v[b], act = n_new_v ? n_new_v[b] : 1;
+    const RingStep r = ring_step(g, t_old, act, cap, max_pos);
     __syncthreads();  // every wave has read t_old
     if (threadIdx.x == 0) {
-        rows_out_v[b] = rows;
-        if (t_next) t_next[b] = rows < 0 ? t_old : t;
+        rows_out_v[b] = r.rows;
+        t_v[b] = r.rows < 0 ? t_old : r.t;
     }
-    if (rows < 0 || act == 0) return;
+    if (r.rows < 0 || act == 0) return;
     for (int hk = threadIdx.x >> 6; hk < Hkv; hk += blockDim.x >> 6)
-        ring_append(kc, vc, k_new, v_new, new_rows, t, cap, b * Hkv + hk, g, row_bytes);
+        ring_append(kc, vc, k_new, v_new, new_rows, r.t, cap, b * Hkv + hk, g, row_bytes);
 }
 
 }  // namespace
@@ -291,12 +314,21 @@ hipError_t launch_cache_ring_convert(bool to_ring, const void* kc_in, const void
 }
 
 hipError_t launch_cache_ring_append(void* kc, void* vc, const void* k_new, const void* v_new, int new_rows, const int* t_old,
-                                    const int* n_new, int* t_next, int cap, int* rows_out, int B, int Hkv, int D, int rp1,
-                                    int sinks, int W, int umode, int elem_bytes, int max_pos, hipStream_t st) {
+                                    const int* n_new, int cap, int* rows_out, int B, int Hkv, int D, int rp1, int sinks,
+                                    int W, int umode, int elem_bytes, int max_pos, hipStream_t st) {
     const RingLay g = make_ring_lay(rp1, sinks, W, umode);
-    const int waves = Hkv < kAppendWaves ? Hkv : kAppendWaves;
-    cache_ring_append_kernel<<<B, 64 * waves, 0, st>>>((char*)kc, (char*)vc, (const char*)k_new, (const char*)v_new, new_rows,
-                                                       t_old, n_new, t_next, cap, rows_out, Hkv, g, D * elem_bytes, max_pos);
+    cache_ring_append_kernel<<<dim3(Hkv, B), 64, 0, st>>>((char*)kc, (char*)vc, (const char*)k_new, (const char*)v_new, new_rows,
+                                                          t_old, n_new, cap, rows_out, Hkv, g, D * elem_bytes, max_pos);
+    return hipGetLastError();
+}
+
+hipError_t launch_cache_ring_step(void* kc, void* vc, const void* k_new, const void* v_new, int new_rows, int* t,
+                                  const int* n_new, int cap, int* rows_out, int B, int Hkv, int D, int rp1, int sinks, int W,
+                                  int umode, int elem_bytes, int max_pos, hipStream_t st) {
+    const RingLay g = make_ring_lay(rp1, sinks, W, umode);
+    cache_ring_step_kernel<<<B, 64 * std::min(Hkv, kStepWaves), 0, st>>>((char*)kc, (char*)vc, (const char*)k_new,
+                                                                        (const char*)v_new, new_rows, t, n_new, cap, rows_out,
+                                                                        Hkv, g, D * elem_bytes, max_pos);
     return hipGetLastError();
 }
 
