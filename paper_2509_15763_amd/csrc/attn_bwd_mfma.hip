@@ -197,24 +197,49 @@ __global__ __launch_bounds__(NT, 2) void dkdv_kernel(const bf16_t* __restrict__ 
                                                     AttnShape s_arg, BwdPlan pl,
                                                     std::conditional_t<PACK, DocTab, NoDocs> docs) {
     constexpr bool JOINT = false;
-    constexpr int BLOCK0 = 0;
     constexpr float* keep = nullptr;
     __shared__ __attribute__((aligned(1024))) DkdvSmem<D> sm;
+    AttnShape s = s_arg;
+    if constexpr (!GEN) {
+        s.S = 0;
+        s.umode = 0;
+    }
+    int n = blockIdx.x;
+    if constexpr (PACK) {  // the document becomes the whole problem
+        const int d = doc_of_block(docs, n);
+        n -= docs.blk0[d];
+        s = doc_view(s, docs.len[d]);
+        plan_counts(s, pl, pl.segc);  // pl arrives with the launch's segment length only
+        const size_t ro = (size_t)docs.c0[d] * (QSTR ? s.D : D);
+        const size_t qro = QSTR ? (size_t)docs.c0[d] * s.q_rs : ro;
+        q += qro;
+        k += ro;
+        v += ro;
+        dout += qro;
+        dk += ro;
+        dv += ro;
+        lse2 += docs.c0[d];
+        delta += docs.c0[d];
+        part += (size_t)docs.part0[d] * (2 * D * BNK);
+        comp += (size_t)docs.comp0[d] * (2 * D * BNK);
+    }
 #include "dkdv_body.inc"
 }
 
-// The same inside the joint launch (below): the partials and the window phase's sums of the gist rows (keep) stay in
-// fp32 for the reduction that follows.
-template <int D, bool GIST, bool GEN, bool PACK, bool QSTR>
-__device__ __forceinline__ void dkdv_part(DkdvSmem<D>& sm, int BLOCK0, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
+// The same inside the joint launch (below), n = the workgroup's number in the phase: the partials and the window phase's
+// sums of the gist rows (keep) stay in fp32 for the reduction that follows.
+template <int D, bool GIST, bool GEN, bool QSTR>
+__device__ __forceinline__ void dkdv_part(DkdvSmem<D>& sm, int n, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                           const bf16_t* __restrict__ v, const float* __restrict__ lse2,
                                           const bf16_t* __restrict__ dout, const float* __restrict__ delta,
                                           bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, float* __restrict__ part,
-                                          float* __restrict__ keep, AttnShape s_arg,
-                                          std::conditional_t<PACK, BwdPlan, const BwdPlan&> pl,
-                                          const std::conditional_t<PACK, DocTab, NoDocs>& docs) {
-    constexpr bool JOINT = true;
+                                          float* __restrict__ keep, AttnShape s, const BwdPlan& pl) {
+    constexpr bool JOINT = true, PACK = false;
     const float* comp = nullptr;
+    if constexpr (!GEN) {
+        s.S = 0;
+        s.umode = 0;
+    }
 #include "dkdv_body.inc"
 }
 
@@ -295,16 +320,40 @@ __global__ __launch_bounds__(NT, 2) void dq_kernel(const bf16_t* __restrict__ q,
                                                   const bf16_t* __restrict__ dout, const float* __restrict__ delta,
                                                   bf16_t* __restrict__ dq, AttnShape s_arg, int nq,
                                                   std::conditional_t<PACK, DocTab, NoDocs> docs) {
-    constexpr int BLOCK0 = 0;
     __shared__ __attribute__((aligned(1024))) DqSmem<D> sm;
+    AttnShape s = s_arg;
+    if constexpr (!GEN) {
+        s.S = 0;
+        s.umode = 0;
+    }
+    int n = blockIdx.x;
+    if constexpr (PACK) {
+        const int d = doc_of_block(docs, n);
+        n -= docs.blk0[d];
+        s = doc_view(s, docs.len[d]);
+        nq = row_units(s.L, s.Hq / s.Hkv).per;
+        const size_t ro = (size_t)docs.c0[d] * (QSTR ? s.D : D);
+        const size_t qro = QSTR ? (size_t)docs.c0[d] * s.q_rs : ro;
+        q += qro;
+        k += ro;
+        v += ro;
+        dout += qro;
+        dq += qro;
+        lse2 += docs.c0[d];
+        delta += docs.c0[d];
+    }
 #include "dq_body.inc"
 }
-template <int D, bool GEN, bool PACK, bool QSTR>
-__device__ __forceinline__ void dq_part(DqSmem<D>& sm, int BLOCK0, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
+template <int D, bool GEN, bool QSTR>
+__device__ __forceinline__ void dq_part(DqSmem<D>& sm, int n, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                         const bf16_t* __restrict__ v, const float* __restrict__ lse2,
                                         const bf16_t* __restrict__ dout, const float* __restrict__ delta,
-                                        bf16_t* __restrict__ dq, AttnShape s_arg, int nq,
-                                        const std::conditional_t<PACK, DocTab, NoDocs>& docs) {
+                                        bf16_t* __restrict__ dq, AttnShape s, int nq) {
+    constexpr bool PACK = false;
+    if constexpr (!GEN) {
+        s.S = 0;
+        s.umode = 0;
+    }
 #include "dq_body.inc"
 }
 
@@ -346,11 +395,11 @@ __global__ __launch_bounds__(NT, 2) void bwd_joint_kernel(const bf16_t* __restri
     __shared__ __attribute__((aligned(1024))) char smem[sizeof(DkdvSmem<D>)];
     const int n = blockIdx.x;
     if (n < n_gist)
-        dkdv_part<D, true, GEN, false, QSTR>(*(DkdvSmem<D>*)smem, 0, q, k, v, lse2, dout, delta, dk, dv, part, comp, s, pl, NoDocs{});
+        dkdv_part<D, true, GEN, QSTR>(*(DkdvSmem<D>*)smem, n, q, k, v, lse2, dout, delta, dk, dv, part, comp, s, pl);
     else if (n < n_gist + n_win)
-        dkdv_part<D, false, GEN, false, QSTR>(*(DkdvSmem<D>*)smem, n_gist, q, k, v, lse2, dout, delta, dk, dv, part, comp, s, pl, NoDocs{});
+        dkdv_part<D, false, GEN, QSTR>(*(DkdvSmem<D>*)smem, n - n_gist, q, k, v, lse2, dout, delta, dk, dv, part, comp, s, pl);
     else
-        dq_part<D, GEN, false, QSTR>(*(DqSmem<D>*)smem, n_gist + n_win, q, k, v, lse2, dout, delta, dq, s, nq, NoDocs{});
+        dq_part<D, GEN, QSTR>(*(DqSmem<D>*)smem, n - n_gist - n_win, q, k, v, lse2, dout, delta, dq, s, nq);
 }
 
 template <int D>
