@@ -103,11 +103,12 @@ unigist_status unigist_attn_fwd_ex(const void* q, const void* k, const void* v, 
  * bitwise reproducible run to run.  dq may take q's or dout's place in memory.
  * workspace: device scratch, 256-byte aligned, contents undefined on entry and exit.
  * unigist_attn_bwd_workspace(...) bytes give the fastest plan.  Short sequences spread their gist phase over more
- * partial sums than they need (32/8 heads, D = 128: 64 MB for 4096 tokens at W = 512 instead of 24, 64 for 2 x 2047 at
+ * partial sums than they need (32/8 heads, D = 128: 54 MB for 4096 tokens at W = 512 instead of 22, 64 for 2 x 2047 at
  * W = 128 instead of 18, 10 for 1024 instead of 4.5), and the size falls where a longer sequence needs no such help.  A
- * smaller workspace, down to what the longest segments take -- which grows with L -- is served with longer segments: a
- * buffer sized for the longest of a caller's sequences serves the shorter ones too.  Below that: UNIGIST_EINVAL.  The
- * sums are the same, grouped differently.
+ * smaller workspace is served with longer segments, down to those of 16 query chunks, so that a buffer sized for a longer
+ * sequence serves the shorter ones too.  (Not across the lengths where even these give way to longer ones and the size
+ * halves: about 30K tokens for 32/8 heads at r = 4, and every power of two from 64K on.)  Too small for those:
+ * UNIGIST_EINVAL.  The sums are the same, grouped differently.
  */
 unigist_status unigist_attn_bwd(const void* q, const void* k, const void* v, const void* out,
                                 const float* lse, const void* dout, void* dq, void* dk, void* dv,

@@ -59,15 +59,24 @@ long gist_chunk_steps(const AttnShape& s) {
 // (batch, kv head) pairs.  A workgroup of segc chunks walks segc * Hq/Hkv steps one after the other, so a launch that
 // does not fill the chip's 512 workgroup slots (2 per CU) takes as long as its longest workgroup and wants short
 // segments; a launch of many rounds wants long ones, whose fp32 partial sums (128 KB per workgroup at D = 128, written
-// and read back once) are fewer.  Measured, gist phase + reduction in us, segments of 2 / 4 / 8 / 16 / 32 chunks:
-//   816 steps (2 x 2047 tokens, r 4, W 128)   58 /   62 /   92 /  152 /  248     (16 was the shortest before)
-//   1300      (4096, W 512)                   83 /   76 /   95 /  152 /  278
-//   5400      (8192, W 1024)                 220 /  219 /  198 /  207 /  279
-//   10900     (8192, r 2, W 128)             441 /  433 /  361 /  356 /  375
-//   23000     (16384, W 1024)                785 /  787 /  791 /  729 /  745
-//   104000    (32768, W 1024)               2806 / 2816 / 2842 / 2833 / 2690
+// and read back once) are fewer.  Measured where the phases are launched apart (packs, and backwards beyond
+// run_jointly's line), gist phase + reduction in us, segments of 2 / 4 / 8 / 16 / 32 chunks:
+//   864 steps (2 x 2047 tokens, r 4, W 128)   58 /   62 /   92 /  152 /  248     (16 was the shortest before)
+//   1392      (4096, W 512)                   83 /   76 /   95 /  152 /  278
+//   5280      (8192, W 1024)                 220 /  219 /  198 /  207 /  279
+//   10752     (8192, r 2, W 128)             441 /  433 /  361 /  356 /  375
+//   23616     (16384, W 1024)                785 /  787 /  791 /  729 /  745
+//   99600     (32768, W 1024)               2806 / 2816 / 2842 / 2833 / 2690
 // The lines lie where neighbours cross: half a round of 512 such workgroups for the short ones, three quarters for
 // 16, five rounds for 32.
+// They are not the best lines for a joint launch (dense backwards up to run_jointly's line): there the other phases fill
+// the slots that a few long units leave, and twice the length is as good or better (whole backward, us, lengths as
+// above; * = what is picked):
+//   864   (2 x 2047, W 128)         141* / 130  / 133  / 178  / 276
+//   1392  (4096, W 512)             233  / 225* / 216  / 211  / 318
+//   1872  (4096, 20 units, sinks)   204  / 187* / 170  / 186  / 318
+//   5280  (8192, W 1024)            745  / 745  / 716* / 696  / 681
+//   10752 (8192, r 2, W 128)        756  / 757  / 692  / 653* / 639
 int pick_segc(long steps) {
     const long slots = 512;
     if (steps >= slots * 32 * 5) return 32;
@@ -75,9 +84,9 @@ int pick_segc(long steps) {
     if (steps >= slots * 8 / 2) return 8;
     return steps >= slots * 4 / 2 ? 4 : 2;
 }
-// The longest segments a launch takes for want of room.  A workspace for them is all that a call insists on: it grows with
-// the sequence, where the one for pick_segc's shrinks at each of its lines (32/8 heads, W 512: 74 MB at 3520 rows, 42 MB
-// at 3521), and a buffer sized for the longest of a caller's sequences has to serve the shorter ones.
+// The longest segments a launch takes for want of room.  A workspace for them is all that a call insists on: below the line
+// of 32 it grows with the sequence, where the one for pick_segc's shrinks at each line (32/8 heads, W 512: 74 MB at 3520
+// rows, 42 MB at 3521), and a buffer sized for the longest of a caller's sequences has to serve the shorter ones.
 int roomiest_segc(long steps) { return std::max(pick_segc(steps), 16); }
 
 long launch_steps(const AttnShape& s) { return gist_chunk_steps(s) * s.B * s.Hkv; }
@@ -362,15 +371,19 @@ __device__ __forceinline__ void dq_part(DqSmem<D>& sm, int n, const bf16_t* __re
 // rows in comp for the reduction that follows), so they run as one launch: workgroups 0 .. n_gist-1 are the gist
 // phase, the next n_win the window phase, the rest dQ, whose short walks come last.  What bounds a short backward is not
 // the chip but the longest workgroup of each of its launches: alone, a phase of 2 x 2047 tokens leaves half of the 512
-// workgroup slots empty.  Phases one by one / jointly (without the delta pass), us, 32/8 heads unless noted:
-//   1 head, 1024, D 64     37 /   19        2 x 4096, W 512, r 16  338 /  313
-//   2 x 512                88 /   55        1 x 8192           720 /  677
-//   2 x 2047              150 /  134        1 x 8192, D 64     317 /  287
-//   2048, W 1024          233 /  182        28/4 heads, 12000 1152 / 1088
-//   4096, W 512           248 /  215        4 x 8192, 16/4, D 64  597 / 549
+// workgroup slots empty.  Phases one by one / jointly (whole backward replayed from a graph, us, 32/8 heads unless noted):
+//   1 head, 1024, D 64     36 /   19        2 x 4096, W 512, r 16  361 /  336
+//   2 x 512                91 /   58        1 x 8192           736 /  718
+//   2 x 2047              160 /  141        1 x 8192, D 64     328 /  304
+//   2048, W 1024          238 /  187        28/4 heads, 12000 1167 / 1115
+//   4096, W 512           258 /  224        4 x 8192, 16/4, D 64  617 / 600
+//   12288 (3072 dQ workgroups) 1326 / 1290  16384, D 64 (4096)  700 / 650
 // From about 16K tokens on (dQ workgroups: 4096 at D = 128) the tails it fills are short, and phases that run side by
-// side share the L2s of each other's streams: 1972 / 1995 (16384), 6194 / 6466 (32768), 6651 / 6876 (65536, D 64).
+// side share the L2s of each other's streams: 2025 / 2054 (16384), 2500 / 2584 (2 x 16384, r 8), 6411 / 6710 (32768).
 // The line lies at six rounds of dQ workgroups: 3072 at two workgroups per CU (D = 128), 4608 at three (D = 64).
+// At D = 128 all four instantiations spill 4 to 8 VGPRs (16 to 20 bytes of scratch per lane), unlike the kernels of the
+// phases: the window phase of the dense sliding-window one keeps a K fragment there and loads it again for every 32-row
+// block, which waits for the next chunk's direct loads as well.  The figures above are with that.
 template <int D> bool run_jointly(long n_dq) { return n_dq <= 256 * 6 * (D <= 64 ? 3 : 2); }
 
 // A dq that shares memory with q or dout, which its own workgroups have read before they write, is written too early there

@@ -1,5 +1,5 @@
 """The least workspace a backward takes: the one for gist-phase segments of 16 query chunks (32 in launches of many rounds),
-which grows with the sequence, whatever shorter segments the plan of a large enough workspace has.  Probed through the
+which grows with the sequence up to that line, whatever shorter segments the plan of a large enough workspace has.  Probed through the
 entry points with pointers that are never dereferenced: a call with too small a workspace is refused before anything is
 launched, any other ends at the launch where there is no GPU."""
 import pytest
