@@ -1,10 +1,13 @@
 """A short backward runs its gist phase, window phase and dQ as one launch and writes the gist rows of dK and dV in the
 reduction behind it; run stage by stage it launches them one after the other.  Both against each other (and the joint one
 against the oracle where it is small): padded head dimensions, sinks, unit windows, launches without a gist phase, gist
-tiles that end inside the sequence, row counts on both sides of the rule that chooses."""
+tiles that end inside the sequence.  On both sides of the rule that chooses, and with sinks and unit windows near it, one kv
+head against float64: beyond the rule whole and staged backwards launch the same kernels."""
+import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_2509_15763_amd as u
 from paper_2509_15763_amd import synth
 from _parity import TOL_GRAD_BF16, oracle_fwd_bwd, rel_l2, to_np
@@ -77,3 +80,47 @@ def test_dq_in_place_of_its_inputs(B, Hq, Hkv, L, D, r, W, onto, strided):
     # the same sums, put together in separate launches (as in test_whole_against_stages)
     for a, b in zip((dk, dv), want[1:]):
         assert (a.float() - b.float()).norm() <= 3e-4 * b.float().norm()
+
+
+def _exact_group(q, k, v, do, r, W, S, mode):
+    """Gradients of one kv head and its query heads (q, do [G, L, D], k, v [L, D] on the GPU) in float64, over row blocks."""
+    G, L, D = q.shape
+    q, k, v, do = (t.double() for t in (q, k, v, do))
+    dq, dk, dv = torch.empty_like(q), torch.zeros_like(k), torch.zeros_like(v)
+    for i0 in range(0, L, 512):
+        i1 = min(L, i0 + 512)
+        seen = torch.from_numpy(oracle.mask_rows(np.arange(i0, i1), L, r, W, sinks=S, units=mode == 1)[:, :i1]).cuda()
+        for g in range(G):
+            p = ((q[g, i0:i1] @ k[:i1].T) / D ** 0.5).masked_fill_(~seen, float("-inf")).softmax(1)
+            d = do[g, i0:i1]
+            ds = p * (d @ v[:i1].T - (d * (p @ v[:i1])).sum(1, keepdim=True)) / D ** 0.5
+            dv[:i1] += p.T @ d
+            dq[g, i0:i1] = ds @ k[:i1]
+            dk[:i1] += ds.T @ q[g, i0:i1]
+    return dq, dk, dv
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L,D,r,W,S,mode", [
+    (1, 32, 8, 12288, 128, 8, 256, 0, 0), (1, 32, 8, 12289, 128, 8, 256, 0, 0),   # 3072 workgroups of dQ: the line at D = 128
+    (1, 32, 8, 18432, 64, 16, 200, 0, 0), (1, 32, 8, 18433, 64, 16, 200, 0, 0),   # 4608: at D = 64
+    (1, 32, 8, 12288, 128, 4, 30, 100, 1),                                        # sinks, window in units
+    (2, 28, 4, 6000, 96, 4, 300, 70, 0),
+])
+def test_both_sides_of_the_line_against_float64(B, Hq, Hkv, L, D, r, W, S, mode):
+    q, k, v, do = (t.cuda() for t in synth.attn_inputs(B, Hq, Hkv, L, D, seed=L))
+    kw = dict(sinks=S, window_mode=mode)
+    out, lse = u.attn_fwd(q, k, v, r, W, **kw)
+    dq, dk, dv = u.attn_bwd(q, k, v, out, lse, do, r, W, **kw)
+    b, h, G = B - 1, Hkv - 2, Hq // Hkv
+    heads = slice(h * G, (h + 1) * G)
+    want = _exact_group(q[b, heads], k[b, h], v[b, h], do[b, heads], r, W, S, mode)
+    got = dq[b, heads], dk[b, h][None], dv[b, h][None]
+    for a, e in zip(got, (want[0], want[1][None], want[2][None])):
+        for i0 in range(0, L, 128):  # tile by tile: a lost or doubled tile does not drown in the others
+            x, y = a[:, i0:i0 + 128].double(), e[:, i0:i0 + 128]
+            assert (x - y).norm() <= TOL_GRAD_BF16 * y.norm(), i0
+    # a gist's column collects every segment's partial sums: the first ones on their own
+    for c in range(min(64, (L - S) // (r + 1))):
+        j = S + c * (r + 1) + r
+        for a, e in ((dk, want[1]), (dv, want[2])):
+            assert (a[b, h, j].double() - e[j]).norm() <= TOL_GRAD_BF16 * e[j].norm(), j
