@@ -334,12 +334,14 @@ hipError_t launch_combine(const float* ws, T* out, float* lse, int BH, int nspli
 // softmax over 16-key columns.
 // A wave takes 32 keys per iteration, the workgroup's four waves 128:
 //   S^T = K Q^T   A = K: lane (key r16, g4) holds D/4 elements of its key's row, eight per k-step (the contraction order is
-//                 free as long as Q uses the same one).  bf16: load t takes the 16 bytes at 64 t + 16 g4, so the four
+//                 free as long as Q uses the same one).  bf16 (SEG64): load t takes the 16 bytes at 64 t + 16 g4, so the four
 //                 lanes of a row read 64 contiguous bytes per instruction; with D/4 contiguous elements per lane every
 //                 16 bytes of an instruction lay in another 64-byte segment, and the loads' address processing cost
 //                 5 to 12 % (slice kernel + combine, us, 32/8 heads, D = 128: 1500 keys 9.3 -> 8.9, 4 x 1500 14.1 -> 12.4, 100 x
 //                 3000 227 -> 215, 24 x 20000 ragged 218 -> 204; 64 x 17408, near the memory's rate, 752 -> 737; nothing at
 //                 D = 64, where a row is 128 bytes).
+//                 Rows of a head dimension below D end before the last loads, all of one t then, which repeat the row's start: 13 x 5437 keys at 72 of 128 columns 39.2 -> 46.4 us, at 96 47.1 -> 49.9.  Such rows
+//                 keep D/4 contiguous elements per lane (SEG64 = false), where a lane of every load has none.
 //                 E4M3: the lane's D/4 codes are two loads that the next lane continues; 64 t + 16 g4 gained nothing.
 //                 B = Q^T: column = query head of the group (columns >= G are zero), in registers;
 //   softmax       a head is a column spread over four lanes, each holding 4 of every 16 keys; its running
@@ -352,7 +354,7 @@ hipError_t launch_combine(const float* ws, T* out, float* lse, int BH, int nspli
 // and 16/4 heads 38.1 -> 35.9; 16 ragged of up to 9001, 64 x 17408 and all launches of few workgroups unchanged.  For a
 // bf16 cache none is asked for: three, which the registers allow without asking, cost 2 to 4 % of a launch of few slices (us
 // with / without: 4 x 1500 keys 12.9 / 12.5, 8000 14.6 / 14.0) and 1.5 % of 64 x 17408 (750 / 738).
-template <int D, bool E4M3>
+template <int D, bool E4M3, bool SEG64>
 __global__ __launch_bounds__(kThreads, E4M3 ? 4 : 1) void decode_split_mfma_kernel(const bf16_t* __restrict__ q,
                                                                          const uint8_t* __restrict__ kc,
                                                                          const uint8_t* __restrict__ vc,
@@ -392,7 +394,7 @@ __global__ __launch_bounds__(kThreads, E4M3 ? 4 : 1) void decode_split_mfma_kern
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
         u32x4 z = {0u, 0u, 0u, 0u};
-        const int e = E4M3 ? BPL * g4 + 8 * ks : 32 * ks + 8 * g4;
+        const int e = SEG64 ? 32 * ks + 8 * g4 : BPL * g4 + 8 * ks;
         if (r16 < G && e < Dt) z = *(const u32x4*)(q + ((size_t)b * Hq + hq0 + r16) * Dt + e);
         qf[ks] = __builtin_bit_cast(bf16x8, z);
     }
@@ -428,7 +430,7 @@ __global__ __launch_bounds__(kThreads, E4M3 ? 4 : 1) void decode_split_mfma_kern
             const int row = min(base + 16 * kb2 + r16, k1 - 1);
 #pragma unroll
             for (int t = 0; t < NKL; ++t) {
-                const int o = E4M3 ? BPL * g4 + 16 * t : 64 * t + 16 * g4;  // a piece the rows do not have: the first one (its q is zero)
+                const int o = SEG64 ? 64 * t + 16 * g4 : BPL * EB * g4 + 16 * t;  // a piece the rows do not have: the first one (its q is zero)
                 kw[kb2][t] = *(const u32x4*)(kb + (size_t)row * row_bytes + (o < row_bytes ? o : 0));
             }
         }
@@ -646,12 +648,13 @@ hipError_t decode_bf16q(const void* q, const void* kc, const void* vc, const flo
     const int nsplit = decode_num_splits(B, Hq, Hkv, Lk, D, UNIGIST_BF16, room);
     const float scale = 1.0f / sqrtf((float)D);
     const dim3 grid(nsplit, Hkv, B);
-    if (D <= 64)
-        decode_split_mfma_kernel<64, E4M3><<<grid, kThreads, 0, st>>>((const bf16_t*)q, (const uint8_t*)kc, (const uint8_t*)vc,
-                                                                      seqlens, k_scale, v_scale, ws, Hq, Hkv, Lk, nsplit, scale, D);
-    else
-        decode_split_mfma_kernel<128, E4M3><<<grid, kThreads, 0, st>>>((const bf16_t*)q, (const uint8_t*)kc, (const uint8_t*)vc,
-                                                                       seqlens, k_scale, v_scale, ws, Hq, Hkv, Lk, nsplit, scale, D);
+    const bool seg64 = D == padded_head_dim(D);
+    auto go = [&](auto kern) {
+        kern<<<grid, kThreads, 0, st>>>((const bf16_t*)q, (const uint8_t*)kc, (const uint8_t*)vc, seqlens, k_scale, v_scale, ws, Hq,
+                                        Hkv, Lk, nsplit, scale, D);
+    };
+    if (D <= 64) seg64 ? go(decode_split_mfma_kernel<64, E4M3, !E4M3>) : go(decode_split_mfma_kernel<64, E4M3, false>);
+    else seg64 ? go(decode_split_mfma_kernel<128, E4M3, !E4M3>) : go(decode_split_mfma_kernel<128, E4M3, false>);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return D <= 64 ? launch_combine<bf16_t, 64>(ws, (bf16_t*)out, lse, B * Hq, nsplit, D, st)
