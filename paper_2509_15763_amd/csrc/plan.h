@@ -69,10 +69,20 @@ __host__ __device__ inline RowSlot row_slot(int n, int NP, int per, int G) {
     const bool by_xcd = (NP & 7) == 0;
     const int P = by_xcd ? NP >> 3 : NP, m = by_xcd ? n >> 3 : n;  // m: place among the P pairs that share the XCD, or all
     const int w = by_xcd || NP >= kBunchPairs ? G : 1;             // workgroups that follow each other
-    const int bunch = m / (w * P), left = per - w * bunch, width = left < w ? left : w, i = m - w * bunch * P;
     RowSlot r;
-    r.pair = by_xcd ? (n & 7) + 8 * (i / width) : i / width;
-    r.wg = left - 1 - i % width;
+    int p = 0;  // pair among the P
+    if (P == 1) {
+        r.wg = per - 1 - m;
+    } else if (w == 1) {
+        r.wg = m / P;
+        p = m - r.wg * P;
+        r.wg = per - 1 - r.wg;
+    } else {
+        const int bunch = m / (w * P), left = per - w * bunch, width = left < w ? left : w, i = m - w * bunch * P;
+        p = i / width;
+        r.wg = left - 1 - (i - p * width);
+    }
+    r.pair = by_xcd ? (n & 7) + 8 * p : p;
     return r;
 }
 // Its wave: a query head of the group and the first of its kWaveRows rows (of which those below `rows` exist).  The last
