@@ -102,6 +102,9 @@ __global__ __launch_bounds__(NT, 3) void fwd_mfma_kernel(const bf16_t* __restric
     const int G = s.Hq / s.Hkv;
     const RowSlot slot = row_slot(n, s.B * s.Hkv, nq, G);
     const int wt = slot.wg;
+    // Eight bytes of padding: where a CU holds one workgroup, the place of the loops below in their 32-byte fetch windows
+    // counts (1024-row chunk of 32/8 heads over 31K positions 174 us without, 166 with; 16, 24, 32 bytes 167, 169, 174).
+    if constexpr (D == 128 && MODE == PLAIN) asm volatile("s_nop 0\n\ts_nop 0");
     const int b = slot.pair / s.Hkv, hk = slot.pair % s.Hkv;
     if constexpr (MODE == RAGGED) {
         // The sequence's state comes from device memory, so it is checked here: a workgroup of a sequence whose
