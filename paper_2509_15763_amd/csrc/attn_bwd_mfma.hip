@@ -69,14 +69,6 @@ long gist_chunk_steps(const AttnShape& s) {
 //   99600     (32768, W 1024)               2806 / 2816 / 2842 / 2833 / 2690
 // The lines lie where neighbours cross: half a round of 512 such workgroups for the short ones, three quarters for
 // 16, five rounds for 32.
-// They are not the best lines for a joint launch (dense backwards up to run_jointly's line): there the other phases fill
-// the slots that a few long units leave, and twice the length is as good or better (whole backward, us, lengths as
-// above; * = what is picked):
-//   864   (2 x 2047, W 128)         141* / 130  / 133  / 178  / 276
-//   1392  (4096, W 512)             233  / 225* / 216  / 211  / 318
-//   1872  (4096, 20 units, sinks)   204  / 187* / 170  / 186  / 318
-//   5280  (8192, W 1024)            745  / 745  / 716* / 696  / 681
-//   10752 (8192, r 2, W 128)        756  / 757  / 692  / 653* / 639
 int pick_segc(long steps) {
     const long slots = 512;
     if (steps >= slots * 32 * 5) return 32;
@@ -109,12 +101,38 @@ BwdPlan sized_plan(const AttnShape& s, int segc) {
     return p;
 }
 
-// the plan of a launch whose workspace has `room` bytes: pick_segc's, or the first doubling of it that fits
-BwdPlan make_plan(const AttnShape& s, size_t room = SIZE_MAX) {
-    const long steps = launch_steps(s);
-    int segc = pick_segc(steps);
+// Segment length for a joint launch (dense backwards up to run_jointly's line).  The other phases fill the slots that a few
+// long units leave, so what limits the length is a unit itself, whose segc * Hq/Hkv steps run one after the other: it may take
+// 1.6 times as long as all steps of the launch spread evenly over the chip's workgroup slots.  (The units come first, and
+// in launches that small many of them walk only a part of their segment.)  A step of dQ, 64 keys, takes about 0.55 of a dK/dV
+// step.  Whole backward, us, segments of 2 / 4 / 8 / 16 / 32 chunks; + = what the lines of pick_segc give, * = what is picked:
+//   2 x 2047, 32/8 heads, W 128             136+ / 124  / 117* / 174  / 275
+//   4096, W 512                             227  / 220+ / 205  / 203* / 319
+//   3000, 16/16 heads, D 96, W 300           90  /  78+ /  70* /  68  /  81
+//   6000, 8/1 heads, W 200                  151+* / 150 / 169  / 300  / 557
+//   5000, 28/4 heads, r 2, 60 units         303  / 300  / 290+* / 310 / 539
+//   3 x 2500, 16/4, D 64, 20 units           84  /  75+* / 80  / 122  / 192
+//   8192, W 1024                            744  / 737  / 702+ / 682  / 669*
+//   12000, 16/16, r 2, W 70                 968  / 962  / 968  / 826+ / 758*
+//   20000, 8/1, D 64, W 1000                375  / 374  / 374+ / 373* / 452
+// Sizes are asked for and refused by pick_segc, whose segments are never longer.
+int pick_joint_segc(const AttnShape& s, int n_dq_wgs) {
+    const long G = s.Hq / s.Hkv, NP = (long)s.B * s.Hkv, slots = 256 * (s.D <= 64 ? 3 : 2);
+    const long reach = s.umode ? (s.W + 1L) * s.rp1 : s.W;  // rows that have a key in their window
+    const double gist = (double)launch_steps(s) * G;
+    const double window = (double)((s.L + BNK - 1) / BNK) * NP * G * (std::min((long)s.L, reach + BNK) / MQ);
+    const double dq = (double)n_dq_wgs * (std::min((long)s.L, reach + kWaveRows) + s.L / s.rp1 / 2) / kDqBn;
+    const double even = (gist + window + 0.55 * dq) / slots;
+    int segc = pick_segc(launch_steps(s));
+    while (segc < 32 && 2 * segc * G <= 1.6 * even) segc *= 2;
+    return segc;
+}
+
+// the plan of a launch whose workspace has `room` bytes: segments of segc chunks, or of the first doubling that fits
+BwdPlan make_plan(const AttnShape& s, size_t room, int segc) {
+    const int longest = std::max(segc, roomiest_segc(launch_steps(s)));
     BwdPlan p = sized_plan(s, segc);
-    while (p.total > room && segc < roomiest_segc(steps)) p = sized_plan(s, segc *= 2);
+    while (p.total > room && segc < longest) p = sized_plan(s, segc *= 2);
     plan_order(s, p);
     return p;
 }
@@ -419,7 +437,11 @@ template <int D>
 hipError_t bwd_launch(const bf16_t* q, const bf16_t* k, const bf16_t* v, const bf16_t* out, const float* lse,
                       const bf16_t* dout, bf16_t* dq, bf16_t* dk, bf16_t* dv, char* ws, size_t room,
                       const AttnShape& s, unsigned stages, hipStream_t st) {
-    const BwdPlan pl = make_plan(s, room);
+    const int nq = row_units(s.L, s.Hq / s.Hkv).per;
+    const long nblk = (long)nq * s.Hkv * s.B;
+    if (nblk > 0x7fffffffL) return hipErrorInvalidValue;
+    const bool joint = stages == UNIGIST_BWD_ALL && run_jointly<D>(nblk) && !dq_on_its_inputs(q, dout, dq, s);
+    const BwdPlan pl = make_plan(s, room, joint ? pick_joint_segc(s, (int)nblk) : pick_segc(launch_steps(s)));
     const bool gen = s.S != 0 || s.umode != 0;
     const bool qstr = s.q_rs != 0;  // q, out, dout, dq with the caller's explicit strides
     float* delta = (float*)ws;
@@ -435,11 +457,8 @@ hipError_t bwd_launch(const bf16_t* q, const bf16_t* k, const bf16_t* v, const b
             out, dout, lse, delta, lse2, nrows, s.L, s.qhs, s.Hq, s.q_bs, s.q_hs, s.q_rs, s.D);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    const int nq = row_units(s.L, s.Hq / s.Hkv).per;
-    const long nblk = (long)nq * s.Hkv * s.B, n_gist = (long)pl.slot0[pl.nseg] * s.Hkv * s.B,
-               n_win = (long)((s.L + BNK - 1) / BNK) * s.Hkv * s.B;
-    if (nblk > 0x7fffffffL) return hipErrorInvalidValue;
-    if (stages == UNIGIST_BWD_ALL && run_jointly<D>(nblk) && !dq_on_its_inputs(q, dout, dq, s)) {
+    const long n_gist = (long)pl.slot0[pl.nseg] * s.Hkv * s.B, n_win = (long)((s.L + BNK - 1) / BNK) * s.Hkv * s.B;
+    if (joint) {
         auto go = [&](auto kern) {
             kern<<<dim3((unsigned)(n_gist + n_win + nblk)), NT, 0, st>>>(q, k, v, lse2, dout, delta, dq, dk, dv, part, comp, s,
                                                                        pl, (int)n_gist, (int)n_win, nq);
@@ -619,7 +638,7 @@ hipError_t bwd_launch_pack(const bf16_t* q, const bf16_t* k, const bf16_t* v, co
 size_t bwd_mfma_workspace(const AttnShape& s) { return sized_plan(s, pick_segc(launch_steps(s))).total; }
 size_t bwd_mfma_least_workspace(const AttnShape& s) { return sized_plan(s, roomiest_segc(launch_steps(s))).total; }
 
-BwdPlan make_bwd_plan(const AttnShape& s) { return make_plan(s); }
+BwdPlan make_bwd_plan(const AttnShape& s) { return make_plan(s, SIZE_MAX, pick_segc(launch_steps(s))); }
 
 size_t bwd_mfma_pack_workspace(const AttnShape& s, const int* cu, int ndocs) { return make_pack_plan(s, cu, ndocs, SIZE_MAX).total; }
 size_t bwd_mfma_pack_least_workspace(const AttnShape& s, const int* cu, int ndocs) { return make_pack_plan(s, cu, ndocs, 0).total; }

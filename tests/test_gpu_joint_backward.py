@@ -24,6 +24,8 @@ SHAPES = [
     (1, 8, 2, 1500, 128, 4, 20, 64, 1),     # window in units
     (2, 4, 2, 901, 64, 1, 16, 3, 1),
     (1, 1, 1, 1024, 64, 4, 128, 0, 0),
+    (3, 16, 16, 3001, 64, 2, 70, 0, 0),     # segments of 32 chunks where separate launches take 16
+    (1, 8, 8, 4100, 128, 4, 500, 3, 0),     # 8 and 2
 ]
 LARGE = [(1, 32, 8, 12288, 128, 8, 256, 0, 0), (1, 32, 8, 12289, 128, 8, 256, 0, 0),  # 3072 workgroups of dQ, and more
          (1, 16, 16, 18432, 64, 16, 200, 0, 0), (1, 16, 16, 18561, 64, 16, 200, 0, 0)]  # 2304, 2336: D = 64, joint
