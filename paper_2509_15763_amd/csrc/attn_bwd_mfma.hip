@@ -138,6 +138,18 @@ BwdPlan make_plan(const AttnShape& s, size_t room, int segc) {
 }
 
 // ------------------------------------------------------------------ 1. delta
+// dO . O of eight columns; the columns are summed in this order and the eights in a tree wherever delta is computed, so that
+// it is the same number to the last bit
+__device__ __forceinline__ float dot8(const u32x4& a, const u32x4& b) {
+    float acc = 0.f;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        acc += __uint_as_float(a[t] << 16) * __uint_as_float(b[t] << 16);
+        acc += __uint_as_float(a[t] & 0xffff0000u) * __uint_as_float(b[t] & 0xffff0000u);
+    }
+    return acc;
+}
+
 template <int D>
 __global__ __launch_bounds__(NT) void delta_kernel(const bf16_t* __restrict__ out, const bf16_t* __restrict__ dout,
                                                   const float* __restrict__ lse, float* __restrict__ delta,
@@ -157,11 +169,7 @@ __global__ __launch_bounds__(NT) void delta_kernel(const bf16_t* __restrict__ ou
             a = *(const u32x4*)(out + eoff + sub * 8);
             b = *(const u32x4*)(dout + eoff + sub * 8);
         }
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            acc += __uint_as_float(a[t] << 16) * __uint_as_float(b[t] << 16);
-            acc += __uint_as_float(a[t] & 0xffff0000u) * __uint_as_float(b[t] & 0xffff0000u);
-        }
+        acc = dot8(a, b);
     }
     // reduce over the LPR lanes of a row (LPR is 8 or 16, rows are aligned to LPR lanes)
 #pragma unroll
@@ -341,10 +349,15 @@ struct DqSmem {
     char v[2][BNQ * D * 2];
 };
 
-template <int D, bool GEN, bool PACK, bool QSTR = false>
+// WITH_DELTA = true: the launch runs first and without a delta pass; a wave takes delta and lse * log2(e) of its rows from out
+// and lse and leaves them in the workspace for the dK/dV phases.  The pass reads out and dout for that alone (2 x 268 MB at
+// 32 heads x 32K x 128: 92 us of 8240 for forward and backward, 186 of 6990 for 4 x 16K at r 16); here dout is in registers
+// already and a workgroup reads its 32 KB of out beside its q and dout.
+template <int D, bool GEN, bool PACK, bool QSTR = false, bool WITH_DELTA = false>
 __global__ __launch_bounds__(NT, 2) void dq_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
-                                                  const bf16_t* __restrict__ v, const float* __restrict__ lse2,
-                                                  const bf16_t* __restrict__ dout, const float* __restrict__ delta,
+                                                  const bf16_t* __restrict__ v, const bf16_t* __restrict__ out,
+                                                  const float* __restrict__ lse, float* lse2,
+                                                  const bf16_t* __restrict__ dout, float* delta,
                                                   bf16_t* __restrict__ dq, AttnShape s_arg, int nq,
                                                   std::conditional_t<PACK, DocTab, NoDocs> docs) {
     __shared__ __attribute__((aligned(1024))) DqSmem<D> sm;
@@ -368,15 +381,21 @@ __global__ __launch_bounds__(NT, 2) void dq_kernel(const bf16_t* __restrict__ q,
         dq += qro;
         lse2 += docs.c0[d];
         delta += docs.c0[d];
+        if constexpr (WITH_DELTA) {
+            out += qro;
+            lse += docs.c0[d];
+        }
     }
 #include "dq_body.inc"
 }
 template <int D, bool GEN, bool QSTR>
 __device__ __forceinline__ void dq_part(DqSmem<D>& sm, int n, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
-                                        const bf16_t* __restrict__ v, const float* __restrict__ lse2,
-                                        const bf16_t* __restrict__ dout, const float* __restrict__ delta,
+                                        const bf16_t* __restrict__ v, float* lse2,
+                                        const bf16_t* __restrict__ dout, float* delta,
                                         bf16_t* __restrict__ dq, AttnShape s, int nq) {
-    constexpr bool PACK = false;
+    constexpr bool PACK = false, WITH_DELTA = false;
+    const bf16_t* out = nullptr;
+    const float* lse = nullptr;
     if constexpr (!GEN) {
         s.S = 0;
         s.umode = 0;
@@ -404,20 +423,21 @@ __device__ __forceinline__ void dq_part(DqSmem<D>& sm, int n, const bf16_t* __re
 // block, which waits for the next chunk's direct loads as well.  The figures above are with that.
 template <int D> bool run_jointly(long n_dq) { return n_dq <= 256 * 6 * (D <= 64 ? 3 : 2); }
 
-// A dq that shares memory with q or dout, which its own workgroups have read before they write, is written too early there
-// for the other phases: such calls keep the launches apart.
-bool dq_on_its_inputs(const bf16_t* q, const bf16_t* dout, const bf16_t* dq, const AttnShape& s) {
+// A dq that shares memory with q or dout, which its own workgroups have read before they write, is written too early for the
+// other phases where dQ does not run last: such calls keep the launches apart, delta first and dQ last.  So do calls whose
+// dq shares memory with out or lse, which the delta pass has read whole before anything is written.
+bool dq_on_its_inputs(const bf16_t* q, const bf16_t* dout, const bf16_t* out, const float* lse, const bf16_t* dq, const AttnShape& s) {
     const long long rows = s.q_rs ? s.q_rs : s.D, heads = s.q_rs ? s.q_hs : (long long)s.qhs * s.D,
                     batches = s.q_rs ? s.q_bs : heads * s.Hq;
     const uintptr_t bytes = 2 * (uintptr_t)((s.B - 1) * batches + (s.Hq - 1) * heads + (s.L - 1) * rows + s.D);
-    auto meets = [&](const bf16_t* x) { return (uintptr_t)x < (uintptr_t)dq + bytes && (uintptr_t)dq < (uintptr_t)x + bytes; };
-    return meets(q) || meets(dout);
+    auto meets = [&](const void* x, uintptr_t n) { return (uintptr_t)x < (uintptr_t)dq + bytes && (uintptr_t)dq < (uintptr_t)x + n; };
+    return meets(q, bytes) || meets(dout, bytes) || meets(out, bytes) || meets(lse, (uintptr_t)s.B * s.Hq * s.qhs * sizeof(float));
 }
 
 template <int D, bool GEN, bool QSTR>
 __global__ __launch_bounds__(NT, 2) void bwd_joint_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
-                                                         const bf16_t* __restrict__ v, const float* __restrict__ lse2,
-                                                         const bf16_t* __restrict__ dout, const float* __restrict__ delta,
+                                                         const bf16_t* __restrict__ v, float* __restrict__ lse2,
+                                                         const bf16_t* __restrict__ dout, float* __restrict__ delta,
                                                          bf16_t* __restrict__ dq, bf16_t* __restrict__ dk,
                                                          bf16_t* __restrict__ dv, float* __restrict__ part,
                                                          float* __restrict__ comp, AttnShape s, BwdPlan pl, int n_gist,
@@ -440,7 +460,8 @@ hipError_t bwd_launch(const bf16_t* q, const bf16_t* k, const bf16_t* v, const b
     const int nq = row_units(s.L, s.Hq / s.Hkv).per;
     const long nblk = (long)nq * s.Hkv * s.B;
     if (nblk > 0x7fffffffL) return hipErrorInvalidValue;
-    const bool joint = stages == UNIGIST_BWD_ALL && run_jointly<D>(nblk) && !dq_on_its_inputs(q, dout, dq, s);
+    const bool free_order = stages == UNIGIST_BWD_ALL && !dq_on_its_inputs(q, dout, out, lse, dq, s);
+    const bool joint = free_order && run_jointly<D>(nblk);
     const BwdPlan pl = make_plan(s, room, joint ? pick_joint_segc(s, (int)nblk) : pick_segc(launch_steps(s)));
     const bool gen = s.S != 0 || s.umode != 0;
     const bool qstr = s.q_rs != 0;  // q, out, dout, dq with the caller's explicit strides
@@ -450,7 +471,16 @@ hipError_t bwd_launch(const bf16_t* q, const bf16_t* k, const bf16_t* v, const b
     float* comp = (float*)(ws + pl.off_comp);
     hipError_t e;
     const dim3 reduce_grid((2 * D * BNK / 4) / NT, std::max(pl.n_gt, 1), s.B * s.Hkv);
-    if (stages & UNIGIST_BWD_DELTA) {
+    auto launch_dq = [&](auto with_delta) {
+        constexpr bool WD = decltype(with_delta)::value;
+        auto go = [&](auto kern) { kern<<<dim3((unsigned)nblk), NT, 0, st>>>(q, k, v, out, lse, lse2, dout, delta, dq, s, nq, NoDocs{}); };
+        if (qstr) gen ? go(dq_kernel<D, true, false, true, WD>) : go(dq_kernel<D, false, false, true, WD>);
+        else gen ? go(dq_kernel<D, true, false, false, WD>) : go(dq_kernel<D, false, false, false, WD>);
+        return hipGetLastError();
+    };
+    if (free_order && !joint) {
+        if ((e = launch_dq(std::true_type{})) != hipSuccess) return e;
+    } else if (stages & UNIGIST_BWD_DELTA) {
         constexpr int rows_per_blk = NT / (D / 8);
         const long nrows = (long)s.B * s.Hq * s.L;
         delta_kernel<D><<<dim3((unsigned)((nrows + rows_per_blk - 1) / rows_per_blk)), NT, 0, st>>>(
@@ -491,13 +521,7 @@ hipError_t bwd_launch(const bf16_t* q, const bf16_t* k, const bf16_t* v, const b
         else dkdv_kernel<D, false, false, false><<<grid, NT, 0, st>>>(q, k, v, lse2, dout, delta, dk, dv, part, comp, s, pl, NoDocs{});
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    if (!(stages & UNIGIST_BWD_DQ)) return hipSuccess;
-    if (qstr) {
-        if (gen) dq_kernel<D, true, false, true><<<dim3((unsigned)nblk), NT, 0, st>>>(q, k, v, lse2, dout, delta, dq, s, nq, NoDocs{});
-        else dq_kernel<D, false, false, true><<<dim3((unsigned)nblk), NT, 0, st>>>(q, k, v, lse2, dout, delta, dq, s, nq, NoDocs{});
-    } else if (gen) dq_kernel<D, true, false><<<dim3((unsigned)nblk), NT, 0, st>>>(q, k, v, lse2, dout, delta, dq, s, nq, NoDocs{});
-    else dq_kernel<D, false, false><<<dim3((unsigned)nblk), NT, 0, st>>>(q, k, v, lse2, dout, delta, dq, s, nq, NoDocs{});
-    return hipGetLastError();
+    return (stages & UNIGIST_BWD_DQ) && !free_order ? launch_dq(std::false_type{}) : hipSuccess;
 }
 
 // ---- packed documents: the non-empty documents, longest first (their long tiles should not start last), and
@@ -563,7 +587,8 @@ hipError_t bwd_launch_pack(const bf16_t* q, const bf16_t* k, const bf16_t* v, co
     float* part = (float*)(ws + pp.off_part);
     float* comp = (float*)(ws + pp.off_comp);
     hipError_t e;
-    {  // delta and lse2 of every row of the pack (a row's delta does not depend on its document)
+    const bool free_order = !dq_on_its_inputs(q, dout, out, lse, dq, s);
+    if (!free_order) {  // delta and lse2 of every row of the pack (a row's delta does not depend on its document)
         constexpr int rows_per_blk = NT / (D / 8);
         const long nrows = (long)s.Hq * s.L;
         delta_kernel<D><<<dim3((unsigned)((nrows + rows_per_blk - 1) / rows_per_blk)), NT, 0, st>>>(
@@ -604,6 +629,16 @@ hipError_t bwd_launch_pack(const bf16_t* q, const bf16_t* k, const bf16_t* v, co
     BwdPlan none = {};
     none.segc = pp.segc;
     const bool gen = s.S != 0 || s.umode != 0, qstr = s.q_rs != 0;
+    auto launch_dq = [&](auto with_delta) {
+        constexpr bool WD = decltype(with_delta)::value;
+        return for_chunks([&](int len) { return (long)row_units(len, s.Hq / s.Hkv).per * s.Hkv; },
+                          [&](const DocTab& t, unsigned nblk) {
+                              auto go = [&](auto kern) { kern<<<dim3(nblk), NT, 0, st>>>(q, k, v, out, lse, lse2, dout, delta, dq, s, 0, t); };
+                              if (qstr) gen ? go(dq_kernel<D, true, true, true, WD>) : go(dq_kernel<D, false, true, true, WD>);
+                              else gen ? go(dq_kernel<D, true, true, false, WD>) : go(dq_kernel<D, false, true, false, WD>);
+                          });
+    };
+    if (free_order && (e = launch_dq(std::true_type{})) != hipSuccess) return e;
     e = for_chunks([&](int len) { const BwdPlan pl = counts(len); return (long)pl.slot0[pl.nseg] * s.Hkv; },
                    [&](const DocTab& t, unsigned nblk) {
                        auto go = [&](auto kern) { kern<<<dim3(nblk), NT, 0, st>>>(q, k, v, lse2, dout, delta, dk, dv, part, comp, s, none, t); };
@@ -625,12 +660,7 @@ hipError_t bwd_launch_pack(const bf16_t* q, const bf16_t* k, const bf16_t* v, co
                        else gen ? go(dkdv_kernel<D, false, true, true>) : go(dkdv_kernel<D, false, false, true>);
                    });
     if (e != hipSuccess) return e;
-    return for_chunks([&](int len) { return (long)row_units(len, s.Hq / s.Hkv).per * s.Hkv; },
-                      [&](const DocTab& t, unsigned nblk) {
-                          auto go = [&](auto kern) { kern<<<dim3(nblk), NT, 0, st>>>(q, k, v, lse2, dout, delta, dq, s, 0, t); };
-                          if (qstr) gen ? go(dq_kernel<D, true, true, true>) : go(dq_kernel<D, false, true, true>);
-                          else gen ? go(dq_kernel<D, true, true>) : go(dq_kernel<D, false, true>);
-                      });
+    return free_order ? hipSuccess : launch_dq(std::false_type{});
 }
 
 }  // namespace

@@ -25,7 +25,7 @@ SHAPES = [
     (2, 4, 2, 901, 64, 1, 16, 3, 1),
     (1, 1, 1, 1024, 64, 4, 128, 0, 0),
     (3, 16, 16, 3001, 64, 2, 70, 0, 0),     # segments of 32 chunks where separate launches take 16
-    (1, 8, 8, 4100, 128, 4, 500, 3, 0),     # 8 and 2
+    (1, 8, 8, 4100, 128, 4, 500, 3, 0),     # 16 and 4
 ]
 LARGE = [(1, 32, 8, 12288, 128, 8, 256, 0, 0), (1, 32, 8, 12289, 128, 8, 256, 0, 0),  # 3072 workgroups of dQ, and more
          (1, 16, 16, 18432, 64, 16, 200, 0, 0), (1, 16, 16, 18561, 64, 16, 200, 0, 0)]  # 2304, 2336: D = 64, joint
@@ -62,8 +62,9 @@ def test_whole_against_stages(B, Hq, Hkv, L, D, r, W, S, mode, strided):
 
 
 @pytest.mark.parametrize("strided", [False, True])
-@pytest.mark.parametrize("onto", ["q", "dout"])
-@pytest.mark.parametrize("B,Hq,Hkv,L,D,r,W", [(2, 32, 8, 2047, 128, 4, 128), (1, 7, 1, 1283, 64, 2, 33)])
+@pytest.mark.parametrize("onto", ["q", "dout", "out"])
+@pytest.mark.parametrize("B,Hq,Hkv,L,D,r,W", [(2, 32, 8, 2047, 128, 4, 128), (1, 7, 1, 1283, 64, 2, 33),
+                                              (8, 32, 8, 1601, 128, 8, 100)])  # 3264 workgroups of dQ: beyond the joint line
 def test_dq_in_place_of_its_inputs(B, Hq, Hkv, L, D, r, W, onto, strided):
     # every row of q and dout is read by the two dK/dV phases as well, so dq has to be written behind them
     lay = (lambda t: t.transpose(1, 2).contiguous().transpose(1, 2)) if strided else (lambda t: t.contiguous())
@@ -73,7 +74,7 @@ def test_dq_in_place_of_its_inputs(B, Hq, Hkv, L, D, r, W, onto, strided):
     want = u.attn_bwd(q, k, v, out, lse, do, r, W)
     ws = torch.empty(u.unigist_attn_bwd_workspace(B, Hq, Hkv, L, D, r, W, u.UNIGIST_BF16), device="cuda", dtype=torch.uint8)
     dk, dv = torch.empty_like(k), torch.empty_like(v)
-    dq = q if onto == "q" else do
+    dq = {"q": q, "dout": do, "out": out}[onto]
     st = q.stride() if strided else (Hq * L * D, L * D, D)
     assert u.unigist_attn_bwd_strided(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(), do.data_ptr(),
                                       dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), B, Hq, Hkv, L, D, r, W, 0, 0, *st[:3],
@@ -81,6 +82,28 @@ def test_dq_in_place_of_its_inputs(B, Hq, Hkv, L, D, r, W, onto, strided):
     assert torch.equal(dq, want[0])
     # the same sums, put together in separate launches (as in test_whole_against_stages)
     for a, b in zip((dk, dv), want[1:]):
+        assert (a.float() - b.float()).norm() <= 3e-4 * b.float().norm()
+
+
+@pytest.mark.parametrize("onto", [None, "q", "dout", "out"])
+def test_packed_dq_in_place_of_its_inputs(onto):
+    # without overlap dQ runs first and computes delta itself; with it the delta pass runs first and dQ last
+    Hq, Hkv, D, r, W, cu = 8, 2, 96, 4, 77, [0, 700, 701, 1500, 2111]
+    q, k, v, do = (t[0].cuda() for t in synth.attn_inputs(1, Hq, Hkv, cu[-1], D, seed=3))
+    out, lse = u.attn_fwd_varlen(q, k, v, r, W, cu)
+    parts = []
+    for a, b in zip(cu, cu[1:]):
+        one = [t[None, :, a:b].contiguous() for t in (q, k, v, out, lse, do)]
+        parts.append(u.attn_bwd(*one, r, W))
+    want = [torch.cat(t, 2)[0] for t in zip(*parts)]
+    ws = torch.empty(u.unigist_attn_bwd_varlen_workspace(Hq, Hkv, cu[-1], D, r, W, cu, u.UNIGIST_BF16), device="cuda", dtype=torch.uint8)
+    dk, dv = torch.empty_like(k), torch.empty_like(v)
+    dq = {"q": q, "dout": do, "out": out}.get(onto, torch.empty_like(q))
+    assert u.unigist_attn_bwd_varlen(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(), do.data_ptr(),
+                                     dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), Hq, Hkv, cu[-1], D, r, W, cu, u.UNIGIST_BF16,
+                                     ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream) == 0
+    assert torch.equal(dq, want[0])
+    for a, b in zip((dk, dv), want[1:]):  # the same sums, grouped by the segments of the pack (as in test_whole_against_stages)
         assert (a.float() - b.float()).norm() <= 3e-4 * b.float().norm()
 
 
