@@ -221,7 +221,7 @@ extern "C" unigist_status unigist_attn_bwd(const void* q, const void* k, const v
 extern "C" size_t unigist_decode_workspace(int B, int Hq, int Hkv, int Lk_max, int D, unigist_dtype dt) {
     if (B < 1 || Hq < 1 || Hkv < 1 || Lk_max < 1 || Hq % Hkv != 0) return 0;
     if (!head_dim_ok(D, dt) || (dt != UNIGIST_BF16 && dt != UNIGIST_F32)) return 0;
-    return decode_split_bytes(B, Hq, decode_num_splits(B, Hq, Hkv, Lk_max, D, dt, SIZE_MAX), D);
+    return decode_split_bytes(B, Hq, decode_num_splits(B, Hq, Hkv, Lk_max, D, dt, SIZE_MAX, true), D);
 }
 
 extern "C" unigist_status unigist_decode(const void* q, const void* kcache, const void* vcache, void* out,

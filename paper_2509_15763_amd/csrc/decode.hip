@@ -18,6 +18,7 @@
 //   groups of a workgroup are merged through LDS and the slice's partial result goes
 //   to the workspace as (m, l, acc[D]).  A second kernel merges the slices:
 //   lse = ln sum_s l_s e^{m_s}, out = sum_s e^{m_s - m} acc_s / sum_s e^{m_s - m} l_s.
+#include <algorithm>
 #include <type_traits>
 
 #include "mfma_common.h"
@@ -349,13 +350,22 @@ hipError_t launch_combine(const float* ws, T* out, float* lse, int BH, int nspli
 //   O^T += V^T P^T  P in place as the B operand (slot 8 g4 + 4 kb + i = key 16 kb + 4 g4 + i); V^T through LDS: the
 //                 wave widens its 32 V rows to bf16 into a private swizzled tile and reads it back transposed.
 // The four waves' partial (m, l, O) are merged through LDS and written to the workspace like the other kernels'.
-// Four workgroups per CU for the 8-bit cache (at D = 128 the compiler's own choice, 130 VGPRs, allows three; a wave has half
-// the bytes in flight that it has for bf16): 64 ragged sequences of up to 3000 keys 54.5 -> 51.9 us, 128 x 1500 at D = 96
-// and 16/4 heads 38.1 -> 35.9; 16 ragged of up to 9001, 64 x 17408 and all launches of few workgroups unchanged.  For a
-// bf16 cache none is asked for: three, which the registers allow without asking, cost 2 to 4 % of a launch of few slices (us
-// with / without: 4 x 1500 keys 12.9 / 12.5, 8000 14.6 / 14.0) and 1.5 % of 64 x 17408 (750 / 738).
-template <int D, bool E4M3, bool SEG64>
-__global__ __launch_bounds__(kThreads, E4M3 ? 4 : 1) void decode_split_mfma_kernel(const bf16_t* __restrict__ q,
+// AHEAD: the loads of the next 128 keys are issued before the work on these, into registers of their own.  Where one or two
+// workgroups share a CU, an iteration is a round trip to memory and then the work, one after the other.  Slice kernel +
+// combine, us, without / with: 8 x 12000 ragged 58.6 / 54.4, 16 x 9001 ragged E4M3 43.5 / 41.5, 13 x 5437 at D = 64 35.3 /
+// 30.7, 12 x 30000 ragged E4M3, 8/1 heads, D = 64 20.8 / 16.6, 16 x 700 ragged E4M3 11.8 / 10.6.  It is left out where
+// - a slice is one iteration (1500 keys, one sequence: 8.7 / 8.8), and
+// - more than two bf16 workgroups per CU at D = 128, where its 224 VGPRs allow two instead of three, walk slabs without
+//   lengths: 64 x 17408 745 / 773, 32 x 17408 388 / 392.  Sequences of different lengths end at different times, and there it
+//   pays all the same: 64 ragged of up to 17408 470 / 457, 128 of up to 2000 at D = 96 96 / 89 (100 x 3000, all full: 227 / 224).
+// - more than two E4M3 workgroups per CU at D = 128 (three fit instead of four) have short slices: 64 ragged of up to 3000 51.0 / 52.2;
+//   64 x 17408 386 / 378, 48 ragged x 20000 231 / 220.
+// At D = 64 four or five workgroups fit a CU with it: 64 x 17408 393 / 387, 48 ragged x 4000 49.4 / 47.6.
+// Without AHEAD four workgroups per CU are asked for with the 8-bit cache (the compiler's own choice at D = 128, 130 VGPRs,
+// allows three), none with bf16: three, which the registers allow without asking, cost 2 to 4 % of a launch of few slices (us with /
+// without: 4 x 1500 keys 12.9 / 12.5, 8000 14.6 / 14.0) and 1.5 % of 64 x 17408 (750 / 738).
+template <int D, bool E4M3, bool SEG64, bool AHEAD>
+__global__ __launch_bounds__(kThreads, E4M3 ? (AHEAD ? 3 : 4) : 1) void decode_split_mfma_kernel(const bf16_t* __restrict__ q,
                                                                          const uint8_t* __restrict__ kc,
                                                                          const uint8_t* __restrict__ vc,
                                                                          const int* __restrict__ seqlens,
@@ -422,100 +432,66 @@ __global__ __launch_bounds__(kThreads, E4M3 ? 4 : 1) void decode_split_mfma_kern
             vwoff[j][t] = row * (CH * 16) + (((NVW * (lane % LPR) + t) ^ swz16<CH>(row)) << 4);
     }
 
-    for (int base = k0 + 32 * w; base < k1; base += 128) {
-        // ---- loads: K rows base + 16 kb + r16 (clamped into the slice: clamped keys are masked below), V rows likewise
+    // ---- loads: K rows base + 16 kb + r16 (clamped into the slice: clamped keys are masked below), V rows likewise
+    struct Tile {
         u32x4 kw[2][NKL], vw[NLV];
+    };
+    auto load = [&](Tile& x, int base) __attribute__((always_inline)) {
 #pragma unroll
         for (int kb2 = 0; kb2 < 2; ++kb2) {
             const int row = min(base + 16 * kb2 + r16, k1 - 1);
 #pragma unroll
             for (int t = 0; t < NKL; ++t) {
                 const int o = SEG64 ? 64 * t + 16 * g4 : BPL * EB * g4 + 16 * t;  // a piece the rows do not have: the first one (its q is zero)
-                kw[kb2][t] = *(const u32x4*)(kb + (size_t)row * row_bytes + (o < row_bytes ? o : 0));
+                x.kw[kb2][t] = *(const u32x4*)(kb + (size_t)row * row_bytes + (o < row_bytes ? o : 0));
             }
         }
 #pragma unroll
         for (int j = 0; j < NLV; ++j) {
             const int row = min(base + (64 / LPR) * j + lane / LPR, k1 - 1);
             const int o = 16 * (lane % LPR);
-            vw[j] = *(const u32x4*)(vb + (size_t)row * row_bytes + (o < row_bytes ? o : 0));
+            x.vw[j] = *(const u32x4*)(vb + (size_t)row * row_bytes + (o < row_bytes ? o : 0));
         }
-        // ---- S^T = K Q^T
-        f32x4 sa[2];
+    };
+    auto step = [&](const Tile& x, int base) __attribute__((always_inline)) {
+        const auto& kw = x.kw;
+        const auto& vw = x.vw;
+#include "decode_step.inc"
+    };
+    if constexpr (AHEAD) {
+        Tile ta, tb;
+        int base = k0 + 32 * w;
+        if (base < k1) {
+            load(ta, base);
+            for (;;) {  // the loads behind the last keys repeat the last row: a branch around them would make the compiler wait for all
+                load(tb, base + 128);
+                step(ta, base);
+                if ((base += 128) >= k1) break;
+                load(ta, base + 128);
+                step(tb, base);
+                if ((base += 128) >= k1) break;
+            }
+        }
+    } else {
+        for (int base = k0 + 32 * w; base < k1; base += 128) {
+            u32x4 kw[2][NKL], vw[NLV];
 #pragma unroll
-        for (int kb2 = 0; kb2 < 2; ++kb2) {
-            sa[kb2] = zero4();
+            for (int kb2 = 0; kb2 < 2; ++kb2) {
+                const int row = min(base + 16 * kb2 + r16, k1 - 1);
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                u32x4 kf;
-                if constexpr (E4M3) {
-                    const uint32_t w0 = kw[kb2][ks / 2][2 * (ks % 2)], w1 = kw[kb2][ks / 2][2 * (ks % 2) + 1];
-                    const f32x2 a0 = __builtin_amdgcn_cvt_pk_f32_fp8((int)w0, false), a1 = __builtin_amdgcn_cvt_pk_f32_fp8((int)w0, true);
-                    const f32x2 a2 = __builtin_amdgcn_cvt_pk_f32_fp8((int)w1, false), a3 = __builtin_amdgcn_cvt_pk_f32_fp8((int)w1, true);
-                    kf[0] = pack_bf16x2(a0[0], a0[1]);
-                    kf[1] = pack_bf16x2(a1[0], a1[1]);
-                    kf[2] = pack_bf16x2(a2[0], a2[1]);
-                    kf[3] = pack_bf16x2(a3[0], a3[1]);
-                } else {
-                    kf = kw[kb2][ks];
+                for (int t = 0; t < NKL; ++t) {
+                    const int o = SEG64 ? 64 * t + 16 * g4 : BPL * EB * g4 + 16 * t;
+                    kw[kb2][t] = *(const u32x4*)(kb + (size_t)row * row_bytes + (o < row_bytes ? o : 0));
                 }
-                sa[kb2] = mfma16(__builtin_bit_cast(bf16x8, kf), qf[ks], sa[kb2]);
             }
+#pragma unroll
+            for (int j = 0; j < NLV; ++j) {
+                const int row = min(base + (64 / LPR) * j + lane / LPR, k1 - 1);
+                const int o = 16 * (lane % LPR);
+                vw[j] = *(const u32x4*)(vb + (size_t)row * row_bytes + (o < row_bytes ? o : 0));
+            }
+#include "decode_step.inc"
         }
-        // ---- V rows (widened to bf16) into the wave's tile
-#pragma unroll
-        for (int j = 0; j < NLV; ++j) {
-            if constexpr (!E4M3) {
-                *(u32x4*)(vt + vwoff[j][0]) = vw[j];
-                continue;
-            }
-#pragma unroll
-            for (int t = 0; t < NVW; ++t) {
-                const uint32_t w0 = vw[j][2 * t], w1 = vw[j][2 * t + 1];
-                const f32x2 a0 = __builtin_amdgcn_cvt_pk_f32_fp8((int)w0, false), a1 = __builtin_amdgcn_cvt_pk_f32_fp8((int)w0, true);
-                const f32x2 a2 = __builtin_amdgcn_cvt_pk_f32_fp8((int)w1, false), a3 = __builtin_amdgcn_cvt_pk_f32_fp8((int)w1, true);
-                u32x4 x;
-                x[0] = pack_bf16x2(a0[0], a0[1]);
-                x[1] = pack_bf16x2(a1[0], a1[1]);
-                x[2] = pack_bf16x2(a2[0], a2[1]);
-                x[3] = pack_bf16x2(a3[0], a3[1]);
-                *(u32x4*)(vt + vwoff[j][t]) = x;
-            }
-        }
-        // ---- softmax over the 32 keys; keys past the slice are masked
-#pragma unroll
-        for (int kb2 = 0; kb2 < 2; ++kb2)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (base + 16 * kb2 + 4 * g4 + i >= k1) sa[kb2][i] = -INFINITY;
-        float mx = fmaxf(fmaxf(fmaxf(sa[0][0], sa[0][1]), fmaxf(sa[0][2], sa[0][3])),
-                         fmaxf(fmaxf(sa[1][0], sa[1][1]), fmaxf(sa[1][2], sa[1][3])));
-        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-        if ((mx - m) * c > kSlack || m == -INFINITY) {  // same decision on the four lanes of a head (same mx, same m)
-            if (mx > m) {
-                const float alpha = __builtin_amdgcn_exp2f((m - mx) * c);  // m = -inf gives 0
-                l *= alpha;
-#pragma unroll
-                for (int db = 0; db < DB; ++db)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) o[db][i] *= alpha;
-                m = mx;
-            }
-        }
-        const float mc = (m == -INFINITY ? 0.f : m) * c;
-        float p[8];
-#pragma unroll
-        for (int kb2 = 0; kb2 < 2; ++kb2)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) p[4 * kb2 + i] = __builtin_amdgcn_exp2f(fmaf(sa[kb2][i], c, -mc));
-        l += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
-        u32x4 pk;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) pk[t] = pack_bf16x2(p[2 * t], p[2 * t + 1]);
-        // ---- O^T += V^T P^T (the tile writes above are this wave's own: LDS operations of a wave complete in order)
-#pragma unroll
-        for (int db = 0; db < DB; ++db) o[db] = mfma16(tr16_frag16<CH>(vt + toff[db], 0), __builtin_bit_cast(bf16x8, pk), o[db]);
     }
 
     // ---- merge the four waves (the tiles are dead: their memory takes the partials)
@@ -567,7 +543,7 @@ hipError_t decode_launch(const void* q, const void* kc, const void* vc, const fl
                          size_t room, hipStream_t st) {
     constexpr int U = kUnroll;
     constexpr unigist_dtype dt = std::is_same<TQ, float>::value ? UNIGIST_F32 : UNIGIST_BF16;
-    const int nsplit = decode_num_splits(B, Hq, Hkv, Lk, Dt, dt, room);
+    const int nsplit = decode_num_splits(B, Hq, Hkv, Lk, Dt, dt, room, seqlens != nullptr);
     const float scale = 1.0f / sqrtf((float)Dt);
     if (decode_grouped(Hq, Hkv, dt) && Hq / Hkv == 4) {
         dim3 grid(nsplit, Hkv, B);
@@ -628,10 +604,24 @@ int best_splits(long units, int Lk, int min_keys) {
 
 int decode_least_splits(int B, int Hq, int Hkv, int Lk, unigist_dtype dt) { return best_splits(decode_units(B, Hq, Hkv, dt), Lk, 256); }
 
-int decode_num_splits(int B, int Hq, int Hkv, int Lk, int D, unigist_dtype dt, size_t room) {
+int decode_base_splits(int B, int Hq, int Hkv, int Lk, unigist_dtype dt) {
     const long units = decode_units(B, Hq, Hkv, dt);
-    const int n = best_splits(units, Lk, units <= 64 ? 128 : 256);  // at least as many as with 256 keys
-    return decode_split_bytes(B, Hq, n, D) <= room ? n : decode_least_splits(B, Hq, Hkv, Lk, dt);
+    return best_splits(units, Lk, units <= 64 ? 128 : 256);  // at least as many as with 256 keys
+}
+
+// Long slabs of bf16 (from 8192 rows) with lengths take up to eight slices, so that the workgroups of the longest sequences end
+// less late, up to 16 rounds of workgroups (slices by the rule above / 8, us: 24 x 20000 206 / 199, 48 x 17408 339 / 325, 64 x 9000 245
+// / 229, 64 x 17408 458 / 427, 120 x 30000 with 8/1 heads 216 / 191, 8 x 12000 54.5 / 50.8; 128 x 10000 with 1 / 4 / 6 slices 508 /
+// 480 / 494).  Shorter ones do not gain (128 x 5000 342 / 350 with two), nor do E4M3 codes, half the bytes (48 ragged x 20000
+// 220 / 202, but 64 full x 17408 377 / 392), nor slabs without lengths (64 x 17408 with four 744 / 745).
+int decode_num_splits(int B, int Hq, int Hkv, int Lk, int D, unigist_dtype dt, size_t room, bool lengths) {
+    const long units = decode_units(B, Hq, Hkv, dt);
+    const int base = decode_base_splits(B, Hq, Hkv, Lk, dt);
+    if (lengths && dt == UNIGIST_BF16 && decode_grouped(Hq, Hkv, dt) && Lk >= 8192 && units >= 64) {
+        const int n = (int)std::min<long>(8, 4096 / units);
+        if (n > base && decode_split_bytes(B, Hq, n, D) <= room) return n;
+    }
+    return decode_split_bytes(B, Hq, base, D) <= room ? base : decode_least_splits(B, Hq, Hkv, Lk, dt);
 }
 
 namespace {
@@ -645,7 +635,7 @@ hipError_t decode_bf16q(const void* q, const void* kc, const void* vc, const flo
         return D <= 64 ? decode_launch<bf16_t, T, 64>(q, kc, vc, k_scale, v_scale, out, lse, B, Hq, Hkv, Lk, seqlens, D, ws, room, st)
                        : decode_launch<bf16_t, T, 128>(q, kc, vc, k_scale, v_scale, out, lse, B, Hq, Hkv, Lk, seqlens, D, ws, room, st);
     }
-    const int nsplit = decode_num_splits(B, Hq, Hkv, Lk, D, UNIGIST_BF16, room);
+    const int nsplit = decode_num_splits(B, Hq, Hkv, Lk, D, E4M3 ? UNIGIST_E4M3 : UNIGIST_BF16, room, seqlens != nullptr);
     const float scale = 1.0f / sqrtf((float)D);
     const dim3 grid(nsplit, Hkv, B);
     const bool seg64 = D == padded_head_dim(D);
@@ -653,8 +643,14 @@ hipError_t decode_bf16q(const void* q, const void* kc, const void* vc, const flo
         kern<<<grid, kThreads, 0, st>>>((const bf16_t*)q, (const uint8_t*)kc, (const uint8_t*)vc, seqlens, k_scale, v_scale, ws, Hq,
                                         Hkv, Lk, nsplit, scale, D);
     };
-    if (D <= 64) seg64 ? go(decode_split_mfma_kernel<64, E4M3, !E4M3>) : go(decode_split_mfma_kernel<64, E4M3, false>);
-    else seg64 ? go(decode_split_mfma_kernel<128, E4M3, !E4M3>) : go(decode_split_mfma_kernel<128, E4M3, false>);
+    const int slice = (Lk + nsplit - 1) / nsplit;  // see AHEAD at the kernel
+    const bool ahead = slice > 128 && (D <= 64 || (long)B * Hkv * nsplit <= 512 || (E4M3 ? slice >= 4096 : seqlens != nullptr));
+    auto pick = [&](auto ah) {
+        constexpr bool A = decltype(ah)::value;
+        if (D <= 64) seg64 ? go(decode_split_mfma_kernel<64, E4M3, !E4M3, A>) : go(decode_split_mfma_kernel<64, E4M3, false, A>);
+        else seg64 ? go(decode_split_mfma_kernel<128, E4M3, !E4M3, A>) : go(decode_split_mfma_kernel<128, E4M3, false, A>);
+    };
+    ahead ? pick(std::true_type{}) : pick(std::false_type{});
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return D <= 64 ? launch_combine<bf16_t, 64>(ws, (bf16_t*)out, lse, B * Hq, nsplit, D, st)

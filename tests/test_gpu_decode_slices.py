@@ -49,6 +49,34 @@ def test_lengths(G, D, Lk):
         assert (out.cpu().double() - o).abs().max() <= 2e-2 and (lse.cpu().double() - l).abs().max() <= 1e-4
 
 
+@pytest.mark.parametrize("B,D", [(16, 64), (40, 32), (16, 128)])  # 64 and 160 (sequence, kv head) pairs
+def test_long_slabs(B, D):
+    # from 8192 rows on: eight slices a sequence with lengths, fewer without and in less room; lengths around the kernel's
+    # iterations, of which it keeps one in flight ahead of the one it works on
+    G, Hkv, Lk = 2, 4, 8200
+    gen = torch.Generator().manual_seed(B + D)
+    q = torch.randn(B, G * Hkv, D, generator=gen).bfloat16()
+    k, v = (torch.randn(B, Hkv, Lk, D, generator=gen).bfloat16() for _ in range(2))
+    n = [Lk, 0, 1, 128, 1024, 1025, 1152, 1153, 1280, 2048, 2049, 4097, 8191, 33, 1023, 3000] + [Lk] * (B - 16)
+    bytes_of = lambda slices: -(-B * G * Hkv * slices * ((64 if D <= 64 else 128) + 2) * 4 // 256) * 256
+    full = u.unigist_decode_workspace(B, G * Hkv, Hkv, Lk, D, u.UNIGIST_BF16)
+    assert full == bytes_of(8)
+    qd, kd, vd = q.cuda(), k.cuda(), v.cuda()
+    one = torch.ones(Hkv).cuda()
+    k8, v8 = (u.quantize_e4m3(t, one) for t in (kd, vd))
+    wide = lambda c: c.cpu().view(torch.float8_e4m3fn).float()
+    for lens in (n, None):
+        sl = None if lens is None else torch.tensor(lens, dtype=torch.int32).cuda()
+        o, l = _exact(q, k, v, lens or [Lk] * B)
+        o8, l8 = _exact(q, wide(k8), wide(v8), lens or [Lk] * B)
+        for size in (full, bytes_of(4)):
+            ws = torch.full((size,), 255, dtype=torch.uint8).cuda()
+            for (out, lse), (a, b) in (((u.decode(qd, kd, vd, sl, workspace=ws)), (o, l)), ((u.decode_e4m3(qd, k8, v8, one, one, sl, workspace=ws)), (o8, l8))):
+                assert (out.cpu().double() - a).abs().max() <= 2e-2  # as in test_lengths
+                live = torch.isfinite(b)
+                assert torch.equal(torch.isfinite(lse.cpu()), live) and (lse.cpu().double()[live] - b[live]).abs().max() <= 1e-4
+
+
 @pytest.mark.parametrize("Lk,slices", [(500, 4), (1000, 8)])  # either combine kernel
 @pytest.mark.parametrize("dt", [torch.bfloat16, torch.float32, "e4m3"])
 @pytest.mark.parametrize("G", [4, 17])  # 17: the vector kernel
