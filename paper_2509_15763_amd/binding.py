@@ -235,8 +235,16 @@ def _head_rows(t: torch.Tensor, lead: int) -> int:
     return rows
 
 
+# The current stream's handle.  torch.cuda.current_stream() builds a Stream object around it, 2.7 us in a loop and 14 us where the
+# autograd thread and the main thread take turns (9 % of a forward and backward over 1K tokens, twice); the handle alone takes 0.1.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None or _device is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 # ---------------------------------------------------------------- raw ABI, same names

@@ -116,21 +116,21 @@ BwdPlan sized_plan(const AttnShape& s, int segc) {
 //   12000, 16/16, r 2, W 70                 968  / 962  / 968  / 826+ / 758*
 //   20000, 8/1, D 64, W 1000                375  / 374  / 374+ / 373* / 452
 // Sizes are asked for and refused by pick_segc, whose segments are never longer.
-int pick_joint_segc(const AttnShape& s, int n_dq_wgs) {
+int pick_joint_segc(const AttnShape& s, long steps, int n_dq_wgs) {
     const long G = s.Hq / s.Hkv, NP = (long)s.B * s.Hkv, slots = 256 * (s.D <= 64 ? 3 : 2);
     const long reach = s.umode ? (s.W + 1L) * s.rp1 : s.W;  // rows that have a key in their window
-    const double gist = (double)launch_steps(s) * G;
+    const double gist = (double)steps * G;
     const double window = (double)((s.L + BNK - 1) / BNK) * NP * G * (std::min((long)s.L, reach + BNK) / MQ);
     const double dq = (double)n_dq_wgs * (std::min((long)s.L, reach + kWaveRows) + s.L / s.rp1 / 2) / kDqBn;
     const double even = (gist + window + 0.55 * dq) / slots;
-    int segc = pick_segc(launch_steps(s));
+    int segc = pick_segc(steps);
     while (segc < 32 && 2 * segc * G <= 1.6 * even) segc *= 2;
     return segc;
 }
 
 // the plan of a launch whose workspace has `room` bytes: segments of segc chunks, or of the first doubling that fits
-BwdPlan make_plan(const AttnShape& s, size_t room, int segc) {
-    const int longest = std::max(segc, roomiest_segc(launch_steps(s)));
+BwdPlan make_plan(const AttnShape& s, long steps, size_t room, int segc) {
+    const int longest = std::max(segc, roomiest_segc(steps));
     BwdPlan p = sized_plan(s, segc);
     while (p.total > room && segc < longest) p = sized_plan(s, segc *= 2);
     plan_order(s, p);
@@ -462,7 +462,8 @@ hipError_t bwd_launch(const bf16_t* q, const bf16_t* k, const bf16_t* v, const b
     if (nblk > 0x7fffffffL) return hipErrorInvalidValue;
     const bool free_order = stages == UNIGIST_BWD_ALL && !dq_on_its_inputs(q, dout, out, lse, dq, s);
     const bool joint = free_order && run_jointly<D>(nblk);
-    const BwdPlan pl = make_plan(s, room, joint ? pick_joint_segc(s, (int)nblk) : pick_segc(launch_steps(s)));
+    const long steps = launch_steps(s);
+    const BwdPlan pl = make_plan(s, steps, room, joint ? pick_joint_segc(s, steps, (int)nblk) : pick_segc(steps));
     const bool gen = s.S != 0 || s.umode != 0;
     const bool qstr = s.q_rs != 0;  // q, out, dout, dq with the caller's explicit strides
     float* delta = (float*)ws;
@@ -668,7 +669,10 @@ hipError_t bwd_launch_pack(const bf16_t* q, const bf16_t* k, const bf16_t* v, co
 size_t bwd_mfma_workspace(const AttnShape& s) { return sized_plan(s, pick_segc(launch_steps(s))).total; }
 size_t bwd_mfma_least_workspace(const AttnShape& s) { return sized_plan(s, roomiest_segc(launch_steps(s))).total; }
 
-BwdPlan make_bwd_plan(const AttnShape& s) { return make_plan(s, SIZE_MAX, pick_segc(launch_steps(s))); }
+BwdPlan make_bwd_plan(const AttnShape& s) {
+    const long steps = launch_steps(s);
+    return make_plan(s, steps, SIZE_MAX, pick_segc(steps));
+}
 
 size_t bwd_mfma_pack_workspace(const AttnShape& s, const int* cu, int ndocs) { return make_pack_plan(s, cu, ndocs, SIZE_MAX).total; }
 size_t bwd_mfma_pack_least_workspace(const AttnShape& s, const int* cu, int ndocs) { return make_pack_plan(s, cu, ndocs, 0).total; }
