@@ -261,23 +261,6 @@ __global__ __launch_bounds__(NT, 2) void dkdv_kernel(const bf16_t* __restrict__ 
 #include "dkdv_body.inc"
 }
 
-// The same inside the joint launch (below), n = the workgroup's number in the phase: the partials and the window phase's
-// sums of the gist rows (keep) stay in fp32 for the reduction that follows.
-template <int D, bool GIST, bool GEN, bool QSTR>
-__device__ __forceinline__ void dkdv_part(DkdvSmem<D>& sm, int n, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
-                                          const bf16_t* __restrict__ v, const float* __restrict__ lse2,
-                                          const bf16_t* __restrict__ dout, const float* __restrict__ delta,
-                                          bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, float* __restrict__ part,
-                                          float* __restrict__ keep, AttnShape s, const BwdPlan& pl) {
-    constexpr bool JOINT = true, PACK = false;
-    const float* comp = nullptr;
-    if constexpr (!GEN) {
-        s.S = 0;
-        s.umode = 0;
-    }
-#include "dkdv_body.inc"
-}
-
 // ------------------------------------------------------------------ 3. sum the segments of each gist tile
 // FINISH = false: the sums go to comp, and the window phase adds them to its own.  FINISH = true (after the joint
 // launch): comp holds the window phase's sums of the gist rows; they are added and the rows of dk and dv written.
@@ -388,20 +371,6 @@ __global__ __launch_bounds__(NT, 2) void dq_kernel(const bf16_t* __restrict__ q,
     }
 #include "dq_body.inc"
 }
-template <int D, bool GEN, bool QSTR>
-__device__ __forceinline__ void dq_part(DqSmem<D>& sm, int n, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
-                                        const bf16_t* __restrict__ v, float* lse2,
-                                        const bf16_t* __restrict__ dout, float* delta,
-                                        bf16_t* __restrict__ dq, AttnShape s, int nq) {
-    constexpr bool PACK = false, WITH_DELTA = false;
-    const bf16_t* out = nullptr;
-    const float* lse = nullptr;
-    if constexpr (!GEN) {
-        s.S = 0;
-        s.umode = 0;
-    }
-#include "dq_body.inc"
-}
 
 // ------------------------------------------------------------------ 2., 4. and 5. in one launch
 // The three heavy parts of a whole backward need nothing from each other (the window phase leaves its sums of the gist
@@ -409,19 +378,18 @@ __device__ __forceinline__ void dq_part(DqSmem<D>& sm, int n, const bf16_t* __re
 // phase, the next n_win the window phase, the rest dQ, whose short walks come last.  What bounds a short backward is not
 // the chip but the longest workgroup of each of its launches: alone, a phase of 2 x 2047 tokens leaves half of the 512
 // workgroup slots empty.  Phases one by one / jointly (whole backward replayed from a graph, us, 32/8 heads unless noted):
-//   1 head, 1024, D 64     36 /   19        2 x 4096, W 512, r 16  361 /  336
-//   2 x 512                91 /   58        1 x 8192           736 /  718
-//   2 x 2047              160 /  141        1 x 8192, D 64     328 /  304
-//   2048, W 1024          238 /  187        28/4 heads, 12000 1167 / 1115
-//   4096, W 512           258 /  224        4 x 8192, 16/4, D 64  617 / 600
-//   12288 (3072 dQ workgroups) 1326 / 1290  16384, D 64 (4096)  700 / 650
-// From about 16K tokens on (dQ workgroups: 4096 at D = 128) the tails it fills are short, and phases that run side by
-// side share the L2s of each other's streams: 2025 / 2054 (16384), 2500 / 2584 (2 x 16384, r 8), 6411 / 6710 (32768).
-// The line lies at six rounds of dQ workgroups: 3072 at two workgroups per CU (D = 128), 4608 at three (D = 64).
-// At D = 128 all four instantiations spill 4 to 8 VGPRs (16 to 20 bytes of scratch per lane), unlike the kernels of the
-// phases: the window phase of the dense sliding-window one keeps a K fragment there and loads it again for every 32-row
-// block, which waits for the next chunk's direct loads as well.  The figures above are with that.
-template <int D> bool run_jointly(long n_dq) { return n_dq <= 256 * 6 * (D <= 64 ? 3 : 2); }
+//   1 head, 1024, D 64     36 /   18        1 x 8192           722 /  656
+//   2 x 512                91 /   55        28/4 heads, 12000  762 /  655
+//   2 x 2047              160 /  121        12288             1081 / 1038
+//   2048, W 1024          238 /  187        4 x 4096, W 512    840 /  815
+//   4096, W 512           258 /  201        16384             1981 / 1942
+//   2 x 9000 (4512 dQ workgroups) 1604 / 1556    4 x 5000, r 8 (5024)  770 /  741    2 x 40000, 8/1 heads, r 8 (5000) 3244 / 3063
+//   D 64: 24000, r 8 (6000) 1425 / 1392          8 x 3000 (6016) 415 / 411
+// Further on the tails it fills are short, and phases that run side by side share the L2s of each other's streams: 24000 (6000)
+// 3436 / 3454, 2 x 16384, r 8 (8192) 3030 / 3043, 32768 (8192) 6161 / 6331, at D = 64 3307 / 3381; without groups earlier: 30000,
+// 16/16 heads (3760) 2707 / 2786.  So the lines lie at ten rounds of dQ workgroups with two per CU (D = 128), eight with three (D =
+// 64), and without groups at six of either, where that was measured.
+template <int D> bool run_jointly(long n_dq, int G) { return n_dq <= 256 * (D <= 64 ? 3 * (G > 1 ? 8 : 6) : 2 * (G > 1 ? 10 : 6)); }
 
 // A dq that shares memory with q or dout, which its own workgroups have read before they write, is written too early for the
 // other phases where dQ does not run last: such calls keep the launches apart, delta first and dQ last.  So do calls whose
@@ -434,23 +402,44 @@ bool dq_on_its_inputs(const bf16_t* q, const bf16_t* dout, const bf16_t* out, co
     return meets(q, bytes) || meets(dout, bytes) || meets(out, bytes) || meets(lse, (uintptr_t)s.B * s.Hq * s.qhs * sizeof(float));
 }
 
+// The bodies are included and not called: as inlined functions of their own they left 4 to 8 VGPRs of all four instantiations
+// at D = 128 in scratch, in the window phase a K fragment that was loaded again for every 32-row block, behind the next
+// chunk's direct loads (whole backward, us, functions / includes: 2 x 2047 128 / 121, 8192 678 / 660, 2 x 9000 with 8/1 heads
+// 574 / 524, 28/4 heads at D = 96 142 / 131).  Now one does, with two (general mask, dense tensors).
 template <int D, bool GEN, bool QSTR>
 __global__ __launch_bounds__(NT, 2) void bwd_joint_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                          const bf16_t* __restrict__ v, float* __restrict__ lse2,
                                                          const bf16_t* __restrict__ dout, float* __restrict__ delta,
                                                          bf16_t* __restrict__ dq, bf16_t* __restrict__ dk,
                                                          bf16_t* __restrict__ dv, float* __restrict__ part,
-                                                         float* __restrict__ comp, AttnShape s, BwdPlan pl, int n_gist,
+                                                         float* __restrict__ comp_, AttnShape s, BwdPlan pl, int n_gist,
                                                          int n_win, int nq) {
     static_assert(sizeof(DqSmem<D>) <= sizeof(DkdvSmem<D>), "one LDS block for both");
     __shared__ __attribute__((aligned(1024))) char smem[sizeof(DkdvSmem<D>)];
-    const int n = blockIdx.x;
-    if (n < n_gist)
-        dkdv_part<D, true, GEN, QSTR>(*(DkdvSmem<D>*)smem, n, q, k, v, lse2, dout, delta, dk, dv, part, comp, s, pl);
-    else if (n < n_gist + n_win)
-        dkdv_part<D, false, GEN, QSTR>(*(DkdvSmem<D>*)smem, n - n_gist, q, k, v, lse2, dout, delta, dk, dv, part, comp, s, pl);
-    else
-        dq_part<D, GEN, QSTR>(*(DqSmem<D>*)smem, n - n_gist - n_win, q, k, v, lse2, dout, delta, dq, s, nq);
+    constexpr bool JOINT = true, PACK = false, WITH_DELTA = false;
+    const float* lse = nullptr;  // names that the bodies have for other launches
+    const bf16_t* out = nullptr;
+    float* keep = comp_;
+    const float* comp = nullptr;
+    if constexpr (!GEN) {
+        s.S = 0;
+        s.umode = 0;
+    }
+    if ((int)blockIdx.x < n_gist) {
+        constexpr bool GIST = true;
+        DkdvSmem<D>& sm = *(DkdvSmem<D>*)smem;
+        const int n = blockIdx.x;
+#include "dkdv_body.inc"
+    } else if ((int)blockIdx.x < n_gist + n_win) {
+        constexpr bool GIST = false;
+        DkdvSmem<D>& sm = *(DkdvSmem<D>*)smem;
+        const int n = blockIdx.x - n_gist;
+#include "dkdv_body.inc"
+    } else {
+        DqSmem<D>& sm = *(DqSmem<D>*)smem;
+        const int n = blockIdx.x - n_gist - n_win;
+#include "dq_body.inc"
+    }
 }
 
 template <int D>
@@ -461,7 +450,7 @@ hipError_t bwd_launch(const bf16_t* q, const bf16_t* k, const bf16_t* v, const b
     const long nblk = (long)nq * s.Hkv * s.B;
     if (nblk > 0x7fffffffL) return hipErrorInvalidValue;
     const bool free_order = stages == UNIGIST_BWD_ALL && !dq_on_its_inputs(q, dout, out, lse, dq, s);
-    const bool joint = free_order && run_jointly<D>(nblk);
+    const bool joint = free_order && run_jointly<D>(nblk, s.Hq / s.Hkv);
     const long steps = launch_steps(s);
     const BwdPlan pl = make_plan(s, steps, room, joint ? pick_joint_segc(s, steps, (int)nblk) : pick_segc(steps));
     const bool gen = s.S != 0 || s.umode != 0;

@@ -27,11 +27,13 @@ SHAPES = [
     (3, 16, 16, 3001, 64, 2, 70, 0, 0),     # segments of 32 chunks where separate launches take 16
     (1, 8, 8, 4100, 128, 4, 500, 3, 0),     # 16 and 4
 ]
+LINE = [(1, 32, 8, 20480, 128, 16, 100, 0, 0), (1, 32, 8, 20481, 128, 16, 100, 0, 0),   # 5120 workgroups of dQ, the line with groups, and more
+        (4, 32, 8, 6144, 64, 16, 64, 4, 0), (4, 32, 8, 6145, 64, 16, 64, 4, 0)]  # 6144, the line at D = 64, and more
 LARGE = [(1, 32, 8, 12288, 128, 8, 256, 0, 0), (1, 32, 8, 12289, 128, 8, 256, 0, 0),  # 3072 workgroups of dQ, and more
          (1, 16, 16, 18432, 64, 16, 200, 0, 0), (1, 16, 16, 18561, 64, 16, 200, 0, 0)]  # 2304, 2336: D = 64, joint
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,L,D,r,W,S,mode", SHAPES + LARGE)
+@pytest.mark.parametrize("B,Hq,Hkv,L,D,r,W,S,mode", SHAPES + LARGE + LINE)
 @pytest.mark.parametrize("strided", [False, True])
 def test_whole_against_stages(B, Hq, Hkv, L, D, r, W, S, mode, strided):
     q, k, v, do = synth.attn_inputs(B, Hq, Hkv, L, D, seed=L)
@@ -64,7 +66,7 @@ def test_whole_against_stages(B, Hq, Hkv, L, D, r, W, S, mode, strided):
 @pytest.mark.parametrize("strided", [False, True])
 @pytest.mark.parametrize("onto", ["q", "dout", "out"])
 @pytest.mark.parametrize("B,Hq,Hkv,L,D,r,W", [(2, 32, 8, 2047, 128, 4, 128), (1, 7, 1, 1283, 64, 2, 33),
-                                              (8, 32, 8, 1601, 128, 8, 100)])  # 3264 workgroups of dQ: beyond the joint line
+                                              (13, 32, 8, 1601, 128, 8, 100)])  # 5304 workgroups of dQ: beyond the joint line
 def test_dq_in_place_of_its_inputs(B, Hq, Hkv, L, D, r, W, onto, strided):
     # every row of q and dout is read by the two dK/dV phases as well, so dq has to be written behind them
     lay = (lambda t: t.transpose(1, 2).contiguous().transpose(1, 2)) if strided else (lambda t: t.contiguous())
@@ -130,6 +132,8 @@ def _exact_group(q, k, v, do, r, W, S, mode):
     (1, 32, 8, 18432, 64, 16, 200, 0, 0), (1, 32, 8, 18433, 64, 16, 200, 0, 0),   # 4608: at D = 64
     (1, 32, 8, 12288, 128, 4, 30, 100, 1),                                        # sinks, window in units
     (2, 28, 4, 6000, 96, 4, 300, 70, 0),
+    (1, 32, 8, 20480, 128, 8, 256, 0, 0), (1, 32, 8, 20481, 128, 8, 256, 0, 0),   # 5120: the line with groups of heads
+    (4, 32, 8, 6144, 64, 16, 200, 0, 0), (4, 32, 8, 6145, 64, 16, 200, 0, 0),     # 6144: at D = 64
 ])
 def test_both_sides_of_the_line_against_float64(B, Hq, Hkv, L, D, r, W, S, mode):
     q, k, v, do = (t.cuda() for t in synth.attn_inputs(B, Hq, Hkv, L, D, seed=L))
