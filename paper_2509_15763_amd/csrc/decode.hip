@@ -226,21 +226,22 @@ __global__ __launch_bounds__(kThreads) void decode_split_kernel(const TQ* __rest
 // weight that has underflowed to zero, so that its infinities and NaN reach the result as they would inside one slice.  A
 // sequence of zero keys (outside the contract) gets the empty sum, not NaN; columns from Dt on are not in the tensors.
 
-// Up to kFewSlices slices: a wave has them all in flight by itself.  Three more waves and their merge through LDS cost a batch
+// Up to kFewSlices slices (N = 4 or 8 of them; five to eight slices, four waves / one, us: 1000 keys 8.5 / 8.0, 4 x 4000 ragged 15.9 /
+// 15.4): a wave has them all in flight by itself.  Three more waves and their merge through LDS cost a batch
 // that the slice kernel fills by itself 2.4 us (slice kernel + combine, us, four waves / one: 128 sequences of up to 500
 // E4M3 rows at D = 64 17.7 / 15.1, 256 of 300 bf16 rows at D = 128 69.5 / 64.6, 32 of 1100 33.1 / 32.4).  With more
-// slices the second trip costs more than that (five slices 14.9 / 15.6, 24 11.8 / 14.3).
-constexpr int kFewSlices = 4;
-template <typename T, int D>
+// slices the second trip costs more than that (24 slices 11.8 / 14.3).
+constexpr int kFewSlices = 8;
+template <typename T, int D, int N>
 __global__ __launch_bounds__(64) void decode_combine_few_kernel(const float* __restrict__ ws, T* __restrict__ out,
                                                                float* __restrict__ lse, int nsplit, int Dt) {
     constexpr int C = D / 64;  // columns per lane
     const int bh = blockIdx.x, lane = threadIdx.x;
     const float* p = ws + (size_t)bh * nsplit * (D + 2);
-    f32x2 ml[kFewSlices];
-    float x[kFewSlices][C];
+    f32x2 ml[N];
+    float x[N][C];
 #pragma unroll
-    for (int s = 0; s < kFewSlices; ++s) {
+    for (int s = 0; s < N; ++s) {
         const float* ps = p + (size_t)min(s, nsplit - 1) * (D + 2);
         ml[s] = *(const f32x2*)ps;
 #pragma unroll
@@ -248,11 +249,11 @@ __global__ __launch_bounds__(64) void decode_combine_few_kernel(const float* __r
     }
     float mm = -INFINITY, ll = 0.f, a[C];
 #pragma unroll
-    for (int s = 0; s < kFewSlices; ++s) mm = fmaxf(mm, ml[s][0]);  // the last one again where there are fewer
+    for (int s = 0; s < N; ++s) mm = fmaxf(mm, ml[s][0]);  // the last one again where there are fewer
 #pragma unroll
     for (int c = 0; c < C; ++c) a[c] = 0.f;
 #pragma unroll
-    for (int s = 0; s < kFewSlices; ++s)
+    for (int s = 0; s < N; ++s)
         if (s < nsplit && ml[s][0] != -INFINITY) {
             const float w = __expf(ml[s][0] - mm);
             ll += w * ml[s][1];
@@ -323,7 +324,8 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const float* __rest
 
 template <typename T, int D>
 hipError_t launch_combine(const float* ws, T* out, float* lse, int BH, int nsplit, int Dt, hipStream_t st) {
-    if (nsplit <= kFewSlices) decode_combine_few_kernel<T, D><<<BH, 64, 0, st>>>(ws, out, lse, nsplit, Dt);
+    if (nsplit <= 4) decode_combine_few_kernel<T, D, 4><<<BH, 64, 0, st>>>(ws, out, lse, nsplit, Dt);
+    else if (nsplit <= kFewSlices) decode_combine_few_kernel<T, D, kFewSlices><<<BH, 64, 0, st>>>(ws, out, lse, nsplit, Dt);
     else decode_combine_kernel<T, D><<<BH, 256, 0, st>>>(ws, out, lse, nsplit, Dt);
     return hipGetLastError();
 }

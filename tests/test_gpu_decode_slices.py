@@ -77,7 +77,7 @@ def test_long_slabs(B, D):
                 assert torch.equal(torch.isfinite(lse.cpu()), live) and (lse.cpu().double()[live] - b[live]).abs().max() <= 1e-4
 
 
-@pytest.mark.parametrize("Lk,slices", [(500, 4), (1000, 8)])  # either combine kernel
+@pytest.mark.parametrize("Lk,slices", [(500, 4), (1000, 8), (2000, 16)])  # each combine kernel
 @pytest.mark.parametrize("dt", [torch.bfloat16, torch.float32, "e4m3"])
 @pytest.mark.parametrize("G", [4, 17])  # 17: the vector kernel
 def test_infinities_and_nan_in_a_slice_without_weight(G, dt, Lk, slices):
