@@ -366,7 +366,14 @@ hipError_t launch_combine(const float* ws, T* out, float* lse, int BH, int nspli
 // Without AHEAD four workgroups per CU are asked for with the 8-bit cache (the compiler's own choice at D = 128, 130 VGPRs,
 // allows three), none with bf16: three, which the registers allow without asking, cost 2 to 4 % of a launch of few slices (us with /
 // without: 4 x 1500 keys 12.9 / 12.5, 8000 14.6 / 14.0) and 1.5 % of 64 x 17408 (750 / 738).
-template <int D, bool E4M3, bool SEG64, bool AHEAD>
+struct DecodeOut {
+    bf16_t* out;
+    float* lse;  // may be null
+};
+// DIRECT: a launch of one slice per sequence writes the result itself, as the merge of one slice would, and has no merge (us
+// with / without: 120 keys x 8 kv heads 6.8 / 4.8, 100 x 16/4 heads x 200 at D = 64 8.8 / 6.4, 128 x 300 36.5 / 32.8, 128 x 3000
+// 274 / 268).
+template <int D, bool E4M3, bool SEG64, bool AHEAD, bool DIRECT>
 __global__ __launch_bounds__(kThreads, E4M3 ? (AHEAD ? 3 : 4) : 1) void decode_split_mfma_kernel(const bf16_t* __restrict__ q,
                                                                          const uint8_t* __restrict__ kc,
                                                                          const uint8_t* __restrict__ vc,
@@ -374,7 +381,8 @@ __global__ __launch_bounds__(kThreads, E4M3 ? (AHEAD ? 3 : 4) : 1) void decode_s
                                                                          const float* __restrict__ k_scale,
                                                                          const float* __restrict__ v_scale,
                                                                          float* __restrict__ ws, int Hq, int Hkv, int Lk,
-                                                                         int nsplit, float scale, int Dt) {
+                                                                         int nsplit, float scale, int Dt,
+                                                                         std::conditional_t<DIRECT, DecodeOut, NoDocs> res) {
     // Dt <= D: the head dimension of the tensors (rows of Dt elements in memory; a multiple of 8, of 16 for E4M3
     // codes); the K and Q columns from Dt on are zeros, the V columns from Dt on are never stored
     constexpr int KS = D / 32, DB = D / 16, CH = D / 8;  // k-steps, 16-row blocks of O^T, 16-byte chunks per bf16 row
@@ -396,7 +404,12 @@ __global__ __launch_bounds__(kThreads, E4M3 ? (AHEAD ? 3 : 4) : 1) void decode_s
     const int k0 = split * per;
     const int k1 = min(n, k0 + per);
     if (k0 >= k1) {  // a slice without keys
-        if (tid < G) *(f32x2*)(ws + (((size_t)b * Hq + hq0 + tid) * nsplit + split) * (D + 2)) = f32x2{-INFINITY, 0.f};
+        if constexpr (DIRECT) {
+            for (int i = tid; i < G * Dt; i += kThreads) res.out[((size_t)b * Hq + hq0) * Dt + i] = 0;
+            if (res.lse && tid < G) res.lse[(size_t)b * Hq + hq0 + tid] = -INFINITY;
+        } else if (tid < G) {
+            *(f32x2*)(ws + (((size_t)b * Hq + hq0 + tid) * nsplit + split) * (D + 2)) = f32x2{-INFINITY, 0.f};
+        }
         return;
     }
     const float c = scale * (E4M3 ? k_scale[hk] : 1.f) * kLog2e;  // exp(x) = exp2(x log2 e); the K scale rides along
@@ -530,6 +543,13 @@ __global__ __launch_bounds__(kThreads, E4M3 ? (AHEAD ? 3 : 4) : 1) void decode_s
                 a += wgt * po[((size_t)t * G + g) * D + d];
             }
         }
+        if constexpr (DIRECT) {
+            const size_t row = (size_t)b * Hq + hq0 + g;
+            const float mn = mm * c * ln2;
+            if (d < Dt) Elem<bf16_t>::store(res.out + row * Dt + d, mn == -INFINITY ? 0.f : a * vmul / ll);
+            if (d == 0 && res.lse) res.lse[row] = mn == -INFINITY ? -INFINITY : mn + __logf(ll);
+            continue;
+        }
         float* outp = ws + (((size_t)b * Hq + hq0 + g) * nsplit + split) * (D + 2);
         if (d == 0) {
             outp[0] = mm * c * ln2;  // the other kernels keep m in natural-log units of the scaled score
@@ -611,6 +631,19 @@ int decode_base_splits(int B, int Hq, int Hkv, int Lk, unigist_dtype dt) {
     return best_splits(units, Lk, units <= 64 ? 128 : 256);  // at least as many as with 256 keys
 }
 
+// One slice of the matrix-core kernel, which then writes the result itself, saves the merge and its launch, 2 to 4 us, and the
+// partial results.  It pays up to three iterations, and longer where the (sequence, kv head) units fill the chip by themselves, the
+// more so when they fill whole rounds of 256 workgroups (us, slices by the rule above / one; 32/8 heads: 8 units a sequence):
+//   1 x 300  7.7 /  7.2    1 x 450   7.5 /  8.6    8 x 300 9.2 / 8.4     8 x 500  9.8 / 10.5    16 x 300 11.6 / 9.7   16 x 900 17.3 / 17.9
+//   24 x 640 ragged 15.2 / 12.7    32 x 1000 29.1 / 26.9    32 x 2200 ragged 38.9 / 37.8     48 x 1500 58.5 / 59.6    48 x 2500 ragged 60 / 65
+//   64 x 600 ragged 27.3 / 21.1    64 x 4000 189 / 181      100 x 1200 ragged 66.6 / 56.4    100 x 2500 189 / 195
+//   E4M3: 32 x 500 15.0 / 10.8, 64 x 2000 56 / 50.5, 100 x 1200 ragged 38.0 / 33.5;  D = 64: 64 x 1500, 16/4 heads 24.0 / 21.0
+// Sizes are asked for and refused by the slices of the other rules.
+bool one_slice(long units, int Lk) {
+    const bool whole_rounds = (units + 255) / 256 * 256 <= units * 1.05;
+    return Lk <= 384 || (units >= 128 && Lk <= (whole_rounds ? 8 : 3) * units && Lk <= (units <= 512 ? 4096 : 2048));
+}
+
 // Long slabs of bf16 (from 8192 rows) with lengths take up to eight slices, so that the workgroups of the longest sequences end
 // less late, up to 16 rounds of workgroups (slices by the rule above / 8, us: 24 x 20000 206 / 199, 48 x 17408 339 / 325, 64 x 9000 245
 // / 229, 64 x 17408 458 / 427, 120 x 30000 with 8/1 heads 216 / 191, 8 x 12000 54.5 / 50.8; 128 x 10000 with 1 / 4 / 6 slices 508 /
@@ -637,23 +670,33 @@ hipError_t decode_bf16q(const void* q, const void* kc, const void* vc, const flo
         return D <= 64 ? decode_launch<bf16_t, T, 64>(q, kc, vc, k_scale, v_scale, out, lse, B, Hq, Hkv, Lk, seqlens, D, ws, room, st)
                        : decode_launch<bf16_t, T, 128>(q, kc, vc, k_scale, v_scale, out, lse, B, Hq, Hkv, Lk, seqlens, D, ws, room, st);
     }
-    const int nsplit = decode_num_splits(B, Hq, Hkv, Lk, D, E4M3 ? UNIGIST_E4M3 : UNIGIST_BF16, room, seqlens != nullptr);
+    const int nsplit = one_slice(decode_units(B, Hq, Hkv, UNIGIST_BF16), Lk) ? 1
+                       : decode_num_splits(B, Hq, Hkv, Lk, D, E4M3 ? UNIGIST_E4M3 : UNIGIST_BF16, room, seqlens != nullptr);
     const float scale = 1.0f / sqrtf((float)D);
     const dim3 grid(nsplit, Hkv, B);
     const bool seg64 = D == padded_head_dim(D);
-    auto go = [&](auto kern) {
-        kern<<<grid, kThreads, 0, st>>>((const bf16_t*)q, (const uint8_t*)kc, (const uint8_t*)vc, seqlens, k_scale, v_scale, ws, Hq,
-                                        Hkv, Lk, nsplit, scale, D);
-    };
     const int slice = (Lk + nsplit - 1) / nsplit;  // see AHEAD at the kernel
     const bool ahead = slice > 128 && (D <= 64 || (long)B * Hkv * nsplit <= 512 || (E4M3 ? slice >= 4096 : seqlens != nullptr));
-    auto pick = [&](auto ah) {
-        constexpr bool A = decltype(ah)::value;
-        if (D <= 64) seg64 ? go(decode_split_mfma_kernel<64, E4M3, !E4M3, A>) : go(decode_split_mfma_kernel<64, E4M3, false, A>);
-        else seg64 ? go(decode_split_mfma_kernel<128, E4M3, !E4M3, A>) : go(decode_split_mfma_kernel<128, E4M3, false, A>);
+    auto pick = [&](auto ah, auto direct, auto res) {
+        constexpr bool A = decltype(ah)::value, R = decltype(direct)::value;
+        auto go = [&](auto kern) {
+            kern<<<grid, kThreads, 0, st>>>((const bf16_t*)q, (const uint8_t*)kc, (const uint8_t*)vc, seqlens, k_scale, v_scale, ws, Hq,
+                                            Hkv, Lk, nsplit, scale, D, res);
+        };
+        if (D <= 64) seg64 ? go(decode_split_mfma_kernel<64, E4M3, !E4M3, A, R>) : go(decode_split_mfma_kernel<64, E4M3, false, A, R>);
+        else seg64 ? go(decode_split_mfma_kernel<128, E4M3, !E4M3, A, R>) : go(decode_split_mfma_kernel<128, E4M3, false, A, R>);
+        return hipGetLastError();
     };
-    ahead ? pick(std::true_type{}) : pick(std::false_type{});
-    hipError_t e = hipGetLastError();
+    const std::true_type yes;
+    const std::false_type no;
+    // an out on q's memory, which a merge writes behind all reads of q, but for the very rows that a workgroup has read itself
+    const size_t row_bytes = (size_t)B * Hq * D * 2;
+    const bool onto_q = out != q && (uintptr_t)out < (uintptr_t)q + row_bytes && (uintptr_t)q < (uintptr_t)out + row_bytes;
+    if (nsplit == 1 && !onto_q) {
+        const DecodeOut res{(bf16_t*)out, lse};
+        return ahead ? pick(yes, yes, res) : pick(no, yes, res);
+    }
+    const hipError_t e = ahead ? pick(yes, no, NoDocs{}) : pick(no, no, NoDocs{});
     if (e != hipSuccess) return e;
     return D <= 64 ? launch_combine<bf16_t, 64>(ws, (bf16_t*)out, lse, B * Hq, nsplit, D, st)
                    : launch_combine<bf16_t, 128>(ws, (bf16_t*)out, lse, B * Hq, nsplit, D, st);

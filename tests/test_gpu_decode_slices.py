@@ -77,6 +77,28 @@ def test_long_slabs(B, D):
                 assert torch.equal(torch.isfinite(lse.cpu()), live) and (lse.cpu().double()[live] - b[live]).abs().max() <= 1e-4
 
 
+@pytest.mark.parametrize("B,Hkv,Lk", [(3, 4, 384), (3, 4, 385), (16, 8, 384), (16, 8, 385), (32, 8, 2048), (32, 8, 2049), (24, 8, 576), (24, 8, 577)])
+@pytest.mark.parametrize("D", [128, 40])
+def test_one_slice_writes_the_result_itself(B, Hkv, Lk, D):
+    # both sides of the lines up to which a sequence stays one slice (three iterations; eight or three times the number of units)
+    G = 3
+    gen = torch.Generator().manual_seed(Lk + D)
+    q = torch.randn(B, G * Hkv, D, generator=gen).bfloat16()
+    k, v = (torch.randn(B, Hkv, Lk, D, generator=gen).bfloat16() for _ in range(2))
+    n = [Lk, 0, 1] + [max(1, Lk - 37 * b) for b in range(3, B)]
+    o, l = _exact(q, k, v, n)
+    live = torch.isfinite(l)
+    ws = torch.full((u.unigist_decode_workspace(B, G * Hkv, Hkv, Lk, D, u.UNIGIST_BF16),), 255, dtype=torch.uint8).cuda()
+    qd, kd, vd, sl = q.cuda(), k.cuda(), v.cuda(), torch.tensor(n, dtype=torch.int32).cuda()
+    for onto in (False, True):  # also with the result in place of the queries
+        out, lse = torch.empty_like(qd), torch.empty(B, G * Hkv, device="cuda")
+        dst = qd if onto else out
+        assert u.unigist_decode(qd.data_ptr(), kd.data_ptr(), vd.data_ptr(), dst.data_ptr(), lse.data_ptr(), B, G * Hkv, Hkv, Lk, sl.data_ptr(),
+                                D, u.UNIGIST_BF16, ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream) == 0
+        assert (dst.cpu().double() - o).abs().max() <= 2e-2  # as in test_lengths
+        assert torch.equal(torch.isfinite(lse.cpu()), live) and (lse.cpu().double()[live] - l[live]).abs().max() <= 1e-4
+
+
 @pytest.mark.parametrize("Lk,slices", [(500, 4), (1000, 8), (2000, 16)])  # each combine kernel
 @pytest.mark.parametrize("dt", [torch.bfloat16, torch.float32, "e4m3"])
 @pytest.mark.parametrize("G", [4, 17])  # 17: the vector kernel
