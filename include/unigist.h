@@ -565,6 +565,8 @@ unigist_status unigist_plan_row_tile(int L, int r, int W, int sinks, int window_
  * workgroup per (segment of seg_chunks chunks, compact tile the segment reaches: tiles 0 .. slot0[sg+1]-slot0[sg]-1
  * for segment sg) and leaves one fp32 partial [dK^T | dV^T] block per such pair in slot slot0[sg] + tile, which a
  * reduction sums over the segments in ascending order; the window phase runs one workgroup per key tile.
+ * (The plan of phases launched apart.  A whole short backward, whose phases share a launch, may take longer segments, in fewer
+ * slots of the same workspace.)
  * partial_bytes / reduced_bytes: the two parts of unigist_attn_bwd_workspace_ex that hold those blocks
  * (2 * D * 128 floats each), workspace_bytes: all of it (with two floats per query row and head in front).
  */
