@@ -6,14 +6,16 @@
 //   dQ_i    = scale sum_j dS_ij K_j           dK_j = scale sum_i dS_ij Q_i   (summed over the q heads of a group)
 //
 // Launch sequence (all on the caller's stream):
-//   1. delta_kernel         delta = rowsum(dO * O)
+//   1. dq_kernel            one workgroup per four units of 32 query rows of a head, same tile walk as the forward;
+//                           leaves delta = rowsum(dO * O) and lse * log2(e) of its rows in the workspace
 //   2. dkdv_kernel<GIST>    one workgroup per (compact gist tile, segment of query chunks): the pairs whose
 //                           gist lies left of the query chunk's window phase; fp32 partials to the workspace
 //   3. gist_reduce_kernel   sums the segments of a gist tile in a fixed order
 //   4. dkdv_kernel<WINDOW>  one workgroup per contiguous 128-key tile: the pairs of the window phase; its
 //                           epilogue adds the reduced gist-phase sums to the gist rows and writes dK, dV
-//   5. dq_kernel            one workgroup per four units of 32 query rows of a head, same tile walk as the forward
-// Short backwards run 2, 4 and 5 as one launch (bwd_joint_kernel) and 3 behind it, where it writes the gist rows.
+// Short backwards run 2, 4 and 1 as one launch (bwd_joint_kernel) behind delta_kernel, which computes delta then, and 3
+// behind it, where it writes the gist rows.  Backwards whose dQ is written over an input of the other phases, and stages
+// launched one by one, start with delta_kernel too and end with 1.
 // Every (query, key) pair is handled by exactly one of the two dkdv phases: a query chunk c (64 rows) sees
 // the sinks and gists at positions < far(c) = floor(win_lo(64c) / 128) * 128 in the gist phase (win_lo = first
 // position of a row's local window) and every key >= far(c) in the window phase.
@@ -335,7 +337,8 @@ struct DqSmem {
 // WITH_DELTA = true: the launch runs first and without a delta pass; a wave takes delta and lse * log2(e) of its rows from out
 // and lse and leaves them in the workspace for the dK/dV phases.  The pass reads out and dout for that alone (2 x 268 MB at
 // 32 heads x 32K x 128: 92 us of 8240 for forward and backward, 186 of 6990 for 4 x 16K at r 16); here dout is in registers
-// already and a workgroup reads its 32 KB of out beside its q and dout.
+// already and a workgroup reads its 32 KB of out beside its q and dout.  Both together, pass + dQ / dQ with delta: 91 + 2534 /
+// 2618 us at 32 x 32K x 128 (rows in registers cost dQ most of what the pass took), 4 x 16K forward and backward 6881 / 6788.
 template <int D, bool GEN, bool PACK, bool QSTR = false, bool WITH_DELTA = false>
 __global__ __launch_bounds__(NT, 2) void dq_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                   const bf16_t* __restrict__ v, const bf16_t* __restrict__ out,

@@ -128,12 +128,14 @@ def _exact_group(q, k, v, do, r, W, S, mode):
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,L,D,r,W,S,mode", [
-    (1, 32, 8, 12288, 128, 8, 256, 0, 0), (1, 32, 8, 12289, 128, 8, 256, 0, 0),   # 3072 workgroups of dQ: the line at D = 128
-    (1, 32, 8, 18432, 64, 16, 200, 0, 0), (1, 32, 8, 18433, 64, 16, 200, 0, 0),   # 4608: at D = 64
+    (1, 32, 8, 12288, 128, 8, 256, 0, 0), (1, 32, 8, 12289, 128, 8, 256, 0, 0),   # 3072 workgroups of dQ
+    (1, 32, 8, 18432, 64, 16, 200, 0, 0), (1, 32, 8, 18433, 64, 16, 200, 0, 0),   # 4608
     (1, 32, 8, 12288, 128, 4, 30, 100, 1),                                        # sinks, window in units
     (2, 28, 4, 6000, 96, 4, 300, 70, 0),
     (1, 32, 8, 20480, 128, 8, 256, 0, 0), (1, 32, 8, 20481, 128, 8, 256, 0, 0),   # 5120: the line with groups of heads
     (4, 32, 8, 6144, 64, 16, 200, 0, 0), (4, 32, 8, 6145, 64, 16, 200, 0, 0),     # 6144: at D = 64
+    (1, 32, 32, 12288, 128, 8, 256, 0, 0), (1, 32, 32, 12289, 128, 8, 256, 0, 0),  # 3072: the line without groups
+    (1, 32, 32, 18432, 64, 16, 200, 0, 0), (1, 32, 32, 18433, 64, 16, 200, 0, 0),  # 4608: at D = 64
 ])
 def test_both_sides_of_the_line_against_float64(B, Hq, Hkv, L, D, r, W, S, mode):
     q, k, v, do = (t.cuda() for t in synth.attn_inputs(B, Hq, Hkv, L, D, seed=L))
