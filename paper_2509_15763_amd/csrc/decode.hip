@@ -689,10 +689,15 @@ hipError_t decode_bf16q(const void* q, const void* kc, const void* vc, const flo
     };
     const std::true_type yes;
     const std::false_type no;
-    // an out on q's memory, which a merge writes behind all reads of q, but for the very rows that a workgroup has read itself
-    const size_t row_bytes = (size_t)B * Hq * D * 2;
-    const bool onto_q = out != q && (uintptr_t)out < (uintptr_t)q + row_bytes && (uintptr_t)q < (uintptr_t)out + row_bytes;
-    if (nsplit == 1 && !onto_q) {
+    // A merge writes out and lse behind all reads of the slice kernel.  The direct write does not: where either lies on an input, the
+    // merge stays, but for an out in q's very place, whose rows a workgroup has all read itself.
+    const size_t q_bytes = (size_t)B * Hq * D * 2, slab_bytes = (size_t)B * Hkv * Lk * D * (E4M3 ? 1 : 2);
+    auto on_inputs = [&](const void* dst, size_t bytes, bool own_rows) {
+        auto meets = [&](const void* x, size_t n) { return dst && x && (uintptr_t)x < (uintptr_t)dst + bytes && (uintptr_t)dst < (uintptr_t)x + n; };
+        return (!own_rows && meets(q, q_bytes)) || meets(kc, slab_bytes) || meets(vc, slab_bytes) || meets(seqlens, (size_t)B * sizeof(int)) ||
+               meets(k_scale, (size_t)Hkv * sizeof(float)) || meets(v_scale, (size_t)Hkv * sizeof(float));
+    };
+    if (nsplit == 1 && !on_inputs(out, q_bytes, out == q) && !on_inputs(lse, (size_t)B * Hq * sizeof(float), false)) {
         const DecodeOut res{(bf16_t*)out, lse};
         return ahead ? pick(yes, yes, res) : pick(no, yes, res);
     }

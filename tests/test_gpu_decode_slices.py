@@ -99,6 +99,40 @@ def test_one_slice_writes_the_result_itself(B, Hkv, Lk, D):
         assert torch.equal(torch.isfinite(lse.cpu()), live) and (lse.cpu().double()[live] - l[live]).abs().max() <= 1e-4
 
 
+@pytest.mark.parametrize("what", ["out a row further in q", "out on k", "out on v", "lse on q", "lse on k", "lse on the lengths", "lse on the scales"])
+@pytest.mark.parametrize("e4m3", [False, True])
+def test_one_slice_onto_its_inputs(what, e4m3):
+    # results on memory that other workgroups still read: a merge writes them, behind all reads
+    B, G, Hkv, Lk, D = 32, 4, 8, 300, 128
+    gen = torch.Generator().manual_seed(7)
+    draw = lambda *s: torch.randn(*s, generator=gen).bfloat16()
+    room = lambda t: torch.cat([t.cuda().flatten(), torch.zeros(4 * D, dtype=t.dtype, device="cuda")])  # and four rows more
+    q, k, v = draw(B, G * Hkv, D), draw(B, Hkv, Lk, D), draw(B, Hkv, Lk, D)
+    n = [Lk - 5 * b for b in range(B)]
+    ks, vs = torch.rand(2, Hkv, generator=gen) + 0.5
+    if e4m3:
+        k, v = (u.quantize_e4m3(t.cuda(), s.cuda()).cpu() for t, s in ((k, ks), (v, vs)))
+        o, l = _exact(q, *(t.view(torch.float8_e4m3fn).float() * s.view(-1, 1, 1) for t, s in ((k, ks), (v, vs))), n)
+    else:
+        o, l = _exact(q, k, v, n)
+    qb, kb, vb = (room(t) for t in (q, k, v))
+    aux = lambda t: torch.cat([t.cuda().view(torch.float32), torch.zeros(B * G * Hkv, device="cuda")])
+    nb, ksb, vsb = aux(torch.tensor(n, dtype=torch.int32)), aux(ks), aux(vs)
+    out, lse = torch.empty(B, G * Hkv, D, dtype=torch.bfloat16, device="cuda"), torch.empty(B, G * Hkv, device="cuda")
+    place = lambda buf, like, at=0: buf.view(torch.uint8)[at:at + like.numel() * like.element_size()].view(like.dtype).view(like.shape)
+    if what.startswith("out"):
+        out = place(qb, out, 2 * D) if "q" in what else place(kb if what.endswith("k") else vb, out)
+    elif e4m3 or "scales" not in what:
+        lse = place({"q": qb, "k": kb, "lengths": nb, "scales": vsb}[what.split()[-1]], lse)
+    ws = torch.full((u.unigist_decode_workspace(B, G * Hkv, Hkv, Lk, D, u.UNIGIST_BF16),), 255, dtype=torch.uint8, device="cuda")
+    p = [t.data_ptr() for t in ([qb, kb, vb, ksb, vsb] if e4m3 else [qb, kb, vb])]
+    rest = [out.data_ptr(), lse.data_ptr(), B, G * Hkv, Hkv, Lk, nb.data_ptr(), D]
+    st = [ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream]
+    assert (u.unigist_decode_e4m3(*p, *rest, *st) if e4m3 else u.unigist_decode(*p, *rest, u.UNIGIST_BF16, *st)) == 0
+    # as in test_lengths: codes times scales are the values before, to 3 bits
+    assert (out.cpu().double() - o).abs().max() <= 2e-2 and (lse.cpu().double() - l).abs().max() <= 1e-4
+
+
 @pytest.mark.parametrize("Lk,slices", [(500, 4), (1000, 8), (2000, 16)])  # each combine kernel
 @pytest.mark.parametrize("dt", [torch.bfloat16, torch.float32, "e4m3"])
 @pytest.mark.parametrize("G", [4, 17])  # 17: the vector kernel
