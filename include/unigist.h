@@ -258,7 +258,7 @@ unigist_status unigist_attn_bwd_varlen_strided(const void* q, const void* k, con
  * workspace: unigist_decode_workspace(...) bytes, 256-byte aligned.  The size is larger for a batch of up to 64
  * (sequence, kv head) pairs, whose slices are shorter, than for the next larger ones; such a batch is served with longer
  * slices from a workspace without room for the short ones.  Too small for those as well: UNIGIST_EINVAL.  Slabs of 8192
- * rows and more ask for up to eight slices a sequence and are served with fewer likewise.
+ * rows and more ask for up to eight slices a sequence and are served with as many as fit.
  */
 unigist_status unigist_decode(const void* q, const void* kcache, const void* vcache, void* out,
                               float* lse, int B, int Hq, int Hkv, int Lk_max, const int* seqlens,
@@ -274,8 +274,8 @@ size_t unigist_decode_workspace(int B, int Hq, int Hkv, int Lk_max, int D, unigi
  * UNIGIST_DECODE_NOALLOC_SCRATCH_BYTES bytes in the library's device image, which every GPU the library runs on
  * holds until the process ends (its address on the current device is looked up on the first call there; the
  * stream must belong to the current device).  The call allocates and frees nothing.
- * A problem for which unigist_decode_workspace(...) exceeds that size (not counting the additional slices of long slabs) is
- * refused with UNIGIST_ESCRATCH and nothing is launched (the benchmark's serving shape, 64 sequences x 32 heads x 17 408 keys, needs 2.1 MB).
+ * A problem for which unigist_decode_workspace(...) exceeds that size is refused with UNIGIST_ESCRATCH and nothing is launched.  (The
+ * slices that long slabs take beyond those of the shorter ones never carry the size past that line.)
  * All calls on one GPU share the array: calls that may overlap there (different streams, different host threads)
  * race on it and must be ordered by the caller; calls on one stream are ordered by the stream.  No
  * earlier call's contents enter a result: every slot is written before it is used.

@@ -225,10 +225,9 @@ hipError_t launch_bwd_mfma_pack(const void* q, const void* k, const void* v, con
                                 const AttnShape& s, const int* cu, int ndocs, hipStream_t st);
 bool decode_grouped(int Hq, int Hkv, unigist_dtype dt);
 // slices per sequence of a decode whose workspace has `room` bytes (dt: UNIGIST_E4M3 for bf16
-// queries over E4M3 codes; lengths: the call has seqlens; most of all for bf16 with lengths);
-// those that the built-in scratch array is measured by; and the fewest that a call insists on room for
+// queries over E4M3 codes; lengths: the call has seqlens; most of all for bf16 with lengths), and the fewest that a call
+// insists on room for
 int decode_num_splits(int B, int Hq, int Hkv, int Lk, int D, unigist_dtype dt, size_t room, bool lengths);
-int decode_base_splits(int B, int Hq, int Hkv, int Lk, unigist_dtype dt);
 int decode_least_splits(int B, int Hq, int Hkv, int Lk, unigist_dtype dt);
 // bytes of n slices' partial results (m, l and an accumulator each)
 inline size_t decode_split_bytes(int B, int Hq, int n, int D) {

@@ -622,14 +622,7 @@ int best_splits(long units, int Lk, int min_keys) {
     }
     return best;
 }
-}  // namespace
-
-int decode_least_splits(int B, int Hq, int Hkv, int Lk, unigist_dtype dt) { return best_splits(decode_units(B, Hq, Hkv, dt), Lk, 256); }
-
-int decode_base_splits(int B, int Hq, int Hkv, int Lk, unigist_dtype dt) {
-    const long units = decode_units(B, Hq, Hkv, dt);
-    return best_splits(units, Lk, units <= 64 ? 128 : 256);  // at least as many as with 256 keys
-}
+int base_splits(long units, int Lk) { return best_splits(units, Lk, units <= 64 ? 128 : 256); }  // at least as many as with 256 keys
 
 // One slice of the matrix-core kernel, which then writes the result itself, saves the merge and its launch, 2 to 4 us, and the
 // partial results.  It pays up to three iterations, and longer where the (sequence, kv head) units fill the chip by themselves, the
@@ -644,19 +637,28 @@ bool one_slice(long units, int Lk) {
     return Lk <= 384 || (units >= 128 && Lk <= (whole_rounds ? 8 : 3) * units && Lk <= (units <= 512 ? 4096 : 2048));
 }
 
+}  // namespace
+
+int decode_least_splits(int B, int Hq, int Hkv, int Lk, unigist_dtype dt) { return best_splits(decode_units(B, Hq, Hkv, dt), Lk, 256); }
+
 // Long slabs of bf16 (from 8192 rows) with lengths take up to eight slices, so that the workgroups of the longest sequences end
 // less late, up to 16 rounds of workgroups (slices by the rule above / 8, us: 24 x 20000 206 / 199, 48 x 17408 339 / 325, 64 x 9000 245
 // / 229, 64 x 17408 458 / 427, 120 x 30000 with 8/1 heads 216 / 191, 8 x 12000 54.5 / 50.8; 128 x 10000 with 1 / 4 / 6 slices 508 /
 // 480 / 494).  Shorter ones do not gain (128 x 5000 342 / 350 with two), nor do E4M3 codes, half the bytes (48 ragged x 20000
 // 220 / 202, but 64 full x 17408 377 / 392), nor slabs without lengths (64 x 17408 with four 744 / 745).
+//
+// The additional slices are as many as `room` holds, and no more than the built-in scratch array holds where the slices by the rule
+// above fit it: a call on that array and one on a workspace of the size asked for then sum alike, to the last bit.
 int decode_num_splits(int B, int Hq, int Hkv, int Lk, int D, unigist_dtype dt, size_t room, bool lengths) {
     const long units = decode_units(B, Hq, Hkv, dt);
-    const int base = decode_base_splits(B, Hq, Hkv, Lk, dt);
+    const int base = base_splits(units, Lk);
+    auto bytes = [&](int n) { return decode_split_bytes(B, Hq, n, D); };
     if (lengths && dt == UNIGIST_BF16 && decode_grouped(Hq, Hkv, dt) && Lk >= 8192 && units >= 64) {
-        const int n = (int)std::min<long>(8, 4096 / units);
-        if (n > base && decode_split_bytes(B, Hq, n, D) <= room) return n;
+        const size_t most = bytes(base) <= UNIGIST_DECODE_NOALLOC_SCRATCH_BYTES ? std::min(room, (size_t)UNIGIST_DECODE_NOALLOC_SCRATCH_BYTES) : room;
+        for (int n = (int)std::min<long>(8, 4096 / units); n > base; --n)
+            if (bytes(n) <= most) return n;
     }
-    return decode_split_bytes(B, Hq, base, D) <= room ? base : decode_least_splits(B, Hq, Hkv, Lk, dt);
+    return bytes(base) <= room ? base : decode_least_splits(B, Hq, Hkv, Lk, dt);
 }
 
 namespace {

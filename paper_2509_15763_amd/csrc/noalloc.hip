@@ -50,8 +50,9 @@ extern "C" unigist_status unigist_decode_noalloc(const void* q, const void* kcac
     if (dt != UNIGIST_BF16 && dt != UNIGIST_F32) return UNIGIST_EUNSUPPORTED;
     if (B > 65535 || Hq > 65535) return UNIGIST_EUNSUPPORTED;
     if (!q || !kcache || !vcache || !out) return UNIGIST_EINVAL;
-    if (unigist_decode_workspace(B, Hq, Hkv, Lk_max, D, dt) == 0) return UNIGIST_EUNSUPPORTED;  // head dim the decode kernels are not built for
-    if (decode_split_bytes(B, Hq, decode_base_splits(B, Hq, Hkv, Lk_max, dt), D) > kScratchBytes) return UNIGIST_ESCRATCH;
+    const size_t need = unigist_decode_workspace(B, Hq, Hkv, Lk_max, D, dt);
+    if (need == 0) return UNIGIST_EUNSUPPORTED;   // head dim the decode kernels are not built for
+    if (need > kScratchBytes) return UNIGIST_ESCRATCH;
     void* ws = scratch_of_current_device();
     if (!ws) return UNIGIST_ELAUNCH;
     // The split kernel writes (m, l) of every (sequence, head, slice) and the accumulator of every slice with keys; the

@@ -104,3 +104,22 @@ def test_decode_takes_what_slices_of_256_keys_need(Hq, Hkv, D, Lk):
     if (Hq, Hkv, Lk) == (32, 8, 200):
         # one slice of 256 keys per sequence from 9 sequences on: a buffer for any of those batches serves 8
         assert all(sizes[7][1] <= q < sizes[7][0] for q, _ in sizes[8:12])
+
+
+@pytest.mark.parametrize("Hq,Hkv,D", [(32, 8, 128), (120, 8, 128), (8, 1, 64), (16, 16, 96)])
+def test_additional_slices_keep_within_the_built_in_array(Hq, Hkv, D):
+    """Long slabs ask for more slices than the rule for shorter ones, up to the size of the built-in array where those fit it: what it
+    serves does not depend on them, and an array and a workspace of the size asked for hold the same slices."""
+    scratch = u.unigist_decode_noalloc_scratch_bytes()
+    more = 0
+    for B in (8, 12, 20, 24, 36, 40, 64, 65, 68, 100, 120, 128, 250, 500, 1000):
+        base = lambda Lk: u.unigist_decode_workspace(B, Hq, Hkv, Lk, D, u.UNIGIST_BF16)
+        for Lk in (8192, 12000, 17408, 40000):
+            if base(8191) > scratch:  # the slices of a shorter slab, as many
+                assert u.unigist_decode_noalloc(*([FAKE] * 4), None, B, Hq, Hkv, Lk, None, D, u.UNIGIST_BF16) == 4
+            else:
+                assert base(Lk) <= scratch
+                assert u.unigist_decode_noalloc(*([FAKE] * 4), None, B, Hq, Hkv, Lk, None, D, u.UNIGIST_BF16) != 4
+            assert base(Lk) >= base(8191)
+            more += base(Lk) > base(8191)
+    assert more

@@ -53,6 +53,28 @@ def test_two_calls_second_smaller(dtype):
     _run_both(1, 4, 4, 300, 64, dtype, seed=13, ragged=True)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,Lk,D", [(64, 32, 8, 8200, 128), (20, 120, 8, 8200, 128), (68, 32, 8, 17000, 64)])
+def test_long_slabs_of_unequal_lengths(B, Hq, Hkv, Lk, D):
+    # eight slices a sequence would pass the end of the array: both calls take as many as it holds
+    g = torch.Generator(device="cuda").manual_seed(B)
+    draw = lambda *s: torch.randn(*s, generator=g, device="cuda").bfloat16()
+    q = draw(B, Hq, D)
+    kc, vc = (torch.empty(B, Hkv, Lk, D, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    for b in range(B):
+        kc[b], vc[b] = draw(Hkv, Lk, D), draw(Hkv, Lk, D)
+    n = [Lk - b * (Lk // B) for b in range(B)]
+    sl = torch.tensor(n, dtype=torch.int32, device="cuda")
+    out_a, lse_a = u.decode(q, kc, vc, sl)
+    out_b, lse_b = torch.zeros_like(q), torch.zeros(B, Hq, device="cuda")
+    assert u.unigist_decode_noalloc(q.data_ptr(), kc.data_ptr(), vc.data_ptr(), out_b.data_ptr(), lse_b.data_ptr(), B, Hq, Hkv, Lk,
+                                    sl.data_ptr(), D, u.UNIGIST_BF16, torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(out_a, out_b) and torch.equal(lse_a, lse_b)
+    for b in (0, B // 2, B - 1):
+        o, l = oracle.decode(*(to_np(t[b:b + 1]) for t in (q, kc[:, :, :n[b]], vc[:, :, :n[b]])))
+        assert max_abs(to_np(out_b[b:b + 1]), o) <= TOL_OUT_BF16 and max_abs(to_np(lse_b[b:b + 1]), l) <= TOL_LSE_BF16
+
+
 def test_refuses_what_does_not_fit():
     B, Hq, Hkv, Lk, D = 2048, 32, 8, 4096, 128
     need = u.unigist_decode_workspace(B, Hq, Hkv, Lk, D, u.UNIGIST_BF16)
