@@ -637,15 +637,41 @@ bool one_slice(long units, int Lk) {
     return Lk <= 384 || (units >= 128 && Lk <= (whole_rounds ? 8 : 3) * units && Lk <= (units <= 512 ? 4096 : 2048));
 }
 
+// Slices of a long bf16 slab (from 8192 rows) with lengths.  Lengths may differ, and then more slices let the workgroups of the longest
+// sequences end less late; they may be equal as well, and then every round of workgroups costs 2 to 3 us and one that is not filled
+// much more, while the launch has no tail to gain.  So: as many slices as fill one round of 512 workgroups (two per CU, with loads
+// ahead) up to 128 units, two up to 256, four beyond; or eight, where those fill rounds of 256 better; but where the slices by the rule
+// above fill their rounds, or units alone do, more than those (four, or six for three) only from 16384 rows of 128 columns on, up to
+// 4096 workgroups.  us, rule above without loads ahead / eight slices / this:
+//                                   lengths all equal    spread from 1/16 to 1    one full, the others an eighth
+//   12 x 17408 (5 / 8 / 8)           151 / 150 / 149      119 / 101 / 101           66 /  47 /  47
+//   18 x 17408 (3 / 8 / 7)           228 / 227 / 221      178 / 142 / 140           76 /  52 /  47
+//   13 x 17408 (2 / 8 / 4)           155 / 173 / 160      136 / 105 / 100          123 /  48 /  59
+//   10 x 30000 (3 / 8 / 6)           205 / 220 / 209      163 / 137 / 149          123 /  63 /  70
+//   16 x 17408 (4 / 8 / 4)           198 / 202 / 199      130 / 120 / 124           80 /  55 /  69
+//   32 x 17408 (2 / 8 / 4)           389 / 393 / 389      247 / 226 / 234          146 /  74 /  90
+//   64 x 9000 (2 / 8 / 2)            394 / 407 / 389      253 / 231 / 232          104 /  84 /  91
+//   64 x 17408 (2 / 8 / 4)           749 / 762 / 749      455 / 429 / 438          205 / 131 / 134
+//   80 x 17408 (2 / 6 / 4)           966 / 972 / 961      606 / 520 / 533          229 / 148 / 154
+//   100 x 30000, 8/1 (5 / 8 / 5)     271 / 299 / 272      178 / 166 / 167           81 /  64 /  72
+// At most equal lengths lose 1 % to the rule above, seldom 2 to 3 (10 x 30000; 37 x 9000, 16/4, D 64 65 / 67); 16 x 40000, where the
+// loads ahead cost more, 432 / 450 / 452 against 285 / 273 / 271 for spread ones.
+int uneven_splits(long units, int base, bool long_slab) {
+    auto fill = [&](int n, long round) { return (double)(units * n) / (double)((units * n + round - 1) / round * round); };
+    if (units >= 512 || fill(base, 512) >= 0.95) {
+        const long more = base < 3 ? 4 : base == 3 ? 6 : base;
+        return long_slab ? std::max(base, (int)std::min(more, 4096 / units)) : base;
+    }
+    const int n = std::max(base, (int)((units <= 128 ? 512 : units <= 256 ? 1024 : 2048) / units));
+    return units < 384 && fill(8, 256) > fill(n, 256) ? 8 : n;
+}
 }  // namespace
 
 int decode_least_splits(int B, int Hq, int Hkv, int Lk, unigist_dtype dt) { return best_splits(decode_units(B, Hq, Hkv, dt), Lk, 256); }
 
-// Long slabs of bf16 (from 8192 rows) with lengths take up to eight slices, so that the workgroups of the longest sequences end
-// less late, up to 16 rounds of workgroups (slices by the rule above / 8, us: 24 x 20000 206 / 199, 48 x 17408 339 / 325, 64 x 9000 245
-// / 229, 64 x 17408 458 / 427, 120 x 30000 with 8/1 heads 216 / 191, 8 x 12000 54.5 / 50.8; 128 x 10000 with 1 / 4 / 6 slices 508 /
-// 480 / 494).  Shorter ones do not gain (128 x 5000 342 / 350 with two), nor do E4M3 codes, half the bytes (48 ragged x 20000
-// 220 / 202, but 64 full x 17408 377 / 392), nor slabs without lengths (64 x 17408 with four 744 / 745).
+// E4M3 codes, half the bytes, keep the slices by the general rule: eight cost equal lengths 2 to 4 % and do not reliably help spread
+// ones (us, rule / eight: 64 x 17408 379 / 393 equal, 229 / 231 spread; 16 x 9001 56.0 / 57.4, 39.5 / 40.5; 48 x 20000 335 / 341, 213 /
+// 203).  So do slabs without lengths, all of whose sequences are full.
 //
 // The additional slices are as many as `room` holds, and no more than the built-in scratch array holds where the slices by the rule
 // above fit it: a call on that array and one on a workspace of the size asked for then sum alike, to the last bit.
@@ -654,8 +680,9 @@ int decode_num_splits(int B, int Hq, int Hkv, int Lk, int D, unigist_dtype dt, s
     const int base = base_splits(units, Lk);
     auto bytes = [&](int n) { return decode_split_bytes(B, Hq, n, D); };
     if (lengths && dt == UNIGIST_BF16 && decode_grouped(Hq, Hkv, dt) && Lk >= 8192 && units >= 64) {
+        const int want = uneven_splits(units, base, (long)Lk * padded_head_dim(D) >= 16384 * 128);
         const size_t most = bytes(base) <= UNIGIST_DECODE_NOALLOC_SCRATCH_BYTES ? std::min(room, (size_t)UNIGIST_DECODE_NOALLOC_SCRATCH_BYTES) : room;
-        for (int n = (int)std::min<long>(8, 4096 / units); n > base; --n)
+        for (int n = want; n > base; --n)
             if (bytes(n) <= most) return n;
     }
     return bytes(base) <= room ? base : decode_least_splits(B, Hq, Hkv, Lk, dt);

@@ -55,7 +55,7 @@ def test_two_calls_second_smaller(dtype):
 
 @pytest.mark.parametrize("B,Hq,Hkv,Lk,D", [(64, 32, 8, 8200, 128), (20, 120, 8, 8200, 128), (68, 32, 8, 17000, 64)])
 def test_long_slabs_of_unequal_lengths(B, Hq, Hkv, Lk, D):
-    # eight slices a sequence would pass the end of the array: both calls take as many as it holds
+    # more slices a sequence than shorter slabs take, for 20 sequences up to the end of the array: both calls sum the same ones
     g = torch.Generator(device="cuda").manual_seed(B)
     draw = lambda *s: torch.randn(*s, generator=g, device="cuda").bfloat16()
     q = draw(B, Hq, D)
