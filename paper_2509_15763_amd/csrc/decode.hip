@@ -330,6 +330,12 @@ hipError_t launch_combine(const float* ws, T* out, float* lse, int BH, int nspli
     return hipGetLastError();
 }
 
+// where a launch of one slice per sequence writes its results
+struct DecodeOut {
+    bf16_t* out;
+    float* lse;  // may be null
+};
+
 // ---------------------------------------------------------------------------------------------
 // bf16 queries, cache in bf16 or as E4M3 codes, query groups of up to 15 heads per kv head: the contractions go to the matrix cores
 // (v_mfma_f32_16x16x32_bf16; operand layouts in mfma_common.h), which are idle in this bandwidth-bound op, and the
@@ -357,19 +363,19 @@ hipError_t launch_combine(const float* ws, T* out, float* lse, int BH, int nspli
 // combine, us, without / with: 8 x 12000 ragged 58.6 / 54.4, 16 x 9001 ragged E4M3 43.5 / 41.5, 13 x 5437 at D = 64 35.3 /
 // 30.7, 12 x 30000 ragged E4M3, 8/1 heads, D = 64 20.8 / 16.6, 16 x 700 ragged E4M3 11.8 / 10.6.  It is left out where
 // - a slice is one iteration (1500 keys, one sequence: 8.7 / 8.8), and
-// - more than two bf16 workgroups per CU at D = 128, where its 224 VGPRs allow two instead of three, walk slabs without
-//   lengths: 64 x 17408 745 / 773, 32 x 17408 388 / 392.  Sequences of different lengths end at different times, and there it
-//   pays all the same: 64 ragged of up to 17408 470 / 457, 128 of up to 2000 at D = 96 96 / 89 (100 x 3000, all full: 227 / 224).
+// - bf16 slabs at D = 128 without lengths, all of whose sequences are full, give more than two workgroups per CU (its 224 VGPRs allow two
+//   instead of three: 64 x 17408 745 / 773) or are longer than 10240 rows: 32 x 17408 380 / 397, 16 x 30000 323 / 327, 8 x 20000 114.3 /
+//   115.6, 1 x 131072 94.7 / 95.9 (32 x 9000 200.6 / 197.9, 16 x 6000 71.9 / 71.5; rows of 96 columns gain longer: 10 x 30000, 16/4 heads
+//   82.8 / 81.3).  With lengths it stays: they may all be equal, and then it costs 1 % of a long slab (48 x 17408, four slices 555.5 / 560.3)
+//   and gains 1 to 6 % of a shorter one (64 x 9000 392 / 387, 100 x 1900 148 / 143), and where they are spread it gains more: 48 x 17408 348
+//   / 332, 64 x 9000 253 / 232, 100 x 1900 84 / 81.  One long sequence among short ones gains (48 x 17408 133 / 114) but for short slabs of
+//   many sequences, whose short ones load 128 keys too many (100 x 3000 34 / 40, 128 x 512 12.8 / 14.7).
 // - more than two E4M3 workgroups per CU at D = 128 (three fit instead of four) have short slices: 64 ragged of up to 3000 51.0 / 52.2;
 //   64 x 17408 386 / 378, 48 ragged x 20000 231 / 220.
 // At D = 64 four or five workgroups fit a CU with it: 64 x 17408 393 / 387, 48 ragged x 4000 49.4 / 47.6.
 // Without AHEAD four workgroups per CU are asked for with the 8-bit cache (the compiler's own choice at D = 128, 130 VGPRs,
 // allows three), none with bf16: three, which the registers allow without asking, cost 2 to 4 % of a launch of few slices (us with /
 // without: 4 x 1500 keys 12.9 / 12.5, 8000 14.6 / 14.0) and 1.5 % of 64 x 17408 (750 / 738).
-struct DecodeOut {
-    bf16_t* out;
-    float* lse;  // may be null
-};
 // DIRECT: a launch of one slice per sequence writes the result itself, as the merge of one slice would, and has no merge (us
 // with / without: 120 keys x 8 kv heads 6.8 / 4.8, 100 x 16/4 heads x 200 at D = 64 8.8 / 6.4, 128 x 300 36.5 / 32.8, 128 x 3000
 // 274 / 268).
@@ -654,8 +660,8 @@ bool one_slice(long units, int Lk) {
 //   64 x 17408 (2 / 8 / 4)           749 / 762 / 749      455 / 429 / 438          205 / 131 / 134
 //   80 x 17408 (2 / 6 / 4)           966 / 972 / 961      606 / 520 / 533          229 / 148 / 154
 //   100 x 30000, 8/1 (5 / 8 / 5)     271 / 299 / 272      178 / 166 / 167           81 /  64 /  72
-// At most equal lengths lose 1 % to the rule above, seldom 2 to 3 (10 x 30000; 37 x 9000, 16/4, D 64 65 / 67); 16 x 40000, where the
-// loads ahead cost more, 432 / 450 / 452 against 285 / 273 / 271 for spread ones.
+// Equal lengths lose 1 % at most to the rule above but for 2 to 3 in few places (10 x 30000; 37 x 9000, 16/4 heads, D 64 65 / 67; 16 x
+// 40000 432 / 450 / 452 on one card, 431 / 439 / 435 on another).
 int uneven_splits(long units, int base, bool long_slab) {
     auto fill = [&](int n, long round) { return (double)(units * n) / (double)((units * n + round - 1) / round * round); };
     if (units >= 512 || fill(base, 512) >= 0.95) {
@@ -705,7 +711,8 @@ hipError_t decode_bf16q(const void* q, const void* kc, const void* vc, const flo
     const dim3 grid(nsplit, Hkv, B);
     const bool seg64 = D == padded_head_dim(D);
     const int slice = (Lk + nsplit - 1) / nsplit;  // see AHEAD at the kernel
-    const bool ahead = slice > 128 && (D <= 64 || (long)B * Hkv * nsplit <= 512 || (E4M3 ? slice >= 4096 : seqlens != nullptr));
+    const bool two_per_cu = (long)B * Hkv * nsplit <= 512;
+    const bool ahead = slice > 128 && (D <= 64 || (E4M3 ? two_per_cu || slice >= 4096 : seqlens || (two_per_cu && (!seg64 || Lk <= 10240))));
     auto pick = [&](auto ah, auto direct, auto res) {
         constexpr bool A = decltype(ah)::value, R = decltype(direct)::value;
         auto go = [&](auto kern) {
