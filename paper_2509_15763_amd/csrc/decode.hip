@@ -637,6 +637,12 @@ int base_splits(long units, int Lk) { return best_splits(units, Lk, units <= 64 
 //   24 x 640 ragged 15.2 / 12.7    32 x 1000 29.1 / 26.9    32 x 2200 ragged 38.9 / 37.8     48 x 1500 58.5 / 59.6    48 x 2500 ragged 60 / 65
 //   64 x 600 ragged 27.3 / 21.1    64 x 4000 189 / 181      100 x 1200 ragged 66.6 / 56.4    100 x 2500 189 / 195
 //   E4M3: 32 x 500 15.0 / 10.8, 64 x 2000 56 / 50.5, 100 x 1200 ragged 38.0 / 33.5;  D = 64: 64 x 1500, 16/4 heads 24.0 / 21.0
+// Ragged there: spread evenly from a sixteenth of Lk to Lk.  One full sequence among others of an eighth is walked by one workgroup per
+// kv head, which shows where a slab has 2000 rows and more, and gains elsewhere (us, slices by the rule above / one, for all equal |
+// spread | one full):
+//   32 x 2048 51.8 / 47.0 | 37.8 / 33.3 | 20.7 / 23.5      64 x 4096 184 / 178 | 128 / 113 | 48.8 / 57.9      E4M3 99.6 / 92.2 | 63.5 / 58.2 | 30.8 / 35.8
+//   64 x 1500 73.9 / 67.7 | 52.2 / 43.2 | 22.0 / 22.5      24 x 576  17.5 / 13.1 | 12.9 / 10.1 | 10.2 / 9.3     128 x 2048 184 / 179 | 123 / 114 | 48.0 / 40.1
+// The other two kinds are taken to be the more frequent, so the line does not depend on whether there are lengths.
 // Sizes are asked for and refused by the slices of the other rules.
 bool one_slice(long units, int Lk) {
     const bool whole_rounds = (units + 255) / 256 * 256 <= units * 1.05;
