@@ -92,7 +92,7 @@ BwdPlan sized_plan(const AttnShape& s, int segc) {
     plan_slots(s, p);
     const size_t a = 255;
     size_t off = ((size_t)s.B * s.Hq * s.L * sizeof(float) + a) & ~a;
-    p.off_lse2 = off;  // lse * log2(e), written by the delta pass
+    p.off_lse2 = off;  // lse * log2(e), written with delta by the leading dQ launch or the delta pass
     off += ((size_t)s.B * s.Hq * s.L * sizeof(float) + a) & ~a;
     p.off_part = off;  // one [2][D][BNK] fp32 block per (batch, kv head, segment, compact tile the segment reaches)
     off += (size_t)s.B * s.Hkv * p.slot0[p.nseg] * 2 * padded_head_dim(s.D) * BNK * sizeof(float);
@@ -139,7 +139,7 @@ BwdPlan make_plan(const AttnShape& s, long steps, size_t room, int segc) {
     return p;
 }
 
-// ------------------------------------------------------------------ 1. delta
+// ------------------------------------------------------------------ delta and lse * log2(e) in a pass of their own
 // dO . O of eight columns; the columns are summed in this order and the eights in a tree wherever delta is computed, so that
 // it is the same number to the last bit
 __device__ __forceinline__ float dot8(const u32x4& a, const u32x4& b) {
@@ -326,7 +326,7 @@ __global__ __launch_bounds__(NT) void gist_reduce_pack_kernel(const float* __res
     *(f32x4*)(comp + ((size_t)docs.comp0[d] + t) * per_tile + idx) = acc;
 }
 
-// ------------------------------------------------------------------ 5. dQ
+// ------------------------------------------------------------------ 1. dQ
 template <int D>
 struct DqSmem {
     // two stages of a K tile and a V tile, rows unpadded, 16-byte chunks swizzled
@@ -375,7 +375,7 @@ __global__ __launch_bounds__(NT, 2) void dq_kernel(const bf16_t* __restrict__ q,
 #include "dq_body.inc"
 }
 
-// ------------------------------------------------------------------ 2., 4. and 5. in one launch
+// ------------------------------------------------------------------ 2., 4. and 1. in one launch
 // The three heavy parts of a whole backward need nothing from each other (the window phase leaves its sums of the gist
 // rows in comp for the reduction that follows), so they run as one launch: workgroups 0 .. n_gist-1 are the gist
 // phase, the next n_win the window phase, the rest dQ, whose short walks come last.  What bounds a short backward is not
