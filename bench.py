@@ -9,7 +9,9 @@ already resident in HBM).  The headline value is TFLOP/s counted over the visibl
 (query, key) pairs only: 4*D flops per pair forward, 10*D backward, recompute not counted.
 The backward is issued one stage at a time with HIP events between the stages (all on
 torch's current stream, which is the stream the kernels run on), so every kernel's
-duration is measured live inside the timed region.  The decode op (a serving-path call on
+duration is measured live inside the timed region.  A whole backward call of this size
+launches dQ first, with delta inside it, instead of a delta pass and a dQ behind the other
+stages; it is timed in a region of its own and reported as bwd.whole_call_ms.  The decode op (a serving-path call on
 a different workload: 64 sequences x 17 408 cached keys) is timed in its own region and
 reported beside it with its HBM roofline.  Prints ONE JSON line.
 """
@@ -201,6 +203,20 @@ def main():
     bwd_ms = sum(ms[n] for n in stage_names)
     step_ms = evs[0][0].elapsed_time(evs[-1][6]) / args.steps
 
+    # the backward as a training step calls it, all stages in one call, in its own timed region
+    out, lse = u.attn_fwd(q, k, v, r, W)
+    for _ in range(2):
+        u.attn_bwd(q, k, v, out, lse, dout, r, W, workspace=ws, grads=grads)
+    torch.cuda.synchronize()
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    e0.record()
+    for _ in range(10):
+        u.attn_bwd(q, k, v, out, lse, dout, r, W, workspace=ws, grads=grads)
+    e1.record()
+    torch.cuda.synchronize()
+    whole_bwd_ms = e0.elapsed_time(e1) / 10
+    del out, lse
+
     # dominant kernel and its roofline: algorithmic flops of that launch / its measured duration.
     # dK/dV kernels: S, dP, dV, dK = 8*D per pair they own; dQ kernel: only dQ is new work (2*D per
     # pair), its recomputed S and dP are overhead and not counted.
@@ -354,7 +370,8 @@ def main():
         "pct_of_bf16_peak": 100.0 * value / PEAK_BF16_TFLOPS,
         "fwd": {"ms": fwd_ms, "tflops": flops_fwd / fwd_ms / 1e9, "pct_of_peak": flops_fwd / fwd_ms / 1e9 / PEAK_BF16_TFLOPS * 100},
         "bwd": {"ms": bwd_ms, "tflops": flops_bwd / bwd_ms / 1e9, "pct_of_peak": flops_bwd / bwd_ms / 1e9 / PEAK_BF16_TFLOPS * 100,
-                "stage_ms": {n: ms[n] for n in stage_names}},
+                "stage_ms": {n: ms[n] for n in stage_names}, "stages": "launched one by one: delta first, dQ last, without delta in it",
+                "whole_call_ms": whole_bwd_ms},
         "wall_ms_per_step": wall_ms,
         "roofline": roofline,
         "mfma_sustained": probe or None,
