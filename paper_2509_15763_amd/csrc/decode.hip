@@ -640,13 +640,17 @@ int base_splits(long units, int Lk) { return best_splits(units, Lk, units <= 64 
 // Ragged there: spread evenly from a sixteenth of Lk to Lk.  One full sequence among others of an eighth is walked by one workgroup per
 // kv head, which shows where a slab has 2000 rows and more, and gains elsewhere (us, slices by the rule above / one, for all equal |
 // spread | one full):
-//   32 x 2048 51.8 / 47.0 | 37.8 / 33.3 | 20.7 / 23.5      64 x 4096 184 / 178 | 128 / 113 | 48.8 / 57.9      E4M3 99.6 / 92.2 | 63.5 / 58.2 | 30.8 / 35.8
-//   64 x 1500 73.9 / 67.7 | 52.2 / 43.2 | 22.0 / 22.5      24 x 576  17.5 / 13.1 | 12.9 / 10.1 | 10.2 / 9.3     128 x 2048 184 / 179 | 123 / 114 | 48.0 / 40.1
-// The other two kinds are taken to be the more frequent, so the line does not depend on whether there are lengths.
+//   32 x 2048  51.8 / 47.0 | 39 / 33.4 | 23 / 25.5         64 x 1500  73.4 / 67.9 | 53 / 47 | 21.1 / 21.9
+//   64 x 2048  98.3 / 92.1 | 68.8 / 63.4 | 24.6 / 28.0     64 x 2500  115 / 110 | 77.7 / 75.6 | 30.4 / 33.5
+//   64 x 3000   136 / 132 | 89 / 88 | 32.7 / 39.2          64 x 4096   183 / 177 | 121 / 121 | 40.1 / 52.0
+//   64 x 4096, D = 64  95 / 91 | 61 / 62 | 23 / 27          64 x 4096, E4M3  99.5 / 92 | 68 / 64 | 30.8 / 35.6
+//   24 x 576   17.5 / 13.1 | 12.9 / 10.1 | 10.2 / 9.3      128 x 2048  184 / 179 | 123 / 114 | 48.0 / 40.1
+// So bf16 rows of 128 columns with lengths stay one slice up to 2560 rows: further on the spread ones gain nothing and one full sequence
+// loses 16 to 30 %.  D = 64 (where loads ahead made up for it: 27 before those too) and E4M3 keep the line that full sequences have.
 // Sizes are asked for and refused by the slices of the other rules.
-bool one_slice(long units, int Lk) {
+bool one_slice(long units, int Lk, bool wide_lengths) {
     const bool whole_rounds = (units + 255) / 256 * 256 <= units * 1.05;
-    return Lk <= 384 || (units >= 128 && Lk <= (whole_rounds ? 8 : 3) * units && Lk <= (units <= 512 ? 4096 : 2048));
+    return Lk <= 384 || (units >= 128 && Lk <= (whole_rounds ? 8 : 3) * units && Lk <= (units > 512 ? 2048 : wide_lengths ? 2560 : 4096));
 }
 
 // Slices of a long bf16 slab (from 8192 rows) with lengths.  Lengths may differ, and then more slices let the workgroups of the longest
@@ -711,7 +715,7 @@ hipError_t decode_bf16q(const void* q, const void* kc, const void* vc, const flo
         return D <= 64 ? decode_launch<bf16_t, T, 64>(q, kc, vc, k_scale, v_scale, out, lse, B, Hq, Hkv, Lk, seqlens, D, ws, room, st)
                        : decode_launch<bf16_t, T, 128>(q, kc, vc, k_scale, v_scale, out, lse, B, Hq, Hkv, Lk, seqlens, D, ws, room, st);
     }
-    const int nsplit = one_slice(decode_units(B, Hq, Hkv, UNIGIST_BF16), Lk) ? 1
+    const int nsplit = one_slice(decode_units(B, Hq, Hkv, UNIGIST_BF16), Lk, seqlens && !E4M3 && D > 64) ? 1
                        : decode_num_splits(B, Hq, Hkv, Lk, D, E4M3 ? UNIGIST_E4M3 : UNIGIST_BF16, room, seqlens != nullptr);
     const float scale = 1.0f / sqrtf((float)D);
     const dim3 grid(nsplit, Hkv, B);

@@ -77,10 +77,10 @@ def test_long_slabs(B, D):
                 assert torch.equal(torch.isfinite(lse.cpu()), live) and (lse.cpu().double()[live] - b[live]).abs().max() <= 1e-4
 
 
-@pytest.mark.parametrize("B,Hkv,Lk", [(3, 4, 384), (3, 4, 385), (16, 8, 384), (16, 8, 385), (32, 8, 2048), (32, 8, 2049), (24, 8, 576), (24, 8, 577)])
+@pytest.mark.parametrize("B,Hkv,Lk", [(3, 4, 384), (3, 4, 385), (16, 8, 384), (16, 8, 385), (32, 8, 2048), (32, 8, 2049), (24, 8, 576), (24, 8, 577), (61, 8, 2560), (61, 8, 2561)])
 @pytest.mark.parametrize("D", [128, 40])
 def test_one_slice_writes_the_result_itself(B, Hkv, Lk, D):
-    # both sides of the lines up to which a sequence stays one slice (three iterations; eight or three times the number of units)
+    # both sides of the lines up to which a sequence stays one slice (three iterations; eight or three times the number of units; 2560 rows of 128 columns)
     G = 3
     gen = torch.Generator().manual_seed(Lk + D)
     q = torch.randn(B, G * Hkv, D, generator=gen).bfloat16()
