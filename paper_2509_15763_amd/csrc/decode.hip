@@ -363,19 +363,22 @@ struct DecodeOut {
 // combine, us, without / with: 8 x 12000 ragged 58.6 / 54.4, 16 x 9001 ragged E4M3 43.5 / 41.5, 13 x 5437 at D = 64 35.3 /
 // 30.7, 12 x 30000 ragged E4M3, 8/1 heads, D = 64 20.8 / 16.6, 16 x 700 ragged E4M3 11.8 / 10.6.  It is left out where
 // - a slice is one iteration (1500 keys, one sequence: 8.7 / 8.8), and
-// - bf16 slabs at D = 128 without lengths, all of whose sequences are full, give more than two workgroups per CU (its 224 VGPRs allow two
-//   instead of three: 64 x 17408 745 / 773) or are longer than 10240 rows: 32 x 17408 380 / 397, 16 x 30000 323 / 327, 8 x 20000 114.3 /
+// - bf16 slabs at D = 128 without lengths, all of whose sequences are full, give more than 512 workgroups (64 x 17408 745 / 773) or are
+//   longer than 10240 rows: 32 x 17408 380 / 397, 16 x 30000 323 / 327, 8 x 20000 114.3 /
 //   115.6, 1 x 131072 94.7 / 95.9 (32 x 9000 200.6 / 197.9, 16 x 6000 71.9 / 71.5; rows of 96 columns gain longer: 10 x 30000, 16/4 heads
 //   82.8 / 81.3).  With lengths it stays: they may all be equal, and then it costs 1 % of a long slab (48 x 17408, four slices 555.5 / 560.3)
 //   and gains 1 to 6 % of a shorter one (64 x 9000 392 / 387, 100 x 1900 148 / 143), and where they are spread it gains more: 48 x 17408 348
 //   / 332, 64 x 9000 253 / 232, 100 x 1900 84 / 81.  One long sequence among short ones gains (48 x 17408 133 / 114) but for short slabs of
 //   many sequences, whose short ones load 128 keys too many (100 x 3000 34 / 40, 128 x 512 12.8 / 14.7).
-// - more than two E4M3 workgroups per CU at D = 128 (three fit instead of four) have short slices: 64 ragged of up to 3000 51.0 / 52.2;
+// - more than 512 E4M3 workgroups at D = 128 (three fit a CU instead of four) have short slices: 64 ragged of up to 3000 51.0 / 52.2;
 //   64 x 17408 386 / 378, 48 ragged x 20000 231 / 220.
-// At D = 64 four or five workgroups fit a CU with it: 64 x 17408 393 / 387, 48 ragged x 4000 49.4 / 47.6.
-// Without AHEAD four workgroups per CU are asked for with the 8-bit cache (the compiler's own choice at D = 128, 130 VGPRs,
-// allows three), none with bf16: three, which the registers allow without asking, cost 2 to 4 % of a launch of few slices (us with /
-// without: 4 x 1500 keys 12.9 / 12.5, 8000 14.6 / 14.0) and 1.5 % of 64 x 17408 (750 / 738).
+// At D = 64 three bf16 or five E4M3 workgroups fit a CU with it: 64 x 17408 393 / 387, 48 ragged x 4000 49.4 / 47.6.
+// Registers with bf16 at D = 128, where none are asked for: 224 and 36 accumulation registers with AHEAD, one workgroup per CU; 158
+// and 32 without, two.  How many fit hardly matters with loads ahead: held to two per CU (224 in all), us, one / two: 64 x 17408 equal
+// 745.6 / 747.5, spread 428.0 / 427.7, 24 x 17408 equal 289.3 / 289.5, 32 x 17408 spread 231.8 / 221.2, 100 x 3000 one full among eighths
+// 40.0 / 42.0.  Three without AHEAD cost 2 to 4 % of a launch of few slices (us with / without: 4 x 1500 keys 12.9 / 12.5, 8000 14.6 /
+// 14.0) and 1.5 % of 64 x 17408 (750 / 738).  With the 8-bit cache four are asked for without AHEAD (the compiler's own choice at D =
+// 128, 130 VGPRs, allows three).
 // DIRECT: a launch of one slice per sequence writes the result itself, as the merge of one slice would, and has no merge (us
 // with / without: 120 keys x 8 kv heads 6.8 / 4.8, 100 x 16/4 heads x 200 at D = 64 8.8 / 6.4, 128 x 300 36.5 / 32.8, 128 x 3000
 // 274 / 268).
@@ -655,12 +658,13 @@ bool one_slice(long units, int Lk, bool wide_lengths) {
 
 // Slices of a long bf16 slab (from 8192 rows) with lengths.  Lengths may differ, and then more slices let the workgroups of the longest
 // sequences end less late; they may be equal as well, and then every round of workgroups costs 2 to 3 us and one that is not filled
-// much more, while the launch has no tail to gain.  So: as many slices as fill one round of 512 workgroups (two per CU, with loads
-// ahead) up to 128 units, two up to 256, four beyond; or eight, where those fill rounds of 256 better; but where the slices by the rule
+// much more, while the launch has no tail to gain.  So: as many slices as fill one round of 512 workgroups up to
+// 128 units, two up to 256, four beyond; or eight, where those fill rounds of 256 better; but where the slices by the rule
 // above fill their rounds, or units alone do, more than those (four, or six for three) only from 16384 rows of 128 columns on, up to
 // 4096 workgroups.  us, rule above without loads ahead / eight slices / this:
 //                                   lengths all equal    spread from 1/16 to 1    one full, the others an eighth
 //   12 x 17408 (5 / 8 / 8)           151 / 150 / 149      119 / 101 / 101           66 /  47 /  47
+//   24 x 17408 (4 / 8 / 8)           281 / 288 / 288      196 / 172 / 172           83 /  62 /  62
 //   18 x 17408 (3 / 8 / 7)           228 / 227 / 221      178 / 142 / 140           76 /  52 /  47
 //   13 x 17408 (2 / 8 / 4)           155 / 173 / 160      136 / 105 / 100          123 /  48 /  59
 //   10 x 30000 (3 / 8 / 6)           205 / 220 / 209      163 / 137 / 149          123 /  63 /  70
@@ -670,8 +674,8 @@ bool one_slice(long units, int Lk, bool wide_lengths) {
 //   64 x 17408 (2 / 8 / 4)           749 / 762 / 749      455 / 429 / 438          205 / 131 / 134
 //   80 x 17408 (2 / 6 / 4)           966 / 972 / 961      606 / 520 / 533          229 / 148 / 154
 //   100 x 30000, 8/1 (5 / 8 / 5)     271 / 299 / 272      178 / 166 / 167           81 /  64 /  72
-// Equal lengths lose 1 % at most to the rule above but for 2 to 3 in few places (10 x 30000; 37 x 9000, 16/4 heads, D 64 65 / 67; 16 x
-// 40000 432 / 450 / 452 on one card, 431 / 439 / 435 on another).
+// Equal lengths lose 1 % at most to the rule above but for 2 to 3 in few places (24 x 17408, where four slices would take 283, 175 and
+// 75; 10 x 30000; 37 x 9000, 16/4 heads, D 64 65 / 67; 16 x 40000 432 / 450 / 452 on one card, 431 / 439 / 435 on another).
 int uneven_splits(long units, int base, bool long_slab) {
     auto fill = [&](int n, long round) { return (double)(units * n) / (double)((units * n + round - 1) / round * round); };
     if (units >= 512 || fill(base, 512) >= 0.95) {
