@@ -659,9 +659,11 @@ bool one_slice(long units, int Lk, bool wide_lengths) {
 // Slices of a long bf16 slab (from 8192 rows) with lengths.  Lengths may differ, and then more slices let the workgroups of the longest
 // sequences end less late; they may be equal as well, and then every round of workgroups costs 2 to 3 us and one that is not filled
 // much more, while the launch has no tail to gain.  So: as many slices as fill one round of 512 workgroups up to
-// 128 units, two up to 256, four beyond; or eight, where those fill rounds of 256 better; but where the slices by the rule
-// above fill their rounds, or units alone do, more than those (four, or six for three) only from 16384 rows of 128 columns on, up to
-// 4096 workgroups.  us, rule above without loads ahead / eight slices / this:
+// 128 units, two up to 256, four beyond; or eight, where those fill rounds of 256 better.  Where the slices by the rule above fill
+// their rounds already, they are two for one and six for two to four, whose rounds cost equal lengths 2 % at most; from 16384 rows of
+// 128 columns on, where six cost 1 to 3 %, four for one or two, six for three, up to 4096 workgroups; below 16384 rows of
+// 64 columns, where six cost 2 to 4 %, and beyond 512 units that do not fill their rounds, no more than those.  us, rule above without
+// loads ahead / eight slices, or the most up to 4096 workgroups / this:
 //                                   lengths all equal    spread from 1/16 to 1    one full, the others an eighth
 //   12 x 17408 (5 / 8 / 8)           151 / 150 / 149      119 / 101 / 101           66 /  47 /  47
 //   24 x 17408 (4 / 8 / 8)           281 / 288 / 288      196 / 172 / 172           83 /  62 /  62
@@ -670,17 +672,29 @@ bool one_slice(long units, int Lk, bool wide_lengths) {
 //   10 x 30000 (3 / 8 / 6)           205 / 220 / 209      163 / 137 / 149          123 /  63 /  70
 //   16 x 17408 (4 / 8 / 4)           198 / 202 / 199      130 / 120 / 124           80 /  55 /  69
 //   32 x 17408 (2 / 8 / 4)           389 / 393 / 389      247 / 226 / 234          146 /  74 /  90
-//   64 x 9000 (2 / 8 / 2)            394 / 407 / 389      253 / 231 / 232          104 /  84 /  91
+//   32 x 12000 (2 / 8 / 6)           267 / 269 / 268      185 / 157 / 158           89 /  51 /  48
+//   64 x 9000 (2 / 8 / 6)            391 / 405 / 396      256 / 231 / 229          105 /  85 /  66
+//   64 x 16000 (2 / 8 / 6)           687 / 703 / 692      431 / 391 / 388          187 / 114 / 123
+//   16 x 12000 (4 / 8 / 6)           138 / 138 / 139       96 /  84 /  86           44 /  36 /  35
+//   48 x 12000 (4 / 8 / 6)           394 / 401 / 400      251 / 229 / 226           87 /  72 /  65
+//   85 x 9000, 16/4 (3 / 8 / 6)      264 / 273 / 266      186 / 160 / 159           61 /  58 /  41
+//   64 x 17408, D 64 (2 / 8 / 6)     378 / 383 / 381      238 / 221 / 221          103 /  65 /  59
+//   128 x 9000, D 64 (1 / 4 / 2)     389 / 400 / 388      258 / 231 / 234          105 /  59 /  70
 //   64 x 17408 (2 / 8 / 4)           749 / 762 / 749      455 / 429 / 438          205 / 131 / 134
 //   80 x 17408 (2 / 6 / 4)           966 / 972 / 961      606 / 520 / 533          229 / 148 / 154
 //   100 x 30000, 8/1 (5 / 8 / 5)     271 / 299 / 272      178 / 166 / 167           81 /  64 /  72
-// Equal lengths lose 1 % at most to the rule above but for 2 to 3 in few places (24 x 17408, where four slices would take 283, 175 and
+// Equal lengths lose 2 % at most to the rule above but for 3 in few places (24 x 17408, where four slices would take 283, 175 and
 // 75; 10 x 30000; 37 x 9000, 16/4 heads, D 64 65 / 67; 16 x 40000 432 / 450 / 452 on one card, 431 / 439 / 435 on another).
-int uneven_splits(long units, int base, bool long_slab) {
+// rows: of 128 columns, a row of 64 being half of one
+int uneven_splits(long units, int base, long rows) {
     auto fill = [&](int n, long round) { return (double)(units * n) / (double)((units * n + round - 1) / round * round); };
     if (units >= 512 || fill(base, 512) >= 0.95) {
+        if (rows < 16384) {
+            if (base == 1) return units <= 2048 ? 2 : 1;
+            return base <= 4 && units <= 512 && rows >= 8192 ? 6 : base;
+        }
         const long more = base < 3 ? 4 : base == 3 ? 6 : base;
-        return long_slab ? std::max(base, (int)std::min(more, 4096 / units)) : base;
+        return std::max(base, (int)std::min(more, 4096 / units));
     }
     const int n = std::max(base, (int)((units <= 128 ? 512 : units <= 256 ? 1024 : 2048) / units));
     return units < 384 && fill(8, 256) > fill(n, 256) ? 8 : n;
@@ -700,7 +714,7 @@ int decode_num_splits(int B, int Hq, int Hkv, int Lk, int D, unigist_dtype dt, s
     const int base = base_splits(units, Lk);
     auto bytes = [&](int n) { return decode_split_bytes(B, Hq, n, D); };
     if (lengths && dt == UNIGIST_BF16 && decode_grouped(Hq, Hkv, dt) && Lk >= 8192 && units >= 64) {
-        const int want = uneven_splits(units, base, (long)Lk * padded_head_dim(D) >= 16384 * 128);
+        const int want = uneven_splits(units, base, (long)Lk * padded_head_dim(D) / 128);
         const size_t most = bytes(base) <= UNIGIST_DECODE_NOALLOC_SCRATCH_BYTES ? std::min(room, (size_t)UNIGIST_DECODE_NOALLOC_SCRATCH_BYTES) : room;
         for (int n = want; n > base; --n)
             if (bytes(n) <= most) return n;

@@ -127,8 +127,10 @@ def test_additional_slices_keep_within_the_built_in_array(Hq, Hkv, D):
 
 @pytest.mark.parametrize("B,Hq,Hkv,Lk,D,slices", [
     (64, 32, 8, 17408, 128, 4), (32, 32, 8, 17408, 128, 4), (16, 32, 8, 17408, 128, 4), (128, 32, 8, 17408, 128, 3),  # whole rounds; what the built-in array holds
-    (64, 32, 8, 12000, 128, 2), (32, 32, 8, 16383, 128, 2), (64, 16, 4, 17408, 64, 2), (100, 8, 1, 30000, 128, 5),    # the same, kept
-    (21, 32, 8, 16383, 128, 3), (21, 32, 8, 16384, 128, 6),
+    (64, 32, 8, 12000, 128, 6), (32, 32, 8, 16383, 128, 6), (32, 32, 8, 16384, 128, 4), (64, 16, 4, 16384, 64, 6), (64, 16, 4, 16383, 64, 2),
+    (16, 32, 8, 12000, 128, 6), (48, 32, 8, 12000, 128, 6), (128, 32, 8, 12000, 128, 2), (192, 32, 8, 9000, 64, 2),   # six for two to four, two for one
+    (100, 8, 1, 30000, 128, 5), (90, 32, 8, 10000, 128, 2), (125, 32, 8, 10000, 128, 2), (100, 8, 1, 12000, 128, 5),  # kept
+    (21, 32, 8, 16383, 128, 6), (21, 32, 8, 16384, 128, 6),
     (8, 32, 8, 8192, 128, 8), (10, 32, 8, 9000, 128, 6), (13, 32, 8, 9000, 128, 4), (18, 32, 8, 9000, 128, 7), (12, 32, 8, 9000, 96, 8),
     (44, 32, 8, 9000, 128, 8), (60, 32, 8, 9000, 64, 4), (1000, 32, 8, 17408, 128, 2)])
 def test_slices_of_long_slabs_fill_rounds_of_workgroups(B, Hq, Hkv, Lk, D, slices):
